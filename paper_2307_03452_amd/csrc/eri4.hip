@@ -29,6 +29,7 @@ namespace eri4 {
 void make_boys_table(std::vector<double>& tab);
 void make_rtabs(std::vector<uint32_t>& tab, std::vector<int>& start);
 void make_solid_table(std::vector<double>& tab);
+void make_tile_tables(std::vector<uint32_t>& tab, std::vector<double>& hcoef, TileTableIndex& ix);
 void solid_dense(int l, double* C);
 
 __global__ void reset_counter_kernel(int* counter) {
@@ -154,7 +155,14 @@ struct DeviceState {
   uint2* rtab = nullptr;
   double* stab = nullptr;  // solid-harmonic coefficients (make_solid_table)
   int rstart[2 * (kMaxL + 1)] = {0};  // [layout][L], in uint2 entries
+  uint32_t* ttab = nullptr;  // tables of the Cartesian integral kernels (make_tile_tables)
+  double* hcoef = nullptr;
+  Tables tables() const { return Tables{boys, rtab, ttab, hcoef}; }
 };
+
+// Host copies of the tile tables (built once, read by the plans' cost estimate).
+std::vector<uint32_t> g_ttab;
+TileTableIndex g_tix;
 
 std::mutex g_mu;
 std::deque<DeviceState> g_dev;  // a deque: growing it keeps pointers to existing entries valid
@@ -193,7 +201,9 @@ eri4_status ensure_device(DeviceState** st) {
     static std::vector<uint32_t> rt;
     static std::vector<int> rs;
     static std::vector<double> st;
+    static std::vector<double> hc;
     if (boys.empty()) {
+      make_tile_tables(g_ttab, hc, g_tix);
       make_boys_table(boys);
       make_rtabs(rt, rs);
       make_solid_table(st);
@@ -208,6 +218,11 @@ eri4_status ensure_device(DeviceState** st) {
     if (hipMalloc(&d.stab, st.size() * sizeof(double)) != hipSuccess)
       return fail(ERI4_ERROR_OUT_OF_MEMORY, "device allocation of the solid-harmonic table failed");
     HIP_TRY(hipMemcpy(d.stab, st.data(), st.size() * sizeof(double), hipMemcpyHostToDevice));
+    if (hipMalloc(&d.ttab, g_ttab.size() * sizeof(uint32_t)) != hipSuccess ||
+        hipMalloc(&d.hcoef, hc.size() * sizeof(double)) != hipSuccess)
+      return fail(ERI4_ERROR_OUT_OF_MEMORY, "device allocation of the tile tables failed");
+    HIP_TRY(hipMemcpy(d.ttab, g_ttab.data(), g_ttab.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(d.hcoef, hc.data(), hc.size() * sizeof(double), hipMemcpyHostToDevice));
     for (int i = 0; i < 2 * (kMaxL + 1); ++i) d.rstart[i] = rs[i];
     HIP_TRY(hipGetSymbolAddress((void**)&d.scratch, HIP_SYMBOL(scratch)));
     eri4_status s = set_attrs();
@@ -288,6 +303,79 @@ bool pick_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d,
   for (const auto& o : order)
     if (try_params(la, lb, lc, ld, kmax, o[0], o[1], d, limit, out)) return true;
   return false;
+}
+
+// Parameters of the Cartesian integral kernels for a class (after
+// ensure_device).  Every class with l <= ERI4_MAX_L fits: at most 149 KB.
+TileParams tile_params(int la, int lb, int lc, int ld, int kmax) {
+  TileParams p{};
+  p.la = la; p.lb = lb; p.lc = lc; p.ld = ld;
+  p.nab = ncart(la) * ncart(lb); p.ncd = ncart(lc) * ncart(ld);
+  p.Lb = la + lb; p.Lk = lc + ld; p.L = p.Lb + p.Lk;
+  p.nq = nherm(p.Lk); p.nqb = (p.nq + 15) / 16;
+  p.kb = nuv(p.Lb); p.kk = nuv(p.Lk);
+  p.nr = nherm(p.L); p.nzt = nuv(p.L);
+  p.tbrow = odd_row(p.Lb + 2); p.tkrow = odd_row(p.Lk + 2);
+  p.tbaxis = ((la + 1) * (lb + 1) + 1) * p.tbrow;
+  p.tkaxis = ((lc + 1) * (ld + 1) + 1) * p.tkrow;
+  p.xs = (p.nq + 3) | 1;  // three zero columns; odd: the 16 rows of an operand read fall in different banks
+  p.kmax = kmax;
+  p.shape = tile_shape(p.nqb);
+  const TileShapeInfo sh = kTileShapes[p.shape];
+  const TileTableIndex& ix = g_tix;
+  const TileTableIndex::Side& b = ix.bra[sh.lim][la][lb];
+  const TileTableIndex::Side& k = ix.ket[lc][ld];
+  p.nunits = b.nunits;
+  p.ntiles = (b.nunits + kWaves / sh.cw - 1) / (kWaves / sh.cw);
+  p.nkblk = k.nblocks;
+  p.o_uv = ix.uv; p.o_qcol = ix.qcol[p.Lk]; p.o_task = ix.task[p.L]; p.ntask = ix.ntask[p.L]; p.o_hexp = ix.hexp;
+  p.o_bunit = b.units; p.o_brows = b.rows;
+  p.o_kunit = k.units; p.o_kcols = k.rows; p.o_klist = k.list;
+  p.nks = 0;
+  for (int i = 0; i < b.nunits; ++i) {
+    const uint32_t w = g_ttab[b.units + 8 * i];
+    const int X = (int)(w & 0xff), m0 = p.Lb - X;
+    p.fsize = std::max(p.fsize, (int)((w >> 8) & 0xff) * tile_f_row(m0, p.Lk, m0 + p.Lk + 1, 0));
+    p.nks = std::max(p.nks, ((X + p.Lk) >> 2) + 1);
+  }
+  const int ug = kWaves / sh.cw;  // units per tile
+  int off = kTileKcol + 16 * p.nkblk * 4;
+  p.o_row1 = off;
+  if (ug > 1) off += kTileRowfSize + kTileRfSize;
+  p.o_union = off;
+  p.buf = align16(std::max(p.nr, 3 * p.tbaxis) * 8);
+  p.o_f = off + 2 * p.buf;
+  const int xbytes = align16(16 * tile_xb(sh.cw, sh.nc) * tile_xu(sh.cw, sh.nc) * p.xs * 8);
+  p.o_zt = p.o_f + align16(ug * p.fsize * 8);
+  p.o_kete = std::max(off + xbytes, p.o_zt);
+  p.o_h = p.o_zt + align16(p.nzt * 8);
+  p.o_g = p.o_h + 3 * 64 * h_steps(p.L) * 8;
+  const int ph1 = p.o_g + ug * sh.rb * 64 * p.nks * 8;
+  const int ph2 = p.o_kete + 3 * p.tkaxis * 8;
+  p.lds_bytes = align16(std::max(ph1, ph2));
+  return p;
+}
+
+// Estimated cycles of tile rt of a quartet with kb / kk bra / ket primitive
+// pairs: products, reads over t, and the steps before them per primitive
+// quartet.
+double tile_cost(const TileParams& p, int rt, double kb, double kk) {
+  const TileShapeInfo sh = kTileShapes[p.shape];
+  const int ug = kWaves / sh.cw;
+  double g1 = 0.0, g2 = 0.0, ket = 0.0;
+  auto steps = [](const uint32_t* w) { return (double)((w[1] + 3) / 4); };
+  for (int i = 0; i < ug && rt * ug + i < p.nunits; ++i) {
+    const uint32_t* w = g_ttab.data() + p.o_bunit + 8 * (rt * ug + i);
+    const double np = (w[0] >> 8) & 0xff, nb = w[0] >> 16, X = w[0] & 0xff;
+    g1 = std::max(g1, steps(w) * sh.nc * (128.0 * np * nb + 12.0 * (X + 1)));
+    const uint32_t v = w[7];
+    g2 += (((v & 0xff) + ((v >> 8) & 0xff) + ((v >> 16) & 0xff) + (v >> 24)) + 15) / 16;
+  }
+  for (int i = 0; i < g_tix.ket[p.lc][p.ld].nunits; ++i) {  // for one row block
+    const uint32_t* w = g_ttab.data() + p.o_kunit + 8 * i;
+    ket += steps(w) * (w[0] >> 8) * (64.0 + 16.0 * ((w[0] & 0xff) / 4 + 1)) / 4.0;
+  }
+  return kb * kk * (g1 + 5000.0 + 2.0 * p.nr) + kk * (g2 * ket + 3000.0) + 4000.0;
 }
 
 // The low-l kernels: one wave per quartet for kets of at most four [ab|q]
@@ -389,22 +477,19 @@ eri4_status eri4_batch(int la, int lb, int lc, int ld, int64_t nquartets, const 
       // blocks, one wave otherwise (measured: (ff|ff) 10-16% faster on four
       // waves at K_bra K_ket = 1, 5 and 25; (dd|dd) faster on one wave)
       const bool four = small_four_waves(p);
-      const Tables tb{d->boys, d->rtab};
+      const Tables tb = d->tables();
       const hipError_t e = four ? small4_launch(p, nq, stream, tb, centers, exponents, coeffs, nprim, out, q0)
                                 : small_launch(p, nq, stream, tb, centers, exponents, coeffs, nprim, out, q0);
       if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
     }
     return ERI4_SUCCESS;
   }
-  if (!pick_params(la, lb, lc, ld, kmax, d, kMaxLdsBytes, &p))
-    return fail(ERI4_ERROR_UNSUPPORTED, "class (%d %d|%d %d) does not fit in LDS", la, lb, lc, ld);
-  const int64_t max_blocks = (int64_t)1 << 30;
-  const int64_t qchunk = max_blocks / p.nrt;
+  const TileParams t = tile_params(la, lb, lc, ld, kmax);
+  const int64_t qchunk = ((int64_t)1 << 22) / t.ntiles;  // grid below 2^32 work-items
   for (int64_t q0 = 0; q0 < nquartets; q0 += qchunk) {
-    const int64_t nq = (nquartets - q0 < qchunk) ? nquartets - q0 : qchunk;
-    const dim3 grid((unsigned)(nq * p.nrt));
+    const int64_t nq = std::min(qchunk, nquartets - q0);
     const hipError_t e =
-        fused_launch(p, grid, stream, Tables{d->boys, d->rtab}, centers, exponents, coeffs, nprim, out, q0);
+        fused_launch(t, nq, stream, d->tables(), centers, exponents, coeffs, nprim, out, q0);
     if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
   }
   return ERI4_SUCCESS;
@@ -469,7 +554,7 @@ eri4_status eri4_batch_solid(int la, int lb, int lc, int ld, int64_t nquartets, 
     double* hket = hbra + nq * kmax * kmax * hbs;
     hipError_t e = solid_h_launch(p, nq, stream, centers, exponents, coeffs, nprim, d->stab, hbra, hket, q0, hbs, hks);
     if (e == hipSuccess)
-      e = solid_launch(p, dim3((unsigned)(nq * p.nrt)), stream, Tables{d->boys, d->rtab}, centers, exponents, coeffs,
+      e = solid_launch(p, dim3((unsigned)(nq * p.nrt)), stream, d->tables(), centers, exponents, coeffs,
                        nprim, out, q0, hbra, hket, hbs, hks);
     if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
   }
@@ -551,7 +636,7 @@ static eri4_status coulomb_passes(int la, int lb, int lc, int ld, int64_t nquart
     double* part = work + nq * kk2 * ds;
     hipError_t e = coulomb_dket_launch(p, nq, stream, centers, exponents, coeffs, nprim, dens, work, q0, ds);
     if (e == hipSuccess)
-      e = coulomb_launch(p, nq, stream, Tables{d->boys, d->rtab}, centers, exponents, coeffs, nprim, part, out, q0,
+      e = coulomb_launch(p, nq, stream, d->tables(), centers, exponents, coeffs, nprim, part, out, q0,
                          work, ds);
     if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
   }
@@ -631,7 +716,7 @@ eri4_status eri4_batch_exchange(int la, int lb, int lc, int ld, int64_t nquartet
     const int64_t nq = std::min(chunk, nquartets - q0);
     double* fb = work;
     double* part = work + nq * (int64_t)kmax * kmax * p.nb * fbs;
-    const hipError_t e = exchange_launch(p, nq, stream, Tables{d->boys, d->rtab}, centers, exponents, coeffs, nprim,
+    const hipError_t e = exchange_launch(p, nq, stream, d->tables(), centers, exponents, coeffs, nprim,
                                          dens, fb, fbs, part, out, q0);
     if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
   }
@@ -703,7 +788,8 @@ struct eri4_plan_s {
   int64_t* d_joff = nullptr;   // per bra entry: its J block in out
   int64_t out_size = 0;
   std::vector<int64_t> qoff;
-  ClassParams* d_classes = nullptr;
+  ClassParams* d_classes = nullptr;  // solid and Coulomb plans
+  TileParams* d_tiles = nullptr;     // Cartesian plans
   int2* d_items = nullptr;
   int64_t* d_qoff = nullptr;
   int32_t* d_nprim = nullptr;
@@ -713,6 +799,7 @@ struct eri4_plan_s {
 static void plan_free(eri4_plan_s* p) {
   if (!p) return;
   if (p->d_classes) (void)hipFree(p->d_classes);
+  if (p->d_tiles) (void)hipFree(p->d_tiles);
   if (p->d_items) (void)hipFree(p->d_items);
   if (p->d_qoff) (void)hipFree(p->d_qoff);
   if (p->d_nprim) (void)hipFree(p->d_nprim);
@@ -842,14 +929,23 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   }
   if (solid)
     for (ClassParams& c : cps) to_solid(&c);  // rows and columns over solid functions; same tile and LDS
+  // Cartesian plans run the kernels of eri4_tile.h, whose one layout of [r] and
+  // tiling follow from the class; a tile choice is checked and changes nothing
+  std::vector<TileParams> tps;
+  if (!solid && !coul)
+    for (const auto& k : keys) tps.push_back(tile_params(k[0], k[1], k[2], k[3], kmax));
   p->nclasses = (int)keys.size();
-  for (const ClassParams& c : cps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
+  if (solid || coul)
+    for (const ClassParams& c : cps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
+  else
+    for (const TileParams& c : tps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
 
   // output offsets in input order, and work items with their cost
   p->qoff.resize(nquartets);
   int64_t off = 0;
   std::vector<int2> items;
   std::vector<double> cost;
+  std::map<std::array<int, 3>, std::vector<double>> cost_of;  // Cartesian: per class and primitive pairs, by tile
   for (int64_t q = 0; q < nquartets; ++q) {
     const ClassParams& c = cps[qcls[q]];
     p->qoff[q] = off;
@@ -861,6 +957,20 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
       cost.push_back(kb * kk * (8000.0 + 4.0 * nherm(c.L) + (double)c.np * c.nq / 128.0) +
                      kb * (double)c.nab * c.np / 256.0 + 4000.0);
       items.push_back(make_int2((int)q, qcls[q] << 16));
+      continue;
+    }
+    if (!solid) {
+      const TileParams& t = tps[qcls[q]];
+      auto it = cost_of.find({qcls[q], (int)kb, (int)kk});
+      if (it == cost_of.end()) {
+        std::vector<double> v(t.ntiles);
+        for (int rt = 0; rt < t.ntiles; ++rt) v[rt] = tile_cost(t, rt, kb, kk);
+        it = cost_of.emplace(std::array<int, 3>{qcls[q], (int)kb, (int)kk}, std::move(v)).first;
+      }
+      for (int rt = 0; rt < t.ntiles; ++rt) {
+        cost.push_back(it->second[rt]);
+        items.push_back(make_int2((int)q, rt | (qcls[q] << 16)));
+      }
       continue;
     }
     for (int rt = 0; rt < c.nrt; ++rt) {
@@ -897,6 +1007,7 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   p->grid = (int)std::min<int64_t>(std::max(p->nitems, 1), (int64_t)ncu * per_cu);
 
   const bool ok = hipMalloc(&p->d_classes, std::max<size_t>(1, cps.size()) * sizeof(ClassParams)) == hipSuccess &&
+                  hipMalloc(&p->d_tiles, std::max<size_t>(1, tps.size()) * sizeof(TileParams)) == hipSuccess &&
                   hipMalloc(&p->d_items, std::max<size_t>(1, sorted.size()) * sizeof(int2)) == hipSuccess &&
                   hipMalloc(&p->d_qoff, std::max<int64_t>(1, nquartets) * sizeof(int64_t)) == hipSuccess &&
                   hipMalloc(&p->d_nprim, std::max<int64_t>(1, 4 * nquartets) * sizeof(int32_t)) == hipSuccess &&
@@ -907,6 +1018,8 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   }
   hipError_t e = hipSuccess;
   if (!cps.empty()) e = hipMemcpy(p->d_classes, cps.data(), cps.size() * sizeof(ClassParams), hipMemcpyHostToDevice);
+  if (e == hipSuccess && !tps.empty())
+    e = hipMemcpy(p->d_tiles, tps.data(), tps.size() * sizeof(TileParams), hipMemcpyHostToDevice);
   if (e == hipSuccess && !sorted.empty())
     e = hipMemcpy(p->d_items, sorted.data(), sorted.size() * sizeof(int2), hipMemcpyHostToDevice);
   if (e == hipSuccess && nquartets > 0)
@@ -1031,9 +1144,9 @@ static eri4_status plan_launch(eri4_plan plan, const Shells& shl, double* work, 
                                 plan->d_pn, shl, plan->d_hoff, d->stab, work));
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, plan->d_counter);
   HIP_TRY(hipGetLastError());
-  const PlanArgs a{plan->d_classes, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
+  const PlanArgs a{plan->d_classes, plan->d_tiles, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
                    out};
-  const Tables t{d->boys, d->rtab};
+  const Tables t = d->tables();
   const dim3 grid(plan->grid);
   if (plan->solid)
     HIP_TRY(plan_solid_launch(plan->pairs, grid, plan->lds_bytes, stream, t, a, plan->nbra, plan->d_hoff, work));
@@ -1268,9 +1381,9 @@ eri4_status eri4_plan_execute_coulomb(eri4_plan plan, const double* bra_centers,
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, plan->d_counter);
   HIP_TRY(hipGetLastError());
   const Shells shl{bra_centers, bra_exponents, bra_coeffs, ket_centers, ket_exponents, ket_coeffs, plan->nket};
-  const PlanArgs a{plan->d_classes, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
+  const PlanArgs a{plan->d_classes, plan->d_tiles, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
                    nullptr};
-  HIP_TRY(plan_coulomb_launch(dim3(plan->grid), plan->lds_bytes, stream, Tables{d->boys, d->rtab}, a,
+  HIP_TRY(plan_coulomb_launch(dim3(plan->grid), plan->lds_bytes, stream, d->tables(), a,
                               (int)plan->nbra, plan->kmax, plan->d_pl, plan->d_pn, ket_dens, plan->d_doff,
                               plan->d_dkoff, plan->d_joff, work, work + plan->dket_size, out));
   return ERI4_SUCCESS;

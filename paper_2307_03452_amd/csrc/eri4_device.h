@@ -635,8 +635,8 @@ __device__ __forceinline__ void exch_gemm(const ClassParams& cp, const double* _
 
 // y of this wave's blocks to outq[(b * na + a) * nc + c] (valid a, b, c only).
 template <int NR>
-__device__ __forceinline__ void exch_store(const ClassParams& cp, const d4 (&yacc)[2], double* __restrict__ outq,
-                                           int row0, int wave, int lane) {
+__device__ __forceinline__ void exch_store(const ClassParams& cp, const d4 (&yacc)[2], double scale,
+                                           double* __restrict__ outq, int row0, int wave, int lane) {
   const int g = lane >> 4, n = lane & 15;
   const int ncc = (cp.nc + 15) / 16;
 #pragma unroll
@@ -649,7 +649,7 @@ __device__ __forceinline__ void exch_store(const ClassParams& cp, const d4 (&yac
     for (int jj = 0; jj < 4; ++jj) {
       int ia, ib;
       exch_row(cp, row0 + r * 16 + acc_row<false>(jj, g), ia, ib);
-      if (ia < cp.na && ib < cp.nb && ic < cp.nc) outq[((int64_t)ib * cp.na + ia) * cp.nc + ic] = yacc[i][jj];
+      if (ia < cp.na && ib < cp.nb && ic < cp.nc) outq[((int64_t)ib * cp.na + ia) * cp.nc + ic] = yacc[i][jj] * scale;
     }
   }
 }
@@ -686,34 +686,54 @@ __device__ __forceinline__ void hermite_base(const Lds& s, int L, const double* 
 
 constexpr int kGroup = 4;  // output column blocks per second-transform pass
 
-// Power-of-two scale of [0]^(m) for the ket pair in s.kpair (FP32 transforms
-// only; 1 otherwise), into kpair[11] and its inverse into kpair[12].  The scale
-// brings the largest product of bra and ket pair weights near 1 so that the
-// FP32 operands of both transforms stay inside FP32's exponent range for
-// quartets with tiny integrals; the output write divides it out.
-template <bool F32>
-__device__ __forceinline__ void ket_scale(const Lds& s, int kmax, int Ka, int Kb) {
-  if constexpr (F32) {
-    const double* A = s.sh;
-    const double* B = s.sh + 3;
-    const double* ex = s.sh + 12;
-    const double* co = s.sh + 12 + 4 * kmax;
-    double ab2 = 0.0;
-    for (int x = 0; x < 3; ++x) ab2 += (A[x] - B[x]) * (A[x] - B[x]);
-    double wmax = 0.0;
-    for (int ij = 0; ij < Ka * Kb; ++ij) {
-      const int i = ij / Kb, j = ij - (ij / Kb) * Kb;
-      const double za = ex[i], zb = ex[kmax + j];
-      wmax = fmax(wmax, fabs(co[i] * co[kmax + j]) * exp(-za * zb / (za + zb) * ab2));
-    }
-    const double wq = wmax * fabs(s.kpair[1]);
-    const int e = (wq > 0.0 && wq < INFINITY) ? max(-1020, min(1020, ilogb(wq))) : 0;
-    s.kpair[11] = ldexp(1.0, -e);
-    s.kpair[12] = ldexp(1.0, e);
-  } else {
-    s.kpair[11] = 1.0;
-    s.kpair[12] = 1.0;
+// Power-of-two scale of [0]^(m) for the ket pair in kpair with FP32 transforms,
+// into kpair[11] and its inverse into kpair[12].  The scale brings the largest
+// product of bra and ket pair weights near 1 so that the FP32 operands of both
+// transforms stay inside FP32's exponent range for quartets with tiny integrals;
+// the output write divides it out.  sh: shell data (load_shells).
+__device__ __forceinline__ void fp32_scale(const double* sh, double* kpair, int kmax, int Ka, int Kb) {
+  const double* A = sh;
+  const double* B = sh + 3;
+  const double* ex = sh + 12;
+  const double* co = sh + 12 + 4 * kmax;
+  double ab2 = 0.0;
+  for (int x = 0; x < 3; ++x) ab2 += (A[x] - B[x]) * (A[x] - B[x]);
+  double wmax = 0.0;
+  for (int ij = 0; ij < Ka * Kb; ++ij) {
+    const int i = ij / Kb, j = ij - (ij / Kb) * Kb;
+    const double za = ex[i], zb = ex[kmax + j];
+    wmax = fmax(wmax, fabs(co[i] * co[kmax + j]) * exp(-za * zb / (za + zb) * ab2));
   }
+  const double wq = wmax * fabs(kpair[1]);
+  const int e = (wq > 0.0 && wq < INFINITY) ? max(-1020, min(1020, ilogb(wq))) : 0;
+  kpair[11] = ldexp(1.0, -e);
+  kpair[12] = ldexp(1.0, e);
+}
+
+// FP64 transforms: the binary exponent of the largest Gaussian product
+// prefactor of the quartet whose shells are in sh where that is below -600, else
+// 0.  [0]^(m) carries its inverse and the output write restores it, so that the
+// steps between work on normal numbers: subnormal values carry few bits, and the
+// transforms amplify what their rounding loses by up to 1e6.  The largest
+// prefactor of a pair is that of its smallest exponents.
+__device__ __forceinline__ int tiny_exponent(const double* sh, int kmax, int Ka, int Kb, int Kc, int Kd) {
+  const double* ex = sh + 12;
+  double arg = 0.0;
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    const int n1 = side ? Kc : Ka, n2 = side ? Kd : Kb;
+    const double* e1 = ex + 2 * side * kmax;
+    double z1 = e1[0], z2 = e1[kmax], r2 = 0.0;
+    for (int i = 1; i < n1; ++i) z1 = fmin(z1, e1[i]);
+    for (int i = 1; i < n2; ++i) z2 = fmin(z2, e1[kmax + i]);
+    for (int x = 0; x < 3; ++x) {
+      const double d = sh[6 * side + x] - sh[6 * side + 3 + x];
+      r2 += d * d;
+    }
+    arg += z1 * z2 / (z1 + z2) * r2;
+  }
+  const double e = -1.4426950408889634 * arg;  // log2
+  return e < -600.0 ? (int)fmax(e, -900.0) : 0;  // (room for the coefficients)
 }
 
 // Everything a workgroup does after its prologue, for NR valid row blocks and
@@ -785,6 +805,7 @@ __device__ __forceinline__ void fused_body(const ClassParams& cp, const Lds& s, 
   }
   const int ncbw = (wave < cp.ncdb) ? (cp.ncdb - wave + 7) / 8 : 0;  // output column blocks of this wave
 
+  const int e2 = EXCH ? tiny_exponent(s.sh, kmax, Ka, Kb, Kc, Kd) : 0;
   StageClock clk;
   clk.start();
   // EXCH: y blocks (row block, 16 columns c) of this wave, kept over the ket pairs
@@ -794,7 +815,7 @@ __device__ __forceinline__ void fused_body(const ClassParams& cp, const Lds& s, 
     if (tid == 0) {
       const int k = kl / Kd, l = kl - (kl / Kd) * Kd;
       make_pair(s.kpair, ex[2 * kmax + k], ex[3 * kmax + l], co[2 * kmax + k], co[3 * kmax + l], C, D);
-      ket_scale<F32>(s, kmax, Ka, Kb);
+      s.kpair[11] = EXCH ? ldexp(1.0, -e2) : 1.0;
     }
     typename Acc<F32>::type acc1[NR][NC1A];
 #pragma unroll
@@ -900,7 +921,7 @@ __device__ __forceinline__ void fused_body(const ClassParams& cp, const Lds& s, 
     ERI4_STAGE(kStGemm2);
   }
   clk.flush(tid);
-  if constexpr (EXCH) exch_store<NR>(cp, yacc, outq, row0, wave, lane);
+  if constexpr (EXCH) exch_store<NR>(cp, yacc, ldexp(1.0, e2), outq, row0, wave, lane);
 }
 
 // Shell data of quartet q into LDS: centres A B C D in sh[0..11], then the
@@ -1047,24 +1068,6 @@ __device__ __forceinline__ void process_tile(const ClassParams& cp, unsigned cha
 #undef BODY
 }
 
-// One workgroup = one quartet x one tile of RB*16 bra rows; 8 waves.  Grid:
-// quartets q0.. in order, cp.nrt tiles each.
-template <int RB, int LAY>
-__global__ __launch_bounds__(kThreads, 1) void eri4_fused_kernel(
-    const ClassParams cp, const double* __restrict__ boys_tab, const uint2* __restrict__ rtab,
-    const double* __restrict__ centers, const double* __restrict__ exps,
-    const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ out,
-    int64_t q0) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (SGPR)
-  const int64_t q = q0 + blockIdx.x / cp.nrt;
-  const int rt = blockIdx.x % cp.nrt;
-  process_tile<RB, LAY, false, false>(cp, lds, boys_tab, rtab + cp.rtab_off, centers, exps, coefs, nprim,
-                                      out + q * (int64_t)cp.nab * cp.ncd, q, rt, tid, wave, lane, nullptr,
-                                      nullptr, nullptr, 0);
-}
-
 // Solid-harmonic output, one class: as eri4_fused_kernel with rows and columns
 // over real solid harmonics (cp.nab = (2la+1)(2lb+1), cp.ncd = (2lc+1)(2ld+1)).
 // The H matrices of quartet q0 + i sit at hbra + i * kmax^2 * hbs and
@@ -1086,89 +1089,6 @@ __global__ __launch_bounds__(kThreads, 1) void eri4_solid_kernel(
                                             out + q * (int64_t)cp.nab * cp.ncd, q, rt, tid, wave, lane, nullptr,
                                             nullptr, nullptr, 0, hbra + i * kk2 * hbs, hket + i * kk2 * hks, hbs,
                                             hks);
-}
-
-// Persistent kernel for a plan: work items {quartet, row tile | class << 16},
-// largest first, taken from a device counter until none are left (every
-// workgroup exits once the counter passes nitems).  qoff[q] is where quartet
-// q's integrals start in out.  Each class brings its own tile height and R
-// layout.  F32: both transforms on FP32 matrix cores (eri4_plan_create).
-template <bool F32, bool PAIRS>
-__global__ __launch_bounds__(kThreads, 1) void eri4_plan_kernel(
-    const ClassParams* __restrict__ classes, const int2* __restrict__ items, int nitems,
-    const int64_t* __restrict__ qoff, const int32_t* __restrict__ nprim, int* __restrict__ counter,
-    const double* __restrict__ boys_tab, const uint2* __restrict__ rtab,
-    const double* __restrict__ centers, const double* __restrict__ exps,
-    const double* __restrict__ coefs, double* __restrict__ out, const double* __restrict__ kcenters,
-    const double* __restrict__ kexps, const double* __restrict__ kcoefs, int64_t nket) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  __shared__ int next_item;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (;;) {
-    if (tid == 0) next_item = atomicAdd(counter, 1);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(next_item);
-    __syncthreads();
-    if (it >= nitems) break;
-    const int2 w = items[it];
-    const int q = __builtin_amdgcn_readfirstlane(w.x);
-    const int rc = __builtin_amdgcn_readfirstlane(w.y);
-    const ClassParams cp = classes[rc >> 16];
-    const int rt = rc & 0xffff;
-    const uint2* rt_L = rtab + cp.rtab_off;
-    double* oq = out + qoff[q];
-    const int lay = cp.lay;
-    if (lay == kLaySlab) {
-      if (cp.rb == 2)
-        process_tile<2, kLaySlab, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-      else
-        process_tile<1, kLaySlab, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-    } else if (lay == kLayBox2) {
-      if (cp.rb == 4)
-        process_tile<4, kLayBox2, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-      else if (cp.rb == 2)
-        process_tile<2, kLayBox2, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-      else
-        process_tile<1, kLayBox2, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-    } else {
-      if (cp.rb == 4)
-        process_tile<4, kLayBox, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-      else if (cp.rb == 2)
-        process_tile<2, kLayBox, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-      else
-        process_tile<1, kLayBox, F32, PAIRS>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave,
-                                              lane, kcenters, kexps, kcoefs, nket);
-    }
-  }
-}
-
-template <bool F32, bool PAIRS>
-hipError_t plan_set_attrs_t() {
-  return hipFuncSetAttribute((const void*)eri4_plan_kernel<F32, PAIRS>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             kMaxLdsBytes - 64);
-}
-
-template <bool F32, bool PAIRS>
-hipError_t plan_occupancy_t(int lds_bytes, int* per_cu) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void*)eri4_plan_kernel<F32, PAIRS>, kThreads,
-                                                      lds_bytes);
-}
-
-template <bool F32, bool PAIRS>
-hipError_t plan_launch_t(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a) {
-  const Shells& h = a.shells;
-  hipLaunchKernelGGL((eri4_plan_kernel<F32, PAIRS>), grid, dim3(kThreads), lds_bytes, s, a.classes, a.items,
-                     a.nitems, a.qoff, a.nprim, a.counter, t.boys, t.rtab, h.centers, h.exps, h.coefs, a.out,
-                     h.kcenters, h.kexps, h.kcoefs, h.nket);
-  return hipGetLastError();
 }
 
 template <int RB, int LAY>

@@ -1,25 +1,40 @@
-// eri4_fused.hip -- the single-class fused kernels (FP64), one instance per
-// tile height (16, 32 or, with a box layout, 64 rows) and R layout (box,
-// slab, two boxes).
-#include "eri4_device.h"
+// eri4_fused.hip -- the single-class Cartesian kernels (FP64), one instance per
+// kernel shape.
+#include "eri4_tile.h"
 
 namespace eri4 {
 
 namespace {
-template <int RB, int LAY>
-hipError_t launch_one(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
+
+// One workgroup = one quartet x one tile of bra rows; 8 waves.  Tiles come in
+// order of decreasing work, so the grid runs over the quartets first.
+template <class S>
+__global__ __launch_bounds__(kThreads, 1) void eri4_fused_kernel(
+    const TileParams cp, const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps,
+    const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ out, int64_t q0,
+    unsigned nq) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (SGPR)
+  const int rt = (int)(blockIdx.x / nq);
+  const int64_t q = q0 + (blockIdx.x - rt * nq);
+  tile_body<S, false, false>(cp, lds, tb, centers, exps, coefs, nprim, out + q * (int64_t)cp.nab * cp.ncd, q, rt, tid,
+                             wave, lane, nullptr, nullptr, nullptr, 0);
+}
+
+template <class S>
+hipError_t launch_one(const TileParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
                       const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0) {
-  hipLaunchKernelGGL((eri4_fused_kernel<RB, LAY>), grid, dim3(kThreads), p.lds_bytes, s, p, t.boys, t.rtab, centers,
-                     exps, coefs, nprim, out, q0);
+  hipLaunchKernelGGL((eri4_fused_kernel<S>), dim3((unsigned)(nq * p.ntiles)), dim3(kThreads), p.lds_bytes, s, p, t,
+                     centers, exps, coefs, nprim, out, q0, (unsigned)nq);
   return hipGetLastError();
 }
 }  // namespace
 
 hipError_t fused_set_attrs() {
-  const void* k[8] = {(const void*)eri4_fused_kernel<1, kLayBox>,  (const void*)eri4_fused_kernel<2, kLayBox>,
-                      (const void*)eri4_fused_kernel<4, kLayBox>,  (const void*)eri4_fused_kernel<1, kLaySlab>,
-                      (const void*)eri4_fused_kernel<2, kLaySlab>, (const void*)eri4_fused_kernel<1, kLayBox2>,
-                      (const void*)eri4_fused_kernel<2, kLayBox2>, (const void*)eri4_fused_kernel<4, kLayBox2>};
+#define B(I, CW, RB, NC) (const void*)eri4_fused_kernel<TileShape<CW, RB, NC>>,
+  const void* k[] = {ERI4_TILE_SHAPES(B)};
+#undef B
   for (const void* f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     if (e != hipSuccess) return e;
@@ -27,22 +42,15 @@ hipError_t fused_set_attrs() {
   return hipSuccess;
 }
 
-hipError_t fused_launch(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
+hipError_t fused_launch(const TileParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
                         const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0) {
-  const bool two = p.rb == 2;
-  switch (p.lay) {
-    case kLaySlab:
-      return two ? launch_one<2, kLaySlab>(p, grid, s, t, centers, exps, coefs, nprim, out, q0)
-                 : launch_one<1, kLaySlab>(p, grid, s, t, centers, exps, coefs, nprim, out, q0);
-    case kLayBox2:
-      if (p.rb == 4) return launch_one<4, kLayBox2>(p, grid, s, t, centers, exps, coefs, nprim, out, q0);
-      return two ? launch_one<2, kLayBox2>(p, grid, s, t, centers, exps, coefs, nprim, out, q0)
-                 : launch_one<1, kLayBox2>(p, grid, s, t, centers, exps, coefs, nprim, out, q0);
-    default:
-      if (p.rb == 4) return launch_one<4, kLayBox>(p, grid, s, t, centers, exps, coefs, nprim, out, q0);
-      return two ? launch_one<2, kLayBox>(p, grid, s, t, centers, exps, coefs, nprim, out, q0)
-                 : launch_one<1, kLayBox>(p, grid, s, t, centers, exps, coefs, nprim, out, q0);
+  switch (p.shape) {
+#define B(I, CW, RB, NC) \
+  case I: return launch_one<TileShape<CW, RB, NC>>(p, nq, s, t, centers, exps, coefs, nprim, out, q0);
+    ERI4_TILE_SHAPES(B)
+#undef B
   }
+  return hipErrorInvalidValue;
 }
 
 #ifdef ERI4_STAGE_TIMERS

@@ -91,6 +91,29 @@ __host__ __device__ constexpr int solid_h_lds(int l1, int l2, int nk4) {
 // than 512 (la + lb >= 13).
 constexpr int kJw = 1024;
 
+// Layout of W (one value per [r]) in the Cartesian integral kernels
+// (eri4_tile.h): nherm(L) values, rows of t = 0..L-s for each (u, v), the rows in order of
+// increasing s = u + v and then u.  Row (u, v) starts at tile_r_base(L, s) +
+// u (L + 1 - s), so that the row of a sum of two (u, v) follows from the sums
+// of their s and u.
+__host__ __device__ constexpr int tile_r_base(int L, int s) { return s * (s + 1) * (3 * (L + 1) - 2 * (s - 1)) / 6; }
+// (u, v) with u + v <= n.
+__host__ __device__ constexpr int nuv(int n) { return (n + 1) * (n + 2) / 2; }
+// Layout of F (eri4_tile.h) of a row group with u + v <= m0 in the bra: rows
+// (u, v) as in [r], s = u + v <= m0 + Lk, of t = 0..min(Lk, m0 + Lk - s).  With s
+// = m0 + Lk + 1 and u = 0: the number of values.
+__host__ __device__ constexpr int tile_f_row(int m0, int Lk, int s, int u) {
+  return s <= m0 ? (Lk + 1) * (nuv(s - 1) + u)
+                 : (Lk + 1) * nuv(m0) + tile_r_base(m0 + Lk, s) - tile_r_base(m0 + Lk, m0 + 1) + u * (m0 + Lk + 1 - s);
+}
+// Steps of 64 of the per-axis tables (eri4_tile.h): rows 0..15, and from 16 to L.
+__host__ __device__ constexpr int h_steps(int L) { return L < 16 ? (L >> 2) + 1 : (L >> 2) + 3; }
+// Row blocks moved to the LDS tile at a time: with five or more column blocks
+// per wave over eight waves (lc + ld >= 13) 32 rows of [ab|q] do not fit.
+__host__ __device__ constexpr int tile_xb(int cw, int nc) { return cw == 8 && nc >= 5 ? 1 : 2; }
+// Units whose rows it holds: both of a tile where they fit (lc + ld <= 9).
+__host__ __device__ constexpr int tile_xu(int cw, int nc) { return cw == 4 && nc <= 4 ? 2 : 1; }
+
 // LDS of one compute unit (gfx950).
 constexpr int kMaxLdsBytes = 160 * 1024;
 
@@ -143,6 +166,80 @@ struct ClassParams {
   int o_ptab, o_qtab, o_base, o_shell;
   int o_jw;      // Coulomb (J-engine) kernels: the Hermite-space J vector w
   int lds_bytes;
+};
+
+// The same for the Cartesian integral kernels (eri4_tile.h).  Table offsets
+// o_uv..o_klist are in words of the tile tables (make_tile_tables).
+struct TileParams {
+  int la, lb, lc, ld;
+  int nab, ncd;
+  int Lb, Lk, L;
+  int nq;              // Hermite functions of the ket
+  int nqb;             // 16-wide column blocks of [ab|q]
+  int kb, kk;          // (u, v) of the bra and the ket: nuv(Lb), nuv(Lk)
+  int nr, nzt;         // values of W and of zt (eri4_tile.h)
+  int nks;             // steps of G, at most
+  int tbrow, tkrow;    // 1-d E table row lengths
+  int tbaxis, tkaxis;  // doubles per axis of the bra / ket tables (incl. zero row)
+  int xs;              // row stride (doubles) of the [ab|q] tile in LDS
+  int kmax;
+  int shape;           // kernel shape (tile_shape)
+  int nunits, ntiles;  // bra units, and tiles of them
+  int nkblk;           // 16-wide column blocks of (ab|cd), grouped by (cx, dx)
+  int ntask;           // wave tasks of W
+  int o_uv, o_qcol, o_task, o_hexp;
+  int o_bunit, o_brows, o_kunit, o_kcols, o_klist;
+  // LDS layout (byte offsets)
+  int o_row1;   // row tables of the second unit of a tile
+  int o_union;  // two buffers of buf bytes (bra tables; W), F, then zt, the per-axis tables and G; or the [ab|q]
+                // tile and, past F too, the ket tables
+  int o_f, o_zt, o_h, o_g, o_kete, buf;
+  int fsize;  // doubles of F per unit, at most
+  int lds_bytes;
+};
+
+// LDS of the Cartesian integral kernels: the small tables sit at fixed places,
+// sized for the largest class (scalar registers for their offsets would spill).
+constexpr int kTileShell = 0;                                             // centres, exponents, coefficients, lengths
+constexpr int kTileBase = kTileShell + (12 + 8 * 16) * 8 + 16;            // [0]^(m) (32), ket pair (16), output rows
+constexpr int kTileRowfSize = ((kMaxL + 1) * (kMaxL + 1) * 2 + 15) / 16 * 16;
+constexpr int kTileRfSize = (nuv(kMaxL) * 4 + 15) / 16 * 16;
+constexpr int kTileRowt = kTileBase + 80 * 8;              // row starts of W by (u, v)
+constexpr int kTileRowf = kTileRowt + kTileRowfSize;       // and of F
+constexpr int kTileRf = kTileRowf + kTileRowfSize;         // rows of F in order
+constexpr int kTileRs = kTileRf + kTileRfSize;             // rows of W in order
+constexpr int kTileRv = kTileRs + kTileRfSize;             // their u, v
+constexpr int kTileBtab = kTileRv + (nuv(kMaxL) * 2 + 15) / 16 * 16;  // (u, v) of the bra
+constexpr int kTileKtab = kTileBtab + (nuv(2 * kTableLMax) + 1) * 16;  // (u, v) of the ket
+constexpr int kTileKcol = kTileKtab + (nuv(2 * kTableLMax) + 1) * 16;  // columns of the ket
+
+// Kernel shapes by the number of [ab|q] column blocks: waves per row of column
+// blocks, bra row blocks per unit, column blocks per wave, limits of a unit
+// (kTileUnitLimits).  Four waves per row (two units of bra rows per tile) where
+// eight would leave more of them without a column block; units of two row blocks
+// where three would need more than 96 accumulator registers (four blocks of four
+// columns, 128 registers, spilled 350 and saved one unit of 34 for (ii|)).
+struct TileShapeInfo { int cw, rb, nc, lim; };
+constexpr TileShapeInfo kTileShapes[9] = {{4, 3, 1, 0}, {4, 3, 2, 0}, {4, 3, 3, 0}, {4, 3, 4, 1}, {4, 2, 5, 2},
+                                          {8, 3, 3, 3}, {8, 3, 4, 3}, {8, 2, 5, 4}, {8, 2, 6, 4}};
+// What a unit of bra rows may hold, for kets up to order Lk: blocks, and doubles of
+// F of its groups together (LDS).
+struct TileUnitLimits { int Lk, rb, fmax; };
+constexpr int kTileLimits = 5;
+constexpr TileUnitLimits kTileUnitLimits[kTileLimits] = {{8, 3, 3200}, {9, 3, 3200}, {10, 2, 3600}, {12, 3, 5200},
+                                                         {14, 2, 4400}};
+constexpr int tile_shape(int nqb) {
+  return nqb <= 16 ? (nqb + 3) / 4 - 1 : (nqb <= 20 ? 4 : (nqb + 7) / 8 + 2);
+}
+
+// Where the tables of the Cartesian integral kernels start (make_tile_tables),
+// in words: per order n, and per shell pair (l1, l2) as bra or ket.
+struct TileTableIndex {
+  int uv, hexp;
+  int qcol[2 * kTableLMax + 1], task[kMaxL + 1], ntask[kMaxL + 1];
+  struct Side {
+    int nunits, nblocks, units, rows, list;
+  } bra[kTileLimits][kTableLMax + 1][kTableLMax + 1], ket[kTableLMax + 1][kTableLMax + 1];
 };
 
 }  // namespace eri4

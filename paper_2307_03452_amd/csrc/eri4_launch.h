@@ -15,11 +15,14 @@ namespace eri4 {
 struct Tables {
   const double* boys;
   const uint2* rtab;
+  const uint32_t* ttab;  // tables of the Cartesian integral kernels (make_tile_tables)
+  const double* hcoef;   // coefficients of their per-axis tables
 };
 
-// The single-class fused kernels (one launch per class and quartet chunk).
+// The single-class Cartesian kernels: quartets q0..q0+nq-1, one workgroup per
+// tile, the tiles of most work first.
 hipError_t fused_set_attrs();
-hipError_t fused_launch(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
+hipError_t fused_launch(const TileParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
                         const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0);
 
 // One wave per quartet (eri4_small.hip) for classes whose shells all have
@@ -81,7 +84,8 @@ struct Shells {
 // The persistent plan kernel, with FP64 or FP32 transforms (f64 / f32), shells
 // from per-quartet arrays or, with the suffix p, from pair lists.
 struct PlanArgs {
-  const ClassParams* classes;
+  const ClassParams* classes;  // solid and Coulomb plans
+  const TileParams* tiles;     // Cartesian plans
   const int2* items;
   int nitems;
   const int64_t* qoff;

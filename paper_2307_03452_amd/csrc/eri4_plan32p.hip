@@ -1,5 +1,5 @@
 // eri4_plan32p.hip -- the persistent plan kernel with FP32 transforms, shells read from a bra and a ket list of shell pairs.
-#include "eri4_device.h"
+#include "eri4_plan.h"
 
 namespace eri4 {
 hipError_t plan_set_attrs_f32p() { return plan_set_attrs_t<true, true>(); }

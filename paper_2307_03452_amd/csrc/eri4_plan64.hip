@@ -1,5 +1,5 @@
 // eri4_plan64.hip -- the persistent plan kernel with FP64 transforms, shells read from per-quartet arrays.
-#include "eri4_device.h"
+#include "eri4_plan.h"
 
 namespace eri4 {
 hipError_t plan_set_attrs_f64() { return plan_set_attrs_t<false, false>(); }

@@ -1,5 +1,5 @@
 // eri4_plan64p.hip -- the persistent plan kernel with FP64 transforms, shells read from a bra and a ket list of shell pairs.
-#include "eri4_device.h"
+#include "eri4_plan.h"
 
 namespace eri4 {
 hipError_t plan_set_attrs_f64p() { return plan_set_attrs_t<false, true>(); }
