@@ -356,26 +356,31 @@ TileParams tile_params(int la, int lb, int lc, int ld, int kmax) {
   return p;
 }
 
-// Estimated cycles of tile rt of a quartet with kb / kk bra / ket primitive
-// pairs: products, reads over t, and the steps before them per primitive
-// quartet.
-double tile_cost(const TileParams& p, int rt, double kb, double kk) {
+// Estimated cycles of each tile of a quartet, per primitive quartet (products,
+// reads over t, and the steps before them) and per ket primitive pair.
+struct TileCost { double quartet, ket; };
+std::vector<TileCost> tile_costs(const TileParams& p) {
   const TileShapeInfo sh = kTileShapes[p.shape];
   const int ug = kWaves / sh.cw;
-  double g1 = 0.0, g2 = 0.0, ket = 0.0;
   auto steps = [](const uint32_t* w) { return (double)((w[1] + 3) / 4); };
-  for (int i = 0; i < ug && rt * ug + i < p.nunits; ++i) {
-    const uint32_t* w = g_ttab.data() + p.o_bunit + 8 * (rt * ug + i);
-    const double np = (w[0] >> 8) & 0xff, nb = w[0] >> 16, X = w[0] & 0xff;
-    g1 = std::max(g1, steps(w) * sh.nc * (128.0 * np * nb + 12.0 * (X + 1)));
-    const uint32_t v = w[7];
-    g2 += (((v & 0xff) + ((v >> 8) & 0xff) + ((v >> 16) & 0xff) + (v >> 24)) + 15) / 16;
-  }
+  double ket = 0.0;
   for (int i = 0; i < g_tix.ket[p.lc][p.ld].nunits; ++i) {  // for one row block
     const uint32_t* w = g_ttab.data() + p.o_kunit + 8 * i;
     ket += steps(w) * (w[0] >> 8) * (64.0 + 16.0 * ((w[0] & 0xff) / 4 + 1)) / 4.0;
   }
-  return kb * kk * (g1 + 5000.0 + 2.0 * p.nr) + kk * (g2 * ket + 3000.0) + 4000.0;
+  std::vector<TileCost> cost;
+  for (int rt = 0; rt < p.ntiles; ++rt) {
+    double g1 = 0.0, g2 = 0.0;
+    for (int i = 0; i < ug && rt * ug + i < p.nunits; ++i) {
+      const uint32_t* w = g_ttab.data() + p.o_bunit + 8 * (rt * ug + i);
+      const double np = (w[0] >> 8) & 0xff, nb = w[0] >> 16, X = w[0] & 0xff;
+      g1 = std::max(g1, steps(w) * sh.nc * (128.0 * np * nb + 12.0 * (X + 1)));
+      const uint32_t v = w[7];
+      g2 += (((v & 0xff) + ((v >> 8) & 0xff) + ((v >> 16) & 0xff) + (v >> 24)) + 15) / 16;
+    }
+    cost.push_back({g1 + 5000.0 + 2.0 * p.nr, g2 * ket + 3000.0});
+  }
+  return cost;
 }
 
 // The low-l kernels: one wave per quartet for kets of at most four [ab|q]
@@ -561,55 +566,49 @@ eri4_status eri4_batch_solid(int la, int lb, int lc, int ld, int64_t nquartets, 
   return ERI4_SUCCESS;
 }
 
-// Parameters and LDS layout of the Coulomb (J-engine) kernels: the R box of
-// the first layout that fits (two boxes up to L = kBox2LMax, one box up to
-// kBoxLMax, else slab), the bra tables, and the w buffer (inside the R box when
-// that is large enough: w is written after the last recursion of a bra pair).
-// No [ab|q] tile and no ket tables.
-bool jengine_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d, ClassParams* out) {
-  const int L = la + lb + lc + ld;
-  if (L > kMaxL) return false;
-  static const int order[3] = {kLayBox2, kLayBox, kLaySlab};
-  for (int lay : order) {
-    const bool slab = lay == kLaySlab, two = lay == kLayBox2;
-    if ((two && L > kBox2LMax) || (lay == kLayBox && L > kBoxLMax)) continue;
-    ClassParams p = make_params(la, lb, lc, ld, kmax, 1, slab, two);
-    const int box_b = r_cells(slab, L) * 8;
-    p.o_brae = p.o_union + align16(box_b);
-    p.o_box1 = p.o_brae + align16(3 * p.tbaxis * 8);
-    int end = p.o_box1 + (two ? align16(box_b) : 0);
-    if (box_b >= kJw * 8) {
-      p.o_jw = p.o_union;
-    } else {
-      p.o_jw = end;
-      end += kJw * 8;
-    }
-    p.o_kete = p.o_union;  // unused
-    p.lds_bytes = end;
-    p.nrt = 1;
-    if (p.lds_bytes > kMaxLdsBytes - 64) continue;
-    p.rtab_off = d ? d->rstart[(slab ? 1 : 0) * (kMaxL + 1) + L] : 0;
-    *out = p;
-    return true;
-  }
-  return false;
+// Parameters and LDS layout of the Coulomb (J-engine) kernels (after
+// ensure_device).  Every class with l <=
+// ERI4_MAX_L fits: at most 103 KB, 75 KB for (ii|ii): two workgroups per compute unit.
+JParams jengine_params(int la, int lb, int lc, int ld, int kmax) {
+  JParams p{};
+  p.la = la; p.lb = lb; p.lc = lc; p.ld = ld;
+  p.nab = ncart(la) * ncart(lb); p.ncd = ncart(lc) * ncart(ld);
+  p.Lb = la + lb; p.Lk = lc + ld; p.L = p.Lb + p.Lk;
+  p.nq = nherm(p.Lk); p.nzt = nuv(p.L);
+  p.tbrow = odd_row(p.Lb + 2);
+  p.tbaxis = ((la + 1) * (lb + 1) + 1) * p.tbrow;
+  p.kmax = kmax;
+  p.ds = 16 * ((p.nq + 15) / 16);
+  const TileTableIndex& ix = g_tix;
+  p.ntask = ix.ntask[p.L]; p.nchunk = ix.nchunk[p.Lb]; p.nitems = ix.nitem[p.Lk];
+  for (p.ncps = 3; (1 << p.ncps) < p.nchunk;) ++p.ncps;
+  p.ncp = 1 << p.ncps;
+  p.o_uv = ix.uv; p.o_task = ix.task[p.L]; p.o_hexp = ix.hexp; p.o_chunk = ix.chunk[p.Lb];
+  p.o_item = ix.item[p.Lk]; p.o_qpos = ix.qpos[p.Lk];
+  p.dsize = ix.dsize[p.Lk];
+  int cells = 0;
+  for (int n = p.L + 1; n >= 1; n -= 2) cells += n * (n | 1);
+  // the parts of w over [r]: twelve values of half the threads
+  p.rsize = kJPad + std::max(cells + kJPad, 12 * kThreads / 2);
+  p.o_d = kJEnd;
+  p.o_r = p.o_d + align16(p.dsize * 8);
+  p.o_w = p.o_r + align16(p.rsize * 8);
+  p.o_zt = p.o_w + align16(nherm(p.L) * 8);
+  p.o_h = p.o_zt + align16(p.nzt * 8);
+  p.o_wp = p.o_w + align16(3 * p.tbaxis * 8);
+  p.o_wf = p.o_wp + align16(nherm(p.Lb) * 8);
+  p.lds_bytes = align16(std::max(p.o_h + 3 * 64 * h_steps(p.L) * 8, p.o_wf + nfold(la, lb) * 8));
+  return p;
 }
 
-// ds: doubles of one ket primitive pair's dket; ps: of one bra pair's J^ij.
-static bool coulomb_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d, ClassParams* p,
-                           int64_t* ds, int64_t* ps) {
-  if (!jengine_params(la, lb, lc, ld, kmax, d, p)) return false;
-  *ds = 16 * (int64_t)p->nqb;
-  *ps = p->nab;
-  return true;
+// Workspace doubles per primitive pair slot: dket of the ket pair, J of the bra's.
+static int64_t coulomb_slot(int la, int lb, int lc, int ld) {
+  return 16 * ((nherm(lc + ld) + 15) / 16) + ncart(la) * ncart(lb);
 }
 
 int64_t eri4_coulomb_work_size(int la, int lb, int lc, int ld, int kmax, int64_t nquartets) {
   if (check_class(la, lb, lc, ld, nquartets, kmax) != ERI4_SUCCESS) return -1;
-  ClassParams p;
-  int64_t ds, ps;
-  if (!coulomb_params(la, lb, lc, ld, kmax, nullptr, &p, &ds, &ps)) return -1;
-  return nquartets * kmax * kmax * (ds + ps);
+  return nquartets * kmax * kmax * coulomb_slot(la, lb, lc, ld);
 }
 
 // J for nquartets quartets in passes of as many as the workspace (work_size
@@ -620,12 +619,9 @@ static eri4_status coulomb_passes(int la, int lb, int lc, int ld, int64_t nquart
                                   const double* exponents, const double* coeffs, const int32_t* nprim, int kmax,
                                   const double* dens, double* work, int64_t work_size, double* out,
                                   hipStream_t stream, const DeviceState* d) {
-  ClassParams p;
-  int64_t ds, ps;
-  if (!coulomb_params(la, lb, lc, ld, kmax, d, &p, &ds, &ps))
-    return fail(ERI4_ERROR_UNSUPPORTED, "class (%d %d|%d %d) does not fit in LDS", la, lb, lc, ld);
+  const JParams p = jengine_params(la, lb, lc, ld, kmax);
   const int64_t kk2 = (int64_t)kmax * kmax;
-  const int64_t perq = kk2 * (ds + ps);
+  const int64_t perq = kk2 * (p.ds + p.nab);
   int64_t chunk = work_size / perq;
   if (chunk < 1)
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "workspace of %lld doubles is below one quartet's %lld",
@@ -633,11 +629,10 @@ static eri4_status coulomb_passes(int la, int lb, int lc, int ld, int64_t nquart
   chunk = std::min<int64_t>(chunk, ((int64_t)1 << 22) / kk2);  // grid of chunk * kmax^2 workgroups
   for (int64_t q0 = 0; q0 < nquartets; q0 += chunk) {
     const int64_t nq = std::min(chunk, nquartets - q0);
-    double* part = work + nq * kk2 * ds;
-    hipError_t e = coulomb_dket_launch(p, nq, stream, centers, exponents, coeffs, nprim, dens, work, q0, ds);
+    double* part = work + nq * kk2 * p.ds;
+    hipError_t e = coulomb_dket_launch(p, nq, stream, d->tables(), centers, exponents, nprim, dens, work, q0);
     if (e == hipSuccess)
-      e = coulomb_launch(p, nq, stream, d->tables(), centers, exponents, coeffs, nprim, part, out, q0,
-                         work, ds);
+      e = coulomb_launch(p, nq, stream, d->tables(), centers, exponents, coeffs, nprim, part, out, q0, work);
     if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
   }
   return ERI4_SUCCESS;
@@ -652,13 +647,9 @@ eri4_status eri4_batch_coulomb(int la, int lb, int lc, int ld, int64_t nquartets
   if (nquartets == 0) return ERI4_SUCCESS;
   if (!centers || !exponents || !coeffs || !nprim || !dens || !out || !work)
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "NULL buffer pointer");
-  ClassParams p;
-  int64_t ds, ps;
-  if (!coulomb_params(la, lb, lc, ld, kmax, nullptr, &p, &ds, &ps))
-    return fail(ERI4_ERROR_UNSUPPORTED, "class (%d %d|%d %d) does not fit in LDS", la, lb, lc, ld);
-  if (work_size < (int64_t)kmax * kmax * (ds + ps))
+  if (work_size < (int64_t)kmax * kmax * coulomb_slot(la, lb, lc, ld))
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "workspace of %lld doubles is below one quartet's %lld",
-                (long long)work_size, (long long)kmax * kmax * (ds + ps));
+                (long long)work_size, (long long)kmax * kmax * coulomb_slot(la, lb, lc, ld));
   DeviceState* d;
   st = ensure_device(&d);
   if (st != ERI4_SUCCESS) return st;
@@ -734,13 +725,9 @@ eri4_status eri4_batch_coulomb_static(int la, int lb, int lc, int ld, int64_t nq
   if (nquartets == 0) return ERI4_SUCCESS;
   if (!centers || !exponents || !coeffs || !nprim || !dens || !out)
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "NULL buffer pointer");
-  ClassParams p;
-  int64_t ds, ps;
-  if (!coulomb_params(la, lb, lc, ld, kmax, nullptr, &p, &ds, &ps))
-    return fail(ERI4_ERROR_UNSUPPORTED, "class (%d %d|%d %d) does not fit in LDS", la, lb, lc, ld);
-  if ((int64_t)kmax * kmax * (ds + ps) > kStaticScratchDoubles)
+  if (kmax * kmax * coulomb_slot(la, lb, lc, ld) > kStaticScratchDoubles)
     return fail(ERI4_ERROR_UNSUPPORTED, "one quartet's Hermite-space densities and partial J (%lld doubles) exceed "
-                "the %lld-double static scratch", (long long)kmax * kmax * (ds + ps),
+                "the %lld-double static scratch", (long long)kmax * kmax * coulomb_slot(la, lb, lc, ld),
                 (long long)kStaticScratchDoubles);
   // no initialisation here: that allocates the tables (eri4_init must have run)
   int dev = 0;
@@ -788,8 +775,7 @@ struct eri4_plan_s {
   int64_t* d_joff = nullptr;   // per bra entry: its J block in out
   int64_t out_size = 0;
   std::vector<int64_t> qoff;
-  ClassParams* d_classes = nullptr;  // solid and Coulomb plans
-  TileParams* d_tiles = nullptr;     // Cartesian plans
+  void* d_classes = nullptr;  // TileParams (Cartesian plans), ClassParams (solid) or JParams (Coulomb) per class
   int2* d_items = nullptr;
   int64_t* d_qoff = nullptr;
   int32_t* d_nprim = nullptr;
@@ -799,7 +785,6 @@ struct eri4_plan_s {
 static void plan_free(eri4_plan_s* p) {
   if (!p) return;
   if (p->d_classes) (void)hipFree(p->d_classes);
-  if (p->d_tiles) (void)hipFree(p->d_tiles);
   if (p->d_items) (void)hipFree(p->d_items);
   if (p->d_qoff) (void)hipFree(p->d_qoff);
   if (p->d_nprim) (void)hipFree(p->d_nprim);
@@ -907,14 +892,12 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "too many (class, tile choice) groups");
   }
   // per group: tile height and R layout (the table's, or see pick_params)
-  std::vector<ClassParams> cps(keys.size());
+  std::vector<ClassParams> cps(coul ? 0 : keys.size());
+  std::vector<JParams> jps;
   for (size_t c = 0; c < keys.size(); ++c) {
     const auto& k = keys[c];
     if (coul) {
-      if (!jengine_params(k[0], k[1], k[2], k[3], kmax, d, &cps[c])) {
-        plan_free(p);
-        return fail(ERI4_ERROR_UNSUPPORTED, "class (%d %d|%d %d) does not fit in LDS", k[0], k[1], k[2], k[3]);
-      }
+      jps.push_back(jengine_params(k[0], k[1], k[2], k[3], kmax));
     } else if (k[4] >= 0) {
       const eri4_tile_choice& ch = choices[k[4]];
       if (!try_params(k[0], k[1], k[2], k[3], kmax, ch.rows16, ch.layout, d, limit, &cps[c])) {
@@ -932,10 +915,16 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   // Cartesian plans run the kernels of eri4_tile.h, whose one layout of [r] and
   // tiling follow from the class; a tile choice is checked and changes nothing
   std::vector<TileParams> tps;
+  std::vector<std::vector<TileCost>> tcs;
   if (!solid && !coul)
-    for (const auto& k : keys) tps.push_back(tile_params(k[0], k[1], k[2], k[3], kmax));
+    for (const auto& k : keys) {
+      tps.push_back(tile_params(k[0], k[1], k[2], k[3], kmax));
+      tcs.push_back(tile_costs(tps.back()));
+    }
   p->nclasses = (int)keys.size();
-  if (solid || coul)
+  if (coul)
+    for (const JParams& c : jps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
+  else if (solid)
     for (const ClassParams& c : cps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
   else
     for (const TileParams& c : tps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
@@ -945,31 +934,26 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   int64_t off = 0;
   std::vector<int2> items;
   std::vector<double> cost;
-  std::map<std::array<int, 3>, std::vector<double>> cost_of;  // Cartesian: per class and primitive pairs, by tile
   for (int64_t q = 0; q < nquartets; ++q) {
-    const ClassParams& c = cps[qcls[q]];
-    p->qoff[q] = off;
-    off += coul ? (int64_t)c.nab : (int64_t)c.nab * c.ncd;  // Coulomb plans: J rows per quartet
     const double kb = (double)nprim[4 * q] * nprim[4 * q + 1], kk = (double)nprim[4 * q + 2] * nprim[4 * q + 3];
+    p->qoff[q] = off;
     if (coul) {
       // one item per quartet (J-engine): per primitive quartet the recursion
       // and the matrix-vector product, per bra pair the bra transform
-      cost.push_back(kb * kk * (8000.0 + 4.0 * nherm(c.L) + (double)c.np * c.nq / 128.0) +
-                     kb * (double)c.nab * c.np / 256.0 + 4000.0);
+      const JParams& j = jps[qcls[q]];
+      off += j.nab;  // J rows per quartet
+      cost.push_back(kb * kk * (5000.0 + 2.0 * nherm(j.L) + nherm(j.Lb) * (double)j.nq / 16.0) +
+                     kb * (4000.0 + 8.0 * j.nab) + 4000.0);
       items.push_back(make_int2((int)q, qcls[q] << 16));
       continue;
     }
+    const ClassParams& c = cps[qcls[q]];
+    off += (int64_t)c.nab * c.ncd;
     if (!solid) {
-      const TileParams& t = tps[qcls[q]];
-      auto it = cost_of.find({qcls[q], (int)kb, (int)kk});
-      if (it == cost_of.end()) {
-        std::vector<double> v(t.ntiles);
-        for (int rt = 0; rt < t.ntiles; ++rt) v[rt] = tile_cost(t, rt, kb, kk);
-        it = cost_of.emplace(std::array<int, 3>{qcls[q], (int)kb, (int)kk}, std::move(v)).first;
-      }
-      for (int rt = 0; rt < t.ntiles; ++rt) {
-        cost.push_back(it->second[rt]);
-        items.push_back(make_int2((int)q, rt | (qcls[q] << 16)));
+      const std::vector<TileCost>& t = tcs[qcls[q]];
+      for (size_t rt = 0; rt < t.size(); ++rt) {
+        cost.push_back(kb * kk * t[rt].quartet + kk * t[rt].ket + 4000.0);
+        items.push_back(make_int2((int)q, (int)rt | (qcls[q] << 16)));
       }
       continue;
     }
@@ -1006,8 +990,9 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   if (oe != hipSuccess || per_cu < 1) per_cu = 1;
   p->grid = (int)std::min<int64_t>(std::max(p->nitems, 1), (int64_t)ncu * per_cu);
 
-  const bool ok = hipMalloc(&p->d_classes, std::max<size_t>(1, cps.size()) * sizeof(ClassParams)) == hipSuccess &&
-                  hipMalloc(&p->d_tiles, std::max<size_t>(1, tps.size()) * sizeof(TileParams)) == hipSuccess &&
+  const void* params = coul ? (const void*)jps.data() : solid ? (const void*)cps.data() : (const void*)tps.data();
+  const size_t params_size = keys.size() * (coul ? sizeof(JParams) : solid ? sizeof(ClassParams) : sizeof(TileParams));
+  const bool ok = hipMalloc(&p->d_classes, std::max<size_t>(1, params_size)) == hipSuccess &&
                   hipMalloc(&p->d_items, std::max<size_t>(1, sorted.size()) * sizeof(int2)) == hipSuccess &&
                   hipMalloc(&p->d_qoff, std::max<int64_t>(1, nquartets) * sizeof(int64_t)) == hipSuccess &&
                   hipMalloc(&p->d_nprim, std::max<int64_t>(1, 4 * nquartets) * sizeof(int32_t)) == hipSuccess &&
@@ -1017,9 +1002,7 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     return fail(ERI4_ERROR_OUT_OF_MEMORY, "device allocation for the plan failed");
   }
   hipError_t e = hipSuccess;
-  if (!cps.empty()) e = hipMemcpy(p->d_classes, cps.data(), cps.size() * sizeof(ClassParams), hipMemcpyHostToDevice);
-  if (e == hipSuccess && !tps.empty())
-    e = hipMemcpy(p->d_tiles, tps.data(), tps.size() * sizeof(TileParams), hipMemcpyHostToDevice);
+  if (params_size) e = hipMemcpy(p->d_classes, params, params_size, hipMemcpyHostToDevice);
   if (e == hipSuccess && !sorted.empty())
     e = hipMemcpy(p->d_items, sorted.data(), sorted.size() * sizeof(int2), hipMemcpyHostToDevice);
   if (e == hipSuccess && nquartets > 0)
@@ -1144,7 +1127,7 @@ static eri4_status plan_launch(eri4_plan plan, const Shells& shl, double* work, 
                                 plan->d_pn, shl, plan->d_hoff, d->stab, work));
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, plan->d_counter);
   HIP_TRY(hipGetLastError());
-  const PlanArgs a{plan->d_classes, plan->d_tiles, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
+  const PlanArgs a{plan->d_classes, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
                    out};
   const Tables t = d->tables();
   const dim3 grid(plan->grid);
@@ -1381,10 +1364,10 @@ eri4_status eri4_plan_execute_coulomb(eri4_plan plan, const double* bra_centers,
   hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(64), 0, stream, plan->d_counter);
   HIP_TRY(hipGetLastError());
   const Shells shl{bra_centers, bra_exponents, bra_coeffs, ket_centers, ket_exponents, ket_coeffs, plan->nket};
-  const PlanArgs a{plan->d_classes, plan->d_tiles, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
+  const PlanArgs a{plan->d_classes, plan->d_items, plan->nitems, plan->d_qoff, plan->d_nprim, plan->d_counter, shl,
                    nullptr};
   HIP_TRY(plan_coulomb_launch(dim3(plan->grid), plan->lds_bytes, stream, d->tables(), a,
-                              (int)plan->nbra, plan->kmax, plan->d_pl, plan->d_pn, ket_dens, plan->d_doff,
+                              (int)plan->nbra, plan->kmax, g_tix.uv, plan->d_pl, plan->d_pn, ket_dens, plan->d_doff,
                               plan->d_dkoff, plan->d_joff, work, work + plan->dket_size, out));
   return ERI4_SUCCESS;
 }

@@ -86,11 +86,6 @@ __host__ __device__ constexpr int solid_h_lds(int l1, int l2, int nk4) {
   return (2 * l1 + 1) * ncart(l2) * 16 * 8 + 3 * ((l1 + 1) * (l2 + 1) + 1) * odd_row(l1 + l2 + 2) * 8 + nk4 * 8;
 }
 
-// Doubles of the Coulomb kernels' w buffer: the bra Hermite functions of up to
-// 8 groups of waves (at most 512 in all), or 2 per thread when there are more
-// than 512 (la + lb >= 13).
-constexpr int kJw = 1024;
-
 // Layout of W (one value per [r]) in the Cartesian integral kernels
 // (eri4_tile.h): nherm(L) values, rows of t = 0..L-s for each (u, v), the rows in order of
 // increasing s = u + v and then u.  Row (u, v) starts at tile_r_base(L, s) +
@@ -164,7 +159,6 @@ struct ClassParams {
   int o_brae;    // bra tables (phase 1)
   int o_kete;    // ket tables (phase 2)
   int o_ptab, o_qtab, o_base, o_shell;
-  int o_jw;      // Coulomb (J-engine) kernels: the Hermite-space J vector w
   int lds_bytes;
 };
 
@@ -237,9 +231,51 @@ constexpr int tile_shape(int nqb) {
 struct TileTableIndex {
   int uv, hexp;
   int qcol[2 * kTableLMax + 1], task[kMaxL + 1], ntask[kMaxL + 1];
+  int chunk[2 * kTableLMax + 1], nchunk[2 * kTableLMax + 1];
+  int item[2 * kTableLMax + 1], nitem[2 * kTableLMax + 1], dsize[2 * kTableLMax + 1], qpos[2 * kTableLMax + 1];
   struct Side {
     int nunits, nblocks, units, rows, list;
   } bra[kTileLimits][kTableLMax + 1][kTableLMax + 1], ket[kTableLMax + 1][kTableLMax + 1];
 };
+
+// The same for the Coulomb (J-engine) kernels (eri4_coulomb.hip).
+struct JParams {
+  int la, lb, lc, ld;
+  int nab, ncd;
+  int Lb, Lk, L;
+  int nq;              // Hermite functions of the ket
+  int nzt;             // values of zt: nuv(L)
+  int ntask;           // wave tasks of W and of [r]
+  int nchunk, ncp, ncps;  // chunks of the bra's Hermite functions, the power of two above (>= 8) and its exponent
+  int nitems;          // items of the ket's
+  int tbrow, tbaxis;   // bra 1-d tables
+  int kmax;
+  int ds;              // doubles of dket per ket primitive pair
+  int rsize, dsize;    // doubles of [r] (with kJPad before and after it) and of dket in LDS
+  int o_uv, o_task, o_hexp, o_chunk, o_item, o_qpos;
+  // LDS (byte offsets): fixed part (kJ..), dket, [r] (or parts of w), then W, zt
+  // and the per-axis tables; or the bra tables, w and the folded w
+  int o_d, o_r, o_w, o_zt, o_h, o_wp, o_wf;
+  int lds_bytes;
+};
+
+constexpr int kJShell = 0;                                             // shells, lengths
+constexpr int kJBase = kJShell + (12 + 8 * 16) * 8 + 16;               // [0]^(m)
+constexpr int kJRowt = kJBase + 32 * 8;                                // row starts of W by (u, v)
+constexpr int kJRs = kJRowt + kTileRowfSize;                           // rows of W in order
+constexpr int kJRv = kJRs + kTileRfSize;                               // their u, v
+constexpr int kJVrow = kJRv + (nuv(kMaxL) * 2 + 15) / 16 * 16;         // [r] by v
+constexpr int kJItem = kJVrow + 32 * 4;                                // items of the ket
+constexpr int kJEnd = kJItem + 64 * 8;
+// Reads of [r] past its rows: at most 3 rows of S <= 29 and a few values.
+constexpr int kJPad = 112;
+// Values of w, or of a density block, folded over the groups (x1, x2) of a shell
+// pair: the (u, v) of each group.
+__host__ __device__ constexpr int nfold(int l1, int l2) {
+  int n = 0;
+  for (int x1 = 0; x1 <= l1; ++x1)
+    for (int x2 = 0; x2 <= l2; ++x2) n += nuv(l1 + l2 - x1 - x2);
+  return n;
+}
 
 }  // namespace eri4

@@ -46,17 +46,17 @@ hipError_t solid_launch(const ClassParams& p, dim3 grid, hipStream_t s, const Ta
                         const double* hbra, const double* hket, int64_t hbs, int64_t hks);
 
 // Coulomb contraction (eri4_coulomb.hip): dket of every ket primitive pair of
-// quartets q0..q0+nq-1 (ds doubles each, kmax^2 slots per quartet), then the
+// quartets q0..q0+nq-1 (p.ds doubles each, kmax^2 slots per quartet), then the
 // J-engine kernel (J^ij of every bra primitive pair into part, kmax^2 * nab
 // doubles per quartet) and the sum over bra pairs into out.  p from
 // jengine_params.
 hipError_t coulomb_set_attrs();
-hipError_t coulomb_dket_launch(const ClassParams& p, int64_t nq, hipStream_t s, const double* centers,
-                               const double* exps, const double* coefs, const int32_t* nprim, const double* dens,
-                               double* dket, int64_t q0, int64_t ds);
-hipError_t coulomb_launch(const ClassParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
+hipError_t coulomb_dket_launch(const JParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
+                               const double* exps, const int32_t* nprim, const double* dens, double* dket,
+                               int64_t q0);
+hipError_t coulomb_launch(const JParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
                           const double* exps, const double* coefs, const int32_t* nprim, double* part, double* out,
-                          int64_t q0, const double* dket, int64_t ds);
+                          int64_t q0, const double* dket);
 
 // Exchange contraction (eri4_exchange.hip): F^b of every ket primitive pair
 // and shell-b component of quartets q0..q0+nq-1 (fbs doubles each), the
@@ -84,8 +84,7 @@ struct Shells {
 // The persistent plan kernel, with FP64 or FP32 transforms (f64 / f32), shells
 // from per-quartet arrays or, with the suffix p, from pair lists.
 struct PlanArgs {
-  const ClassParams* classes;  // solid and Coulomb plans
-  const TileParams* tiles;     // Cartesian plans
+  const void* classes;  // per class: TileParams (Cartesian plans), ClassParams (solid), JParams (Coulomb)
   const int2* items;
   int nitems;
   const int64_t* qoff;
@@ -105,7 +104,7 @@ hipError_t plan_solid_launch(bool pairs, dim3 grid, int lds_bytes, hipStream_t s
 hipError_t plan_coulomb_set_attrs();
 hipError_t plan_coulomb_occupancy(int lds_bytes, int* per_cu);
 hipError_t plan_coulomb_launch(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a,
-                               int nbra, int kmax, const int32_t* pl, const int32_t* pn, const double* ket_dens,
+                               int nbra, int kmax, int uv, const int32_t* pl, const int32_t* pn, const double* ket_dens,
                                const int64_t* doff, const int64_t* dkoff, const int64_t* joff, double* dket,
                                double* jpart, double* out);
 // nbra < 0: the alternating (quartet) form, all entries read from x.centers, ...;

@@ -60,7 +60,7 @@ hipError_t plan_occupancy_t(int lds_bytes, int* per_cu) {
 template <bool F32, bool PAIRS>
 hipError_t plan_launch_t(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a) {
   const Shells& h = a.shells;
-  hipLaunchKernelGGL((eri4_plan_kernel<F32, PAIRS>), grid, dim3(kThreads), lds_bytes, s, a.tiles, a.items, a.nitems,
+  hipLaunchKernelGGL((eri4_plan_kernel<F32, PAIRS>), grid, dim3(kThreads), lds_bytes, s, (const TileParams*)a.classes, a.items, a.nitems,
                      a.qoff, a.nprim, a.counter, t, h.centers, h.exps, h.coefs, a.out, h.kcenters, h.kexps, h.kcoefs,
                      h.nket);
   return hipGetLastError();

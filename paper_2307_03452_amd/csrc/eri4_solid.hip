@@ -271,11 +271,11 @@ hipError_t plan_solid_launch(bool pairs, dim3 grid, int lds_bytes, hipStream_t s
                              int64_t nbra, const int64_t* hoff, const double* h) {
   const Shells& x = a.shells;
   if (pairs)
-    hipLaunchKernelGGL(eri4_plan_solid_kernel<true>, grid, dim3(kThreads), lds_bytes, s, a.classes, a.items, a.nitems,
+    hipLaunchKernelGGL(eri4_plan_solid_kernel<true>, grid, dim3(kThreads), lds_bytes, s, (const ClassParams*)a.classes, a.items, a.nitems,
                        a.qoff, a.nprim, a.counter, t.boys, t.rtab, x.centers, x.exps, x.coefs, a.out, x.kcenters,
                        x.kexps, x.kcoefs, x.nket, nbra, hoff, h);
   else
-    hipLaunchKernelGGL(eri4_plan_solid_kernel<false>, grid, dim3(kThreads), lds_bytes, s, a.classes, a.items,
+    hipLaunchKernelGGL(eri4_plan_solid_kernel<false>, grid, dim3(kThreads), lds_bytes, s, (const ClassParams*)a.classes, a.items,
                        a.nitems, a.qoff, a.nprim, a.counter, t.boys, t.rtab, x.centers, x.exps, x.coefs, a.out,
                        nullptr, nullptr, nullptr, (int64_t)0, (int64_t)0, hoff, h);
   return hipGetLastError();

@@ -331,6 +331,10 @@ static TileTableIndex::Side make_ket_side(std::vector<uint32_t>& tab, int l1, in
 //   qcol  per order n: t | u << 8 | s << 16 of each Hermite function, in (u, v)
 //         order, t fastest, padded with zeros to whole blocks of 16
 //   task  per order L: the blocks of W, most steps first: first pair (v, j) | ub << 12
+//   chunk per bra order (Coulomb kernels): 4 t x 3 u of its Hermite functions: u | v << 8 | t << 16
+//   item  per ket order (Coulomb kernels): 3 u of one v, longest first: v | u << 8 | values of t of the
+//         first u << 16, place of its first dket (three to a t)
+//   qpos  per ket order: the place of each Hermite function (in the order of W) among them
 // and the sides (make_bra_side, make_ket_side).
 void make_tile_tables(std::vector<uint32_t>& tab, std::vector<double>& hcoef, TileTableIndex& ix) {
   tab.clear();
@@ -365,6 +369,30 @@ void make_tile_tables(std::vector<uint32_t>& tab, std::vector<double>& hcoef, Ti
       for (int r = 0; r < nuv(L - 16); r += 16) tab.push_back((uint32_t)(r | (1 << 12)));
     for (int r = 0; r < nuv(L); r += 16) tab.push_back((uint32_t)r);
     ix.ntask[L] = (int)tab.size() - ix.task[L];
+  }
+  for (int n = 0; n <= 2 * kTableLMax; ++n) {
+    ix.chunk[n] = (int)tab.size();
+    for (int t = 0; t <= n; t += 4)
+      for (int v = 0; v <= n - t; ++v)
+        for (int u = 0; u <= n - t - v; u += 3) tab.push_back((uint32_t)(u | (v << 8) | (t << 16)));
+    ix.nchunk[n] = (int)tab.size() - ix.chunk[n];
+    ix.item[n] = (int)tab.size();
+    std::vector<int> place((n + 1) * (n + 1), 0);
+    int at = 0;
+    for (int len = n + 1; len >= 1; --len)
+      for (int u = 0; u <= n + 1 - len; u += 3) {
+        const int v = n + 1 - len - u;
+        tab.push_back((uint32_t)(v | (u << 8) | (len << 16)));
+        tab.push_back((uint32_t)at);
+        for (int b = 0; b < 3 && u + b <= n; ++b) place[(u + b) * (n + 1) + v] = at + b;
+        at += 3 * len;
+      }
+    ix.nitem[n] = ((int)tab.size() - ix.item[n]) / 2;
+    ix.dsize[n] = at;
+    ix.qpos[n] = (int)tab.size();
+    for (int s = 0; s <= n; ++s)
+      for (int u = 0; u <= s; ++u)
+        for (int t = 0; t <= n - s; ++t) tab.push_back((uint32_t)(place[u * (n + 1) + s - u] + 3 * t));
   }
   for (int l1 = 0; l1 <= kTableLMax; ++l1)
     for (int l2 = 0; l2 <= kTableLMax; ++l2) {
