@@ -266,8 +266,7 @@ ClassParams make_params(int la, int lb, int lc, int ld, int kmax, int rb, bool s
   const int box_b = r_cells(slab, p.L) * 8;
   p.lay = slab ? kLaySlab : (box2 ? kLayBox2 : kLayBox);
   // phase 1: R box, bra tables[, second R box]
-  p.o_box1 = off + align16(box_b) + align16(3 * p.tbaxis * 8);
-  const int ph1 = box2 ? p.o_box1 - off + box_b : align16(box_b) + 3 * p.tbaxis * 8;
+  const int ph1 = align16(box_b) + (box2 ? align16(3 * p.tbaxis * 8) + box_b : 3 * p.tbaxis * 8);
   const int xb = align16(rb * 16 * p.xs * 8);
   const int ph2 = xb + 3 * p.tkaxis * 8;
   p.o_brae = off + align16(box_b);
@@ -410,22 +409,46 @@ bool small_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d
   return true;
 }
 
+// LDS layout of the solid (exch false) and exchange kernels and the tables of their
+// recursion (their places need d, an initialised device): [r], whose
+// unused cells hold W, then zt and the per-axis tables, for exch under the bra
+// tables; or the [ab|q] tile.  It fits wherever the layout of make_params does
+// (checked over all classes, tiles and layouts), without the second box that the
+// two-box layout once held.
+void dense_layout(ClassParams* p, bool exch, const DeviceState* d) {
+  if (d) {
+    const TileTableIndex& ix = g_tix;
+    p->ntask = ix.ntask[p->L]; p->o_uv = ix.uv; p->o_task = ix.task[p->L]; p->o_hexp = ix.hexp;
+  }
+  const int nzt = nuv(p->L);
+  p->o_rowt = p->o_qtab + align16(16 * p->nqb * 8);
+  p->o_rs = p->o_rowt + align16((p->L + 1) * (p->L + 1) * 2);
+  p->o_rv = p->o_rs + align16(nzt * 4);
+  p->o_union = p->o_rv + align16(nzt * 2);
+  p->o_zt = p->o_union + align16((r_cells(p->slab, p->L) + (p->S1 == p->L + 1 ? p->L + 1 : 0)) * 8);
+  p->o_h = p->o_zt + align16(nzt * 8);
+  p->o_brae = p->o_zt;
+  const int end = std::max(p->o_h + 3 * 64 * h_steps(p->L) * 8, exch ? p->o_brae + 3 * p->tbaxis * 8 : 0);
+  p->lds_bytes = align16(std::max(end, p->o_union + p->rb * 16 * p->xs * 8));
+}
+
 // Solid-harmonic output: the library's tile for the class, with rows and
 // columns over the 2l+1 real solid harmonics of each shell; hbs / hks doubles
 // of H per bra / ket primitive pair (rows padded to whole tiles, columns to
 // whole 16-column blocks, k to the padded Hermite counts).
-void to_solid(ClassParams* p) {
+void to_solid(ClassParams* p, const DeviceState* d) {
   p->na = 2 * p->la + 1; p->nb = 2 * p->lb + 1; p->nc = 2 * p->lc + 1; p->nd = 2 * p->ld + 1;
   p->nab = p->na * p->nb;
   p->ncd = p->nc * p->nd;
   p->nrt = (p->nab + 16 * p->rb - 1) / (16 * p->rb);
   p->ncdb = (p->ncd + 15) / 16;
+  dense_layout(p, false, d);
 }
 
 bool solid_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d, ClassParams* p, int64_t* hbs,
                   int64_t* hks) {
   if (!pick_params(la, lb, lc, ld, kmax, d, kMaxLdsBytes, p)) return false;
-  to_solid(p);
+  to_solid(p, d);
   *hbs = (int64_t)p->nrt * p->rb * 16 * p->np4;
   *hks = (int64_t)p->ncdb * 16 * p->nq4;
   return true;
@@ -666,6 +689,7 @@ static bool exchange_params(int la, int lb, int lc, int ld, int kmax, const Devi
   if (!pick_params(la, lb, lc, ld, kmax, d, kMaxLdsBytes, p)) return false;
   const int blocks = p->nb * ((p->na + 15) / 16);
   p->nrt = (blocks + p->rb - 1) / p->rb;
+  dense_layout(p, true, d);
   *fbs = (int64_t)((p->nc + 15) / 16) * 16 * p->nq4;
   *ps = (int64_t)p->nb * p->na * p->nc;
   return true;
@@ -911,7 +935,7 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     }
   }
   if (solid)
-    for (ClassParams& c : cps) to_solid(&c);  // rows and columns over solid functions; same tile and LDS
+    for (ClassParams& c : cps) to_solid(&c, d);  // rows and columns over solid functions; same tile and LDS
   // Cartesian plans run the kernels of eri4_tile.h, whose one layout of [r] and
   // tiling follow from the class; a tile choice is checked and changes nothing
   std::vector<TileParams> tps;

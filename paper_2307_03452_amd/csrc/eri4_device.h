@@ -252,42 +252,6 @@ __device__ void hermite_r_lds(double* R, const double* baseM, int L, const doubl
   }
 }
 
-// The same recursion between two boxes (R0, R1 of the same layout): level m
-// reads [.]^(m+1) from one box and writes [.]^(m) to the other, so one barrier
-// per level suffices.  Level m writes R0 when m is even, so [r]^(0) ends in R0.
-template <int NE>
-__device__ void hermite_r_lds2(double* R0, double* R1, const double* baseM, int L, const double* PQ,
-                               const uint2 (&ent_in)[NE], int tid) {
-  uint2 ent[NE];
-#pragma unroll
-  for (int k = 0; k < NE; ++k) ent[k] = ent_in[k];
-  const int Roff = (int)(R1 - R0);  // R1 = R0 + Roff (same LDS array)
-  if (tid == 0) R0[(L & 1) ? Roff : 0] = baseM[L];
-  __syncthreads();
-  const double px = PQ[0], py = PQ[1], pz = PQ[2];
-  for (int m = L - 1; m >= 0; --m) {
-    const int src = ((m + 1) & 1) ? Roff : 0, dst = (m & 1) ? Roff : 0;
-    const int nact = nherm(L - m);
-    const int kact = (nact + kThreads - 1) / kThreads;  // entry slots in use at this level (uniform)
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-      if (k < kact) {
-        asm volatile("" : "+v"(ent[k].x), "+v"(ent[k].y));
-        const int e = tid + k * kThreads;
-        const int o1 = (int)(ent[k].x >> 16);
-        const int o2 = (int)(ent[k].y & 0xffffu);
-        const int dir = (int)((ent[k].y >> 16) & 3u);
-        const int ri = (int)(ent[k].y >> 18);
-        const double c1 = dir == 0 ? px : (dir == 1 ? py : pz);
-        const double v = c1 * R0[src + o1] + (double)max(ri - 1, 0) * R0[src + o2];
-        if (e < nact && e > 0) R0[dst + (int)(ent[k].x & 0xffffu)] = v;
-      }
-    }
-    if (tid == 0) R0[dst] = baseM[m];
-    __syncthreads();
-  }
-}
-
 template <int NE>
 __device__ __forceinline__ void load_rtab(uint2 (&ent)[NE], const uint2* __restrict__ rt, int L, int tid) {
   const int n = nherm(L);
@@ -365,15 +329,6 @@ __device__ __forceinline__ void gemm1_range(typename Acc<F32>::type (&acc)[NR][N
       for (int c = 0; c < NC; ++c) acc[r][c] = mfma16<F32>(a, b[c], acc[r][c]);
     }
   }
-}
-
-template <int NR, int NC, bool SLAB, bool F32>
-__device__ __forceinline__ void gemm1_pair(typename Acc<F32>::type (&acc)[NR][NC], const double* __restrict__ brae,
-                                           const double* __restrict__ R, const int2* __restrict__ ptab,
-                                           const int (&rowx)[NR], const int (&rowy)[NR], const int (&rowz)[NR],
-                                           const int (&offq)[NC], const int (&tq)[NC], int np4, int L, int S1,
-                                           int lane) {
-  gemm1_range<NR, NC, SLAB, F32>(acc, brae, R, ptab, rowx, rowy, rowz, offq, tq, 0, np4, L, S1, lane);
 }
 
 // Second transform for one group of NC output column blocks (cb0, cb0+CSTRIDE, ...)
@@ -482,210 +437,6 @@ __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double*
     }
 }
 
-// Solid-harmonic mode: the transform matrices H = (C_a x C_b) E of one
-// primitive pair come from device memory (solid_h_kernel), stored in the
-// operand order of the matrix cores: for row (or column) block u and k step s,
-// 64 doubles, lane l holding H[16u + (l & 15)][4s + (l >> 4)].  A wave's load of
-// one operand is one contiguous 512-byte read.
-
-// First transform, A operand from H: acc[r][c] += sum_p H[row block r][p] [p|q].
-// H points at this lane's element of row block 0, k step 0; operands of step
-// k+8 are requested while step k runs.
-template <int NR, int NC, bool SLAB>
-__device__ __forceinline__ void gemm1_h(typename Acc<false>::type (&acc)[NR][NC], const double* __restrict__ H,
-                                        const double* __restrict__ R, const int2* __restrict__ ptab,
-                                        const int (&offq)[NC], const int (&tq)[NC], int np4, int L, int S1,
-                                        int lane) {
-  const int g = lane >> 4;
-  const int rs = np4 * 16;  // doubles per row block
-  double a0[NR], a1[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    a0[r] = H[r * rs];
-    a1[r] = H[r * rs + min(4, np4 - 4) * 16];
-  }
-  int2 pt = ptab[g];
-  for (int kk = 0; kk < np4; kk += 4) {
-    double b[NC], a2[NR];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if constexpr (SLAB) {
-        const int t = (pt.x >> 24) + tq[c];
-        b[c] = R[slab_base(t, L, S1) + pt.y + offq[c]];
-      } else {
-        b[c] = R[pt.y + offq[c]];
-      }
-    }
-    pt = ptab[min(kk + 4, np4 - 4) + g];
-    const int k2 = min(kk + 8, np4 - 4);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) a2[r] = H[r * rs + k2 * 16];
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) acc[r][c] = mfma16<false>(a0[r], b[c], acc[r][c]);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      a0[r] = a1[r];
-      a1[r] = a2[r];
-    }
-  }
-}
-
-// Second transform for one group of NC output column blocks, B operand from
-// H_cd (Hk: this lane's element of column block 0, k step 0), then the output
-// write, as gemm2_group.
-template <int NR, int NC>
-__device__ __forceinline__ void gemm2_group_h(const ClassParams& cp, const double* __restrict__ X,
-                                              const double* __restrict__ Hk, int cb0, int row0,
-                                              double* __restrict__ outq, bool first, int lane) {
-  const int g = lane >> 4, n = lane & 15;
-  const int cs = cp.nq4 * 16;  // doubles per column block
-  typename Acc<false>::type acc[NR][NC];
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) acc[r][c] = acc_zero<false>();
-  const int xs = cp.xs, nq4 = cp.nq4;
-  double b0[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) b0[c] = Hk[(cb0 + 8 * c) * cs];
-  for (int kk = 0; kk < nq4; kk += 4) {
-    double a[NR], b1[NC];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) a[r] = X[(r * 16 + n) * xs + kk + g];
-    const int kn = min(kk + 4, nq4 - 4);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) b1[c] = Hk[(cb0 + 8 * c) * cs + kn * 16];
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-      for (int r = 0; r < NR; ++r) acc[r][c] = mfma16<false>(a[r], b0[c], acc[r][c]);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) b0[c] = b1[c];
-  }
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int cd = (cb0 + 8 * c) * 16 + n;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int ab = row0 + r * 16 + acc_row<false>(jj, g);
-        if (ab < cp.nab && cd < cp.ncd) {
-          double* o = outq + (int64_t)ab * cp.ncd + cd;
-          const double v = acc[r][c][jj];
-          if (first)
-            __builtin_nontemporal_store(v, o);
-          else
-            *o += v;
-        }
-      }
-    }
-}
-
-// Exchange mode: bra row order.  Padded row pr of a quartet is shell-b
-// component pr / P and shell-a component pr % P, with P = 16 * ceil(na / 16)
-// rows per b (components a >= na are padding).
-__device__ __forceinline__ int exch_rows_per_b(const ClassParams& cp) { return 16 * ((cp.na + 15) / 16); }
-__device__ __forceinline__ void exch_row(const ClassParams& cp, int pr, int& ia, int& ib) {
-  const int P = exch_rows_per_b(cp);
-  ib = pr / P;
-  ia = pr - ib * P;
-}
-
-// y blocks of one ket pair: block i of this wave (blk = wave + 8 i) is row
-// block r = blk / ncc and column block cc = blk % ncc (c = 16 cc + lane % 16):
-//   y[r][cc] += sum_q X[row block r][q] F^b[q][cc],  b the row block's shell-b component.
-// F^b of this ket pair at F + (b * ncc + cc) * nq4 * 16 in operand order (k
-// step s, lane l: F^b[4 s + l / 16][16 cc + l % 16]).  The operands of eight k
-// steps are read before their products are issued.
-template <int NR>
-__device__ __forceinline__ void exch_gemm(const ClassParams& cp, const double* __restrict__ X,
-                                          const double* __restrict__ F, int row0, int wave, int lane, d4 (&yacc)[2]) {
-  const int g = lane >> 4, n = lane & 15;
-  const int ncc = (cp.nc + 15) / 16;
-  const int P = exch_rows_per_b(cp);
-  const int64_t fs = (int64_t)cp.nq4 * 16;
-  const int nq4 = cp.nq4;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int blk = wave + 8 * i;
-    if (blk >= NR * ncc) break;
-    const int r = blk / ncc, cc = blk - (blk / ncc) * ncc;
-    const int ib = (row0 + r * 16) / P;  // one b per row block
-    if (ib >= cp.nb) continue;           // padding rows past the last b
-    const double* __restrict__ Fb = F + ((int64_t)ib * ncc + cc) * fs + lane;
-    const double* __restrict__ Xr = X + (r * 16 + n) * cp.xs + g;
-    d4 acc = yacc[i];
-    int kk = 0;
-    for (; kk + 32 <= nq4; kk += 32) {
-      double a[8], b[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) b[u] = Fb[(kk + 4 * u) * 16];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) a[u] = Xr[kk + 4 * u];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc = mfma16<false>(a[u], b[u], acc);
-    }
-    for (; kk < nq4; kk += 4) acc = mfma16<false>(Xr[kk], Fb[kk * 16], acc);
-    yacc[i] = acc;
-  }
-}
-
-// y of this wave's blocks to outq[(b * na + a) * nc + c] (valid a, b, c only).
-template <int NR>
-__device__ __forceinline__ void exch_store(const ClassParams& cp, const d4 (&yacc)[2], double scale,
-                                           double* __restrict__ outq, int row0, int wave, int lane) {
-  const int g = lane >> 4, n = lane & 15;
-  const int ncc = (cp.nc + 15) / 16;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int blk = wave + 8 * i;
-    if (blk >= NR * ncc) break;
-    const int r = blk / ncc, cc = blk - (blk / ncc) * ncc;
-    const int ic = 16 * cc + n;
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      int ia, ib;
-      exch_row(cp, row0 + r * 16 + acc_row<false>(jj, g), ia, ib);
-      if (ia < cp.na && ib < cp.nb && ic < cp.nc) outq[((int64_t)ib * cp.na + ia) * cp.nc + ic] = yacc[i][jj] * scale;
-    }
-  }
-}
-
-// LDS regions of the fused kernel (see make_params for the layout).
-struct Lds {
-  double *sh, *baseM, *kpair, *bpair, *pqv, *box, *box1, *brae, *X, *kete;
-  int2 *ptab, *qtab;
-};
-
-// P - Q into s.pqv and [0]^(m) = (-2 rho)^m 2 pi^(5/2) / (zp zq sqrt(zp + zq))
-// w_bra w_ket F_m(rho |PQ|^2) for m = 0..L into s.baseM (eq. (md1)'s start,
-// with the pair weights of s.bpair[1], s.kpair[1] and the scale s.kpair[11]
-// folded in), for the pairs in s.bpair and s.kpair.  Called by one wave.
-__device__ __forceinline__ void hermite_base(const Lds& s, int L, const double* __restrict__ boys_tab, int lane) {
-  if (lane < 3) s.pqv[lane] = s.bpair[2 + lane] - s.kpair[2 + lane];
-  if (lane <= L) {
-    const double pref = 2.0 * pow(M_PI, 2.5);
-    const double zp = s.bpair[0], zq = s.kpair[0];
-    const double zs = zp + zq;
-    const double rho = zp * zq / zs;
-    double r2 = 0.0;
-#pragma unroll
-    for (int x = 0; x < 3; ++x) {
-      const double d = s.bpair[2 + x] - s.kpair[2 + x];
-      r2 += d * d;
-    }
-    const double F = boys_fm(lane, rho * r2, boys_tab);
-    double pw = 1.0;
-    for (int mm = 0; mm < lane; ++mm) pw *= -2.0 * rho;
-    s.baseM[lane] = pw * (pref / (zp * zq * sqrt(zs))) * (s.bpair[1] * (s.kpair[1] * s.kpair[11])) * F;
-  }
-}
-
-constexpr int kGroup = 4;  // output column blocks per second-transform pass
-
 // Power-of-two scale of [0]^(m) for the ket pair in kpair with FP32 transforms,
 // into kpair[11] and its inverse into kpair[12].  The scale brings the largest
 // product of bra and ket pair weights near 1 so that the FP32 operands of both
@@ -736,194 +487,6 @@ __device__ __forceinline__ int tiny_exponent(const double* sh, int kmax, int Ka,
   return e < -600.0 ? (int)fmax(e, -900.0) : 0;  // (room for the coefficients)
 }
 
-// Everything a workgroup does after its prologue, for NR valid row blocks and
-// NC1 first-transform column blocks of this wave.
-// SOLID: rows and columns are real solid harmonics and both transforms read
-// their H matrices from hb / hk (this quartet's, hbs / hks doubles per
-// primitive pair, pair (i, j) of shells with K1, K2 primitives at slot
-// i * K2 + j); FP64 only.
-// EXCH: no second transform either; bra rows are ordered (b, a) with a padded
-// to a multiple of 16 (exch_row), so each 16-row block has one b, and [ab|q]
-// is contracted on the matrix cores with F^b[q][c] = sum_d E_cd^q D_bd of ket
-// pair (k, l) (exchange_f_kernel, at hk + (k * kmax + l) * hks in operand
-// order), accumulated over the ket pairs into y[a][c] = sum_d (ab|cd) D_bd,
-// written to outq[(b * na + a) * nc + c] for the tile's b (FP64, Cartesian).
-template <int NR, int NC1, int LAY, bool F32, bool SOLID = false, bool EXCH = false>
-__device__ __forceinline__ void fused_body(const ClassParams& cp, const Lds& s, const double* __restrict__ boys_tab,
-                           const uint2 (&rent)[LAY == kLaySlab ? kRPerThread : kRPerBox], double* __restrict__ outq,
-                           int row0, int Ka, int Kb, int Kc, int Kd, int tid, int wave, int lane,
-                           const double* __restrict__ hb = nullptr, const double* __restrict__ hk = nullptr,
-                           int64_t hbs = 0, int64_t hks = 0) {
-  static_assert(!(SOLID && F32), "solid-harmonic output runs FP64 transforms");
-  static_assert(!(EXCH && (F32 || SOLID)), "the exchange contraction runs FP64 Cartesian transforms");
-  constexpr bool SLAB = LAY == kLaySlab;
-  const int kmax = cp.kmax;
-  const double* A = s.sh;
-  const double* B = s.sh + 3;
-  const double* C = s.sh + 6;
-  const double* D = s.sh + 9;
-  const double* ex = s.sh + 12;
-  const double* co = s.sh + 12 + 4 * kmax;
-  constexpr int NC1A = NC1 > 0 ? NC1 : 1;
-
-  // bra rows of this lane (A operand of the first transform)
-  int rowx[NR], rowy[NR], rowz[NR];
-#pragma unroll
-  for (int r = 0; r < NR && !SOLID; ++r) {
-    int ia, ib;
-    bool valid;
-    if constexpr (EXCH) {
-      exch_row(cp, row0 + r * 16 + (lane & 15), ia, ib);
-      valid = ia < cp.na && ib < cp.nb;
-    } else {
-      const int ab = row0 + r * 16 + (lane & 15);
-      valid = ab < cp.nab;
-      ia = ab / cp.nb;
-      ib = ab - ia * cp.nb;
-    }
-    if (valid) {
-      int ax, ay, az, bx, by, bz;
-      cart_of(cp.la, ia, ax, ay, az);
-      cart_of(cp.lb, ib, bx, by, bz);
-      rowx[r] = (ax * (cp.lb + 1) + bx) * cp.tbrow;
-      rowy[r] = cp.tbaxis + (ay * (cp.lb + 1) + by) * cp.tbrow;
-      rowz[r] = 2 * cp.tbaxis + (az * (cp.lb + 1) + bz) * cp.tbrow;
-    } else {
-      const int zr = (cp.la + 1) * (cp.lb + 1) * cp.tbrow;
-      rowx[r] = zr;
-      rowy[r] = cp.tbaxis + zr;
-      rowz[r] = 2 * cp.tbaxis + zr;
-    }
-  }
-  // [ab|q] columns of this lane (B operand of the first transform)
-  int offq[NC1A], tq[NC1A];
-#pragma unroll
-  for (int c = 0; c < NC1A; ++c) {
-    const int2 e = (c < NC1) ? s.qtab[(wave + 8 * c) * 16 + (lane & 15)] : make_int2(0, 0);
-    offq[c] = e.y;
-    tq[c] = (int)((unsigned)e.x >> 24);
-  }
-  const int ncbw = (wave < cp.ncdb) ? (cp.ncdb - wave + 7) / 8 : 0;  // output column blocks of this wave
-
-  const int e2 = EXCH ? tiny_exponent(s.sh, kmax, Ka, Kb, Kc, Kd) : 0;
-  StageClock clk;
-  clk.start();
-  // EXCH: y blocks (row block, 16 columns c) of this wave, kept over the ket pairs
-  d4 yacc[2] = {acc_zero<false>(), acc_zero<false>()};
-
-  for (int kl = 0; kl < Kc * Kd; ++kl) {
-    if (tid == 0) {
-      const int k = kl / Kd, l = kl - (kl / Kd) * Kd;
-      make_pair(s.kpair, ex[2 * kmax + k], ex[3 * kmax + l], co[2 * kmax + k], co[3 * kmax + l], C, D);
-      s.kpair[11] = EXCH ? ldexp(1.0, -e2) : 1.0;
-    }
-    typename Acc<F32>::type acc1[NR][NC1A];
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-      for (int c = 0; c < NC1A; ++c) acc1[r][c] = acc_zero<F32>();
-
-    for (int ij = 0; ij < Ka * Kb; ++ij) {
-      if (tid == 64) {
-        const int i = ij / Kb, j = ij - (ij / Kb) * Kb;
-        make_pair(s.bpair, ex[i], ex[kmax + j], co[i], co[kmax + j], A, B);
-      }
-      __syncthreads();
-      ERI4_STAGE(kStPair);
-      if (wave == 0) {
-        hermite_base(s, cp.L, boys_tab, lane);
-      } else if constexpr (!SOLID) {
-        if (wave == 1)
-          build_etab(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, 0.5 / s.bpair[0], s.bpair + 5, s.bpair + 8, false,
-                     lane);
-      }
-      __syncthreads();
-      ERI4_STAGE(kStBoysE);
-      if constexpr (LAY == kLayBox2)
-        hermite_r_lds2(s.box, s.box1, s.baseM, cp.L, s.pqv, rent, tid);
-      else
-        hermite_r_lds(s.box, s.baseM, cp.L, s.pqv, rent, tid);
-      ERI4_STAGE(kStR);
-      // first transform, accumulated over ij: [ab|q] += E_ab^p [p|q]
-      if constexpr (NC1 > 0 && SOLID) {
-        const int i = ij / Kb, j = ij - (ij / Kb) * Kb;
-        gemm1_h<NR, NC1, SLAB>(acc1, hb + (i * Kb + j) * hbs + (row0 / 16) * (cp.np4 * 16) + lane, s.box, s.ptab,
-                               offq, tq, cp.np4, cp.L, cp.S1, lane);
-      } else if constexpr (NC1 > 0) {
-        gemm1_pair<NR, NC1, SLAB, F32>(acc1, s.brae, s.box, s.ptab, rowx, rowy, rowz, offq, tq, cp.np4, cp.L, cp.S1, lane);
-      }
-      __syncthreads();
-      ERI4_STAGE(kStGemm1);
-    }
-
-    // [ab_tile|q] -> LDS (aliases the R box); ket tables for kl
-    if constexpr (NC1 > 0) {
-#pragma unroll
-      for (int r = 0; r < NR; ++r)
-#pragma unroll
-        for (int c = 0; c < NC1; ++c) {
-          const int cb = wave + 8 * c;
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
-            s.X[(r * 16 + acc_row<F32>(jj, lane >> 4)) * cp.xs + cb * 16 + (lane & 15)] = acc1[r][c][jj];
-        }
-    }
-    if constexpr (EXCH) {
-      // y[a][c] += sum_q [ab|q] F^b[q][c] for this ket pair; the barrier after
-      // it protects the tile (aliased by the next pair's R box) until all reads
-      __syncthreads();
-      const int k = kl / Kd, l = kl - (kl / Kd) * Kd;
-      exch_gemm<NR>(cp, s.X, hk + (k * kmax + l) * hks, row0, wave, lane, yacc);
-      __syncthreads();
-      continue;
-    }
-    if constexpr (!SOLID) {
-      if (wave == 0)
-        build_etab(s.kete, cp.lc, cp.ld, cp.tkrow, cp.tkaxis, 0.5 / s.kpair[0], s.kpair + 5, s.kpair + 8, true, lane);
-    }
-    __syncthreads();
-    ERI4_STAGE(kStMove);
-
-    // second transform, written to HBM (accumulated over kl); groups of
-    // kGroup column blocks (2 with four row blocks, for the accumulators)
-    const double unscale = s.kpair[12];
-    constexpr int G2 = NR >= 4 ? 2 : kGroup;
-    for (int g0 = 0; g0 < ncbw; g0 += G2) {
-      const int ng = min(G2, ncbw - g0);
-      const int cb0 = wave + 8 * g0;
-      const bool first = kl == 0;
-      if constexpr (SOLID) {
-        const int k = kl / Kd, l = kl - (kl / Kd) * Kd;
-        const double* hkp = hk + (k * Kd + l) * hks + lane;
-        if (ng >= 2 && G2 >= 2)
-          gemm2_group_h<NR, 2>(cp, s.X, hkp, cb0, row0, outq, first, lane);
-        else
-          gemm2_group_h<NR, 1>(cp, s.X, hkp, cb0, row0, outq, first, lane);
-        if (ng == 3) gemm2_group_h<NR, 1>(cp, s.X, hkp, cb0 + 16, row0, outq, first, lane);
-        if (ng == 4) gemm2_group_h<NR, 2>(cp, s.X, hkp, cb0 + 16, row0, outq, first, lane);
-      } else if constexpr (G2 == 4) {
-        if (ng == 4)
-          gemm2_group<NR, 4, F32>(cp, s.X, s.kete, s.qtab, cb0, row0, outq, first, unscale, lane);
-        else if (ng == 3)
-          gemm2_group<NR, 3, F32>(cp, s.X, s.kete, s.qtab, cb0, row0, outq, first, unscale, lane);
-        else if (ng == 2)
-          gemm2_group<NR, 2, F32>(cp, s.X, s.kete, s.qtab, cb0, row0, outq, first, unscale, lane);
-        else
-          gemm2_group<NR, 1, F32>(cp, s.X, s.kete, s.qtab, cb0, row0, outq, first, unscale, lane);
-      } else {
-        if (ng == 2)
-          gemm2_group<NR, 2, F32>(cp, s.X, s.kete, s.qtab, cb0, row0, outq, first, unscale, lane);
-        else
-          gemm2_group<NR, 1, F32>(cp, s.X, s.kete, s.qtab, cb0, row0, outq, first, unscale, lane);
-      }
-    }
-    __syncthreads();
-    ERI4_STAGE(kStGemm2);
-  }
-  clk.flush(tid);
-  if constexpr (EXCH) exch_store<NR>(cp, yacc, ldexp(1.0, e2), outq, row0, wave, lane);
-}
-
 // Shell data of quartet q into LDS: centres A B C D in sh[0..11], then the
 // exponents and the coefficients of shells a b c d (kmax each), and the four
 // contraction lengths in shn[0..3].  PAIRS: the bra pair is entry q / nket of
@@ -960,144 +523,6 @@ __device__ __forceinline__ void load_shells(double* sh, int* shn, int kmax, cons
       shn[tid - 256] = nprim[q * 4 + (tid - 256)];
     }
   }
-}
-
-// All the work of one tile: quartet q, bra rows rt*RB*16.., whose integrals
-// start at outq.  Called by every thread of the workgroup; ends with a barrier.
-// Shells of quartet q: from per-quartet arrays (PAIRS false: centers
-// [q][4][3], exps/coefs [q][4][kmax]) or from a bra and a ket list of shell
-// pairs (PAIRS true: bra pair q / nket, ket pair q % nket, each list centers
-// [i][2][3], exps/coefs [i][2][kmax]; centers/exps/coefs are the bra list).
-// SOLID: solid-harmonic rows and columns, H matrices from hb / hk (fused_body).
-template <int RB, int LAY, bool F32, bool PAIRS, bool SOLID = false, bool EXCH = false>
-__device__ __forceinline__ void process_tile(const ClassParams& cp, unsigned char* lds,
-                                             const double* __restrict__ boys_tab,
-                                             const uint2* __restrict__ rtab_L,
-                                             const double* __restrict__ centers, const double* __restrict__ exps,
-                                             const double* __restrict__ coefs, const int32_t* __restrict__ nprim,
-                                             double* __restrict__ outq, int64_t q, int rt, int tid, int wave,
-                                             int lane, const double* __restrict__ kcenters,
-                                             const double* __restrict__ kexps, const double* __restrict__ kcoefs,
-                                             int64_t nket, const double* __restrict__ hb = nullptr,
-                                             const double* __restrict__ hk = nullptr, int64_t hbs = 0,
-                                             int64_t hks = 0) {
-  constexpr bool SLAB = LAY == kLaySlab;
-  const int kmax = cp.kmax;
-  Lds s;
-  s.sh = (double*)(lds + cp.o_shell);
-  s.baseM = (double*)(lds + cp.o_base);
-  s.kpair = s.baseM + 32;
-  s.bpair = s.kpair + 16;
-  s.pqv = s.bpair + 16;
-  s.ptab = (int2*)(lds + cp.o_ptab);
-  s.qtab = (int2*)(lds + cp.o_qtab);
-  s.box = (double*)(lds + cp.o_union);
-  s.box1 = (double*)(lds + cp.o_box1);
-  s.brae = (double*)(lds + cp.o_brae);
-  s.X = (double*)(lds + cp.o_union);
-  s.kete = (double*)(lds + cp.o_kete);
-  int* shn = (int*)(s.sh + 12 + 8 * kmax);
-  load_shells<PAIRS>(s.sh, shn, kmax, centers, exps, coefs, nprim, q, kcenters, kexps, kcoefs, nket, tid);
-  build_htab(s.ptab, cp.Lb, cp.np, cp.np4, cp.S1, cp.S2, SLAB, tid);
-  build_htab(s.qtab, cp.Lk, cp.nq, 16 * cp.nqb, cp.S1, cp.S2, SLAB, tid);
-  uint2 rent[SLAB ? kRPerThread : kRPerBox];
-  load_rtab(rent, rtab_L, cp.L, tid);
-  __syncthreads();
-
-  const int Ka = shn[0], Kb = shn[1], Kc = shn[2], Kd = shn[3];
-  const int row0 = rt * RB * 16;
-  if (Ka < 1 || Ka > kmax || Kb < 1 || Kb > kmax || Kc < 1 || Kc > kmax || Kd < 1 || Kd > kmax) {
-    if constexpr (EXCH) {
-      // this tile's rows (b, a) of y
-      for (int i = tid; i < RB * 16 * cp.nc; i += kThreads) {
-        int ia, ib;
-        exch_row(cp, row0 + i / cp.nc, ia, ib);
-        if (ia < cp.na && ib < cp.nb) outq[((int64_t)ib * cp.na + ia) * cp.nc + i % cp.nc] = __builtin_nan("");
-      }
-    } else {
-      const int nrows = min(RB * 16, cp.nab - row0);
-      const int ncols = cp.ncd;
-      double* o = outq + (int64_t)row0 * ncols;
-      for (int i = tid; i < nrows * ncols; i += kThreads) o[i] = __builtin_nan("");
-    }
-    __syncthreads();
-    return;
-  }
-  const int nc1 = (wave < cp.nqb) ? min(kMaxC1, (cp.nqb - wave + 7) / 8) : 0;  // [ab|q] column blocks of this wave
-  const int nrows_all = EXCH ? cp.nb * 16 * ((cp.na + 15) / 16) : cp.nab;           // (padded) bra rows
-  const int nrv = min(RB, (nrows_all - row0 + 15) / 16);                          // valid row blocks of this tile
-#define BODY(NR, NC1) \
-  fused_body<NR, NC1, LAY, F32, SOLID, EXCH>(cp, s, boys_tab, rent, outq, row0, Ka, Kb, Kc, Kd, tid, wave, lane, hb, \
-                                             hk, hbs, hks)
-  constexpr int NR2 = RB >= 2 ? 2 : 1;
-  if constexpr (RB == 4) {
-    // 64-row tiles (kets with at most 2 column blocks per wave): the last tile
-    // of a quartet runs with padding rows, whose outputs are not written
-    switch (nc1) {
-      case 0: BODY(4, 0); break;
-      case 1: BODY(4, 1); break;
-      default: BODY(4, 2); break;
-    }
-  } else if (nrv == NR2 && NR2 == 2) {
-    switch (nc1) {
-      case 0: BODY(NR2, 0); break;
-      case 1: BODY(NR2, 1); break;
-      case 2: BODY(NR2, 2); break;
-      case 3: BODY(NR2, 3); break;
-      default: BODY(NR2, 4); break;
-    }
-  } else if constexpr (SLAB) {
-    switch (nc1) {
-      case 0: BODY(1, 0); break;
-      case 1: BODY(1, 1); break;
-      case 2: BODY(1, 2); break;
-      case 3: BODY(1, 3); break;
-      case 4: BODY(1, 4); break;
-      case 5: BODY(1, 5); break;
-      default: BODY(1, 6); break;
-    }
-  } else {
-    switch (nc1) {
-      case 0: BODY(1, 0); break;
-      case 1: BODY(1, 1); break;
-      case 2: BODY(1, 2); break;
-      case 3: BODY(1, 3); break;
-      default: BODY(1, 4); break;
-    }
-  }
-#undef BODY
-}
-
-// Solid-harmonic output, one class: as eri4_fused_kernel with rows and columns
-// over real solid harmonics (cp.nab = (2la+1)(2lb+1), cp.ncd = (2lc+1)(2ld+1)).
-// The H matrices of quartet q0 + i sit at hbra + i * kmax^2 * hbs and
-// hket + i * kmax^2 * hks (solid_h_kernel).
-template <int RB, int LAY>
-__global__ __launch_bounds__(kThreads, 1) void eri4_solid_kernel(
-    const ClassParams cp, const double* __restrict__ boys_tab, const uint2* __restrict__ rtab,
-    const double* __restrict__ centers, const double* __restrict__ exps,
-    const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ out,
-    int64_t q0, const double* __restrict__ hbra, const double* __restrict__ hket, int64_t hbs, int64_t hks) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t i = blockIdx.x / cp.nrt;
-  const int64_t q = q0 + i;
-  const int rt = blockIdx.x % cp.nrt;
-  const int64_t kk2 = (int64_t)cp.kmax * cp.kmax;
-  process_tile<RB, LAY, false, false, true>(cp, lds, boys_tab, rtab + cp.rtab_off, centers, exps, coefs, nprim,
-                                            out + q * (int64_t)cp.nab * cp.ncd, q, rt, tid, wave, lane, nullptr,
-                                            nullptr, nullptr, 0, hbra + i * kk2 * hbs, hket + i * kk2 * hks, hbs,
-                                            hks);
-}
-
-template <int RB, int LAY>
-hipError_t solid_launch_t(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
-                          const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0,
-                          const double* hbra, const double* hket, int64_t hbs, int64_t hks) {
-  hipLaunchKernelGGL((eri4_solid_kernel<RB, LAY>), grid, dim3(kThreads), p.lds_bytes, s, p, t.boys, t.rtab, centers,
-                     exps, coefs, nprim, out, q0, hbra, hket, hbs, hks);
-  return hipGetLastError();
 }
 
 }  // namespace

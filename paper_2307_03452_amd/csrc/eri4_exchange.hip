@@ -6,7 +6,7 @@
 // cores instead of running the second transform (rows of a tile ordered
 // (b, a), one b per 16-row block), and a last kernel sums the per-b partial
 // rows y^b[a][c] = sum_d (ab|cd) D_bd over b in a fixed order.
-#include "eri4_device.h"
+#include "eri4_dense.h"
 
 namespace eri4 {
 namespace {
@@ -122,14 +122,12 @@ __global__ __launch_bounds__(kThreads, 1) void exchange_f_kernel(
 }
 
 // One workgroup = one quartet x one tile of RB*16 bra rows in (b, a) order
-// (eri4_fused_kernel with the exchange contraction); the tile's y^b rows go to
-// part + q * nb * na * nc.
-template <int RB, int LAY>
+// (dense_tile); the tile's y^b rows go to part + q * nb * na * nc.
+template <int RB, bool SLAB>
 __global__ __launch_bounds__(kThreads, 1) void eri4_exchange_kernel(
-    const ClassParams cp, const double* __restrict__ boys_tab, const uint2* __restrict__ rtab,
-    const double* __restrict__ centers, const double* __restrict__ exps, const double* __restrict__ coefs,
-    const int32_t* __restrict__ nprim, double* __restrict__ part, int64_t q0, const double* __restrict__ fb,
-    int64_t fss) {
+    const ClassParams cp, const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps,
+    const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ part, int64_t q0,
+    const double* __restrict__ fb, int64_t fss) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -137,10 +135,9 @@ __global__ __launch_bounds__(kThreads, 1) void eri4_exchange_kernel(
   const int64_t q = q0 + i;
   const int rt = blockIdx.x % cp.nrt;
   const int64_t kk2 = (int64_t)cp.kmax * cp.kmax;
-  process_tile<RB, LAY, false, false, false, true>(
-      cp, lds, boys_tab, rtab + cp.rtab_off, centers, exps, coefs, nprim,
-      part + i * (int64_t)cp.nb * cp.na * cp.nc, q, rt, tid, wave, lane, nullptr, nullptr, nullptr, 0, nullptr,
-      fb + i * kk2 * fss, 0, fss);
+  dense_tile<RB, SLAB, false, true>(cp, lds, tb, centers, exps, coefs, nprim,
+                                    part + i * (int64_t)cp.nb * cp.na * cp.nc, q, rt, tid, wave, lane, nullptr,
+                                    nullptr, nullptr, 0, nullptr, fb + i * kk2 * fss, 0, fss);
 }
 
 // K[q0 + blockIdx.x][a][c] = sum over b = 0..nb-1, in that order, of the
@@ -157,22 +154,21 @@ __global__ void exchange_reduce_kernel(const ClassParams cp, const double* __res
   }
 }
 
-template <int RB, int LAY>
+template <int RB, bool SLAB>
 hipError_t exchange_launch_t(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
                              const double* exps, const double* coefs, const int32_t* nprim, double* part, int64_t q0,
                              const double* fb, int64_t fss) {
-  hipLaunchKernelGGL((eri4_exchange_kernel<RB, LAY>), grid, dim3(kThreads), p.lds_bytes, s, p, t.boys, t.rtab, centers,
-                     exps, coefs, nprim, part, q0, fb, fss);
+  hipLaunchKernelGGL((eri4_exchange_kernel<RB, SLAB>), grid, dim3(kThreads), p.lds_bytes, s, p, t, centers, exps,
+                     coefs, nprim, part, q0, fb, fss);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t exchange_set_attrs() {
-  const void* k[8] = {(const void*)eri4_exchange_kernel<1, kLayBox>,  (const void*)eri4_exchange_kernel<2, kLayBox>,
-                      (const void*)eri4_exchange_kernel<4, kLayBox>,  (const void*)eri4_exchange_kernel<1, kLaySlab>,
-                      (const void*)eri4_exchange_kernel<2, kLaySlab>, (const void*)eri4_exchange_kernel<1, kLayBox2>,
-                      (const void*)eri4_exchange_kernel<2, kLayBox2>, (const void*)eri4_exchange_kernel<4, kLayBox2>};
+  const void* k[5] = {(const void*)eri4_exchange_kernel<1, false>, (const void*)eri4_exchange_kernel<2, false>,
+                      (const void*)eri4_exchange_kernel<4, false>, (const void*)eri4_exchange_kernel<1, true>,
+                      (const void*)eri4_exchange_kernel<2, true>};
   for (const void* f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     if (e != hipSuccess) return e;
@@ -193,18 +189,11 @@ hipError_t exchange_launch(const ClassParams& p, int64_t nq, hipStream_t s, cons
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)(nq * p.nrt));
   const int64_t fss = fbs * p.nb;  // doubles per ket pair slot
-  const bool two = p.rb == 2;
-#define L(RB, LAY) exchange_launch_t<RB, LAY>(p, grid, s, t, centers, exps, coefs, nprim, part, q0, fb, fss)
-  switch (p.lay) {
-    case kLaySlab:
-      e = two ? L(2, kLaySlab) : L(1, kLaySlab);
-      break;
-    case kLayBox2:
-      e = p.rb == 4 ? L(4, kLayBox2) : (two ? L(2, kLayBox2) : L(1, kLayBox2));
-      break;
-    default:
-      e = p.rb == 4 ? L(4, kLayBox) : (two ? L(2, kLayBox) : L(1, kLayBox));
-  }
+#define L(RB, SLAB) exchange_launch_t<RB, SLAB>(p, grid, s, t, centers, exps, coefs, nprim, part, q0, fb, fss)
+  if (p.slab)
+    e = p.rb == 2 ? L(2, true) : L(1, true);
+  else
+    e = p.rb == 4 ? L(4, false) : p.rb == 2 ? L(2, false) : L(1, false);
 #undef L
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(exchange_reduce_kernel, dim3((unsigned)nq), dim3(256), 0, s, p, part, out, q0);

@@ -153,12 +153,13 @@ struct ClassParams {
   int slab;            // R layout: 0 box, 1 slab
   int rb;              // 16-row blocks per tile (1, 2, or 4 with a box layout)
   int lay;             // kLayBox, kLaySlab or kLayBox2 (slab == (lay == kLaySlab))
-  int o_box1;          // kLayBox2: byte offset of the second R box
   // LDS layout (byte offsets)
   int o_union;   // phase 1: R box then bra tables; phase 2: [ab|q] tile then ket tables
   int o_brae;    // bra tables (phase 1)
   int o_kete;    // ket tables (phase 2)
   int o_ptab, o_qtab, o_base, o_shell;
+  int o_rowt, o_rs, o_rv, o_zt, o_h;        // recursion of the solid and exchange kernels (eri4_dense.h)
+  int ntask, o_uv, o_task, o_hexp;          // and its tables (make_tile_tables), in words
   int lds_bytes;
 };
 

@@ -3,7 +3,7 @@
 // read them, one instance per tile height and R layout.
 #include <algorithm>
 
-#include "eri4_device.h"
+#include "eri4_dense.h"
 
 namespace eri4 {
 namespace {
@@ -203,8 +203,7 @@ template <bool PAIRS>
 __global__ __launch_bounds__(kThreads, 1) void eri4_plan_solid_kernel(
     const ClassParams* __restrict__ classes, const int2* __restrict__ items, int nitems,
     const int64_t* __restrict__ qoff, const int32_t* __restrict__ nprim, int* __restrict__ counter,
-    const double* __restrict__ boys_tab, const uint2* __restrict__ rtab, const double* __restrict__ centers,
-    const double* __restrict__ exps, const double* __restrict__ coefs, double* __restrict__ out,
+    const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps, const double* __restrict__ coefs, double* __restrict__ out,
     const double* __restrict__ kcenters, const double* __restrict__ kexps, const double* __restrict__ kcoefs,
     int64_t nket, int64_t nbra, const int64_t* __restrict__ hoff, const double* __restrict__ h) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -222,7 +221,6 @@ __global__ __launch_bounds__(kThreads, 1) void eri4_plan_solid_kernel(
     const int rc = __builtin_amdgcn_readfirstlane(w.y);
     const ClassParams cp = classes[rc >> 16];
     const int rt = rc & 0xffff;
-    const uint2* rt_L = rtab + cp.rtab_off;
     double* oq = out + qoff[q];
     const double* hb;
     const double* hk;
@@ -236,19 +234,46 @@ __global__ __launch_bounds__(kThreads, 1) void eri4_plan_solid_kernel(
     }
     const int64_t hbs = (int64_t)solid_pair_units(cp.la, cp.lb, false) * 16 * cp.np4;
     const int64_t hks = (int64_t)cp.ncdb * 16 * cp.nq4;
-#define T(RB, LAY)                                                                                                   \
-  process_tile<RB, LAY, false, PAIRS, true>(cp, lds, boys_tab, rt_L, centers, exps, coefs, nprim, oq, q, rt, tid, wave, \
-                                           lane, kcenters, kexps, kcoefs, nket, hb, hk, hbs, hks)
-    const int lay = cp.lay;
-    if (lay == kLaySlab) {
-      if (cp.rb == 2) T(2, kLaySlab); else T(1, kLaySlab);
-    } else if (lay == kLayBox2) {
-      if (cp.rb == 4) T(4, kLayBox2); else if (cp.rb == 2) T(2, kLayBox2); else T(1, kLayBox2);
+#define T(RB, SLAB)                                                                                             \
+  dense_tile<RB, SLAB, PAIRS, false>(cp, lds, tb, centers, exps, coefs, nprim, oq, q, rt, tid, wave, lane, kcenters, \
+                                     kexps, kcoefs, nket, hb, hk, hbs, hks)
+    if (cp.slab) {
+      if (cp.rb == 2) T(2, true); else T(1, true);
     } else {
-      if (cp.rb == 4) T(4, kLayBox); else if (cp.rb == 2) T(2, kLayBox); else T(1, kLayBox);
+      if (cp.rb == 4) T(4, false); else if (cp.rb == 2) T(2, false); else T(1, false);
     }
 #undef T
   }
+}
+
+// Solid-harmonic output, one class: one workgroup per tile of RB*16 rows over real
+// solid harmonics (cp.nab = (2la+1)(2lb+1), cp.ncd = (2lc+1)(2ld+1)).  The H
+// matrices of quartet q0 + i sit at hbra + i * kmax^2 * hbs and hket + i * kmax^2 *
+// hks (solid_h_kernel).
+template <int RB, bool SLAB>
+__global__ __launch_bounds__(kThreads, 1) void eri4_solid_kernel(
+    const ClassParams cp, const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps,
+    const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ out, int64_t q0,
+    const double* __restrict__ hbra, const double* __restrict__ hket, int64_t hbs, int64_t hks) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t i = blockIdx.x / cp.nrt;
+  const int64_t q = q0 + i;
+  const int rt = blockIdx.x % cp.nrt;
+  const int64_t kk2 = (int64_t)cp.kmax * cp.kmax;
+  dense_tile<RB, SLAB, false, false>(cp, lds, tb, centers, exps, coefs, nprim,
+                                     out + q * (int64_t)cp.nab * cp.ncd, q, rt, tid, wave, lane, nullptr, nullptr,
+                                     nullptr, 0, hbra + i * kk2 * hbs, hket + i * kk2 * hks, hbs, hks);
+}
+
+template <int RB, bool SLAB>
+hipError_t solid_launch_t(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
+                          const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0,
+                          const double* hbra, const double* hket, int64_t hbs, int64_t hks) {
+  hipLaunchKernelGGL((eri4_solid_kernel<RB, SLAB>), grid, dim3(kThreads), p.lds_bytes, s, p, t, centers, exps, coefs,
+                     nprim, out, q0, hbra, hket, hbs, hks);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -272,11 +297,11 @@ hipError_t plan_solid_launch(bool pairs, dim3 grid, int lds_bytes, hipStream_t s
   const Shells& x = a.shells;
   if (pairs)
     hipLaunchKernelGGL(eri4_plan_solid_kernel<true>, grid, dim3(kThreads), lds_bytes, s, (const ClassParams*)a.classes, a.items, a.nitems,
-                       a.qoff, a.nprim, a.counter, t.boys, t.rtab, x.centers, x.exps, x.coefs, a.out, x.kcenters,
+                       a.qoff, a.nprim, a.counter, t, x.centers, x.exps, x.coefs, a.out, x.kcenters,
                        x.kexps, x.kcoefs, x.nket, nbra, hoff, h);
   else
     hipLaunchKernelGGL(eri4_plan_solid_kernel<false>, grid, dim3(kThreads), lds_bytes, s, (const ClassParams*)a.classes, a.items,
-                       a.nitems, a.qoff, a.nprim, a.counter, t.boys, t.rtab, x.centers, x.exps, x.coefs, a.out,
+                       a.nitems, a.qoff, a.nprim, a.counter, t, x.centers, x.exps, x.coefs, a.out,
                        nullptr, nullptr, nullptr, (int64_t)0, (int64_t)0, hoff, h);
   return hipGetLastError();
 }
@@ -297,10 +322,9 @@ hipError_t solid_hpairs_launch(int64_t nbra, int64_t nentries, int kmax, int lds
 }
 
 hipError_t solid_set_attrs() {
-  const void* k[8] = {(const void*)eri4_solid_kernel<1, kLayBox>,  (const void*)eri4_solid_kernel<2, kLayBox>,
-                      (const void*)eri4_solid_kernel<4, kLayBox>,  (const void*)eri4_solid_kernel<1, kLaySlab>,
-                      (const void*)eri4_solid_kernel<2, kLaySlab>, (const void*)eri4_solid_kernel<1, kLayBox2>,
-                      (const void*)eri4_solid_kernel<2, kLayBox2>, (const void*)eri4_solid_kernel<4, kLayBox2>};
+  const void* k[5] = {(const void*)eri4_solid_kernel<1, false>, (const void*)eri4_solid_kernel<2, false>,
+                      (const void*)eri4_solid_kernel<4, false>, (const void*)eri4_solid_kernel<1, true>,
+                      (const void*)eri4_solid_kernel<2, true>};
   for (const void* f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     if (e != hipSuccess) return e;
@@ -325,18 +349,9 @@ hipError_t solid_h_launch(const ClassParams& p, int64_t nq, hipStream_t s, const
 hipError_t solid_launch(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
                         const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0,
                         const double* hbra, const double* hket, int64_t hbs, int64_t hks) {
-  const bool two = p.rb == 2;
-#define L(RB, LAY) solid_launch_t<RB, LAY>(p, grid, s, t, centers, exps, coefs, nprim, out, q0, hbra, hket, hbs, hks)
-  switch (p.lay) {
-    case kLaySlab:
-      return two ? L(2, kLaySlab) : L(1, kLaySlab);
-    case kLayBox2:
-      if (p.rb == 4) return L(4, kLayBox2);
-      return two ? L(2, kLayBox2) : L(1, kLayBox2);
-    default:
-      if (p.rb == 4) return L(4, kLayBox);
-      return two ? L(2, kLayBox) : L(1, kLayBox);
-  }
+#define L(RB, SLAB) solid_launch_t<RB, SLAB>(p, grid, s, t, centers, exps, coefs, nprim, out, q0, hbra, hket, hbs, hks)
+  if (p.slab) return p.rb == 2 ? L(2, true) : L(1, true);
+  return p.rb == 4 ? L(4, false) : p.rb == 2 ? L(2, false) : L(1, false);
 #undef L
 }
 
