@@ -429,7 +429,9 @@ void dense_layout(ClassParams* p, bool exch, const DeviceState* d) {
   p->o_h = p->o_zt + align16(nzt * 8);
   p->o_brae = p->o_zt;
   const int end = std::max(p->o_h + 3 * 64 * h_steps(p->L) * 8, exch ? p->o_brae + 3 * p->tbaxis * 8 : 0);
-  p->lds_bytes = align16(std::max(end, p->o_union + p->rb * 16 * p->xs * 8));
+  // over the tile at the end: the exchange blocks of every wave (exch_store)
+  const int tile = std::max(p->rb * 16 * p->xs, exch ? kWaves * 4 * 64 : 0);
+  p->lds_bytes = align16(std::max(end, p->o_union + tile * 8));
 }
 
 // Solid-harmonic output: the library's tile for the class, with rows and
