@@ -157,6 +157,7 @@ struct DeviceState {
   int rstart[2 * (kMaxL + 1)] = {0};  // [layout][L], in uint2 entries
   uint32_t* ttab = nullptr;  // tables of the Cartesian integral kernels (make_tile_tables)
   double* hcoef = nullptr;
+  int cus = 0;  // compute units
   Tables tables() const { return Tables{boys, rtab, ttab, hcoef}; }
 };
 
@@ -176,6 +177,7 @@ std::deque<DeviceState> g_dev;  // a deque: growing it keeps pointers to existin
 eri4_status set_attrs() {
   HIP_TRY(fused_set_attrs());
   HIP_TRY(small_set_attrs());
+  HIP_TRY(quad_set_attrs());
   HIP_TRY(solid_set_attrs());
   HIP_TRY(plan_solid_set_attrs());
   HIP_TRY(coulomb_set_attrs());
@@ -225,6 +227,7 @@ eri4_status ensure_device(DeviceState** st) {
     HIP_TRY(hipMemcpy(d.hcoef, hc.data(), hc.size() * sizeof(double), hipMemcpyHostToDevice));
     for (int i = 0; i < 2 * (kMaxL + 1); ++i) d.rstart[i] = rs[i];
     HIP_TRY(hipGetSymbolAddress((void**)&d.scratch, HIP_SYMBOL(scratch)));
+    HIP_TRY(hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev));
     eri4_status s = set_attrs();
     if (s != ERI4_SUCCESS) return s;
     d.ready = true;
@@ -409,6 +412,63 @@ bool small_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d
   return true;
 }
 
+// Parameters of the kernels of eri4_quad.hip (l <= kSmallLMax; after
+// ensure_device).  At most 153 KB of LDS: (ff|ff).
+QuadParams quad_params(int la, int lb, int lc, int ld, int kmax) {
+  QuadParams p{};
+  p.t = tile_params(la, lb, lc, ld, kmax);
+  const TileParams& t = p.t;
+  const int n2 = (t.L + 1) * (t.L + 1);
+  int off = 0;
+  auto take = [&](int bytes) { const int o = off; off += align16(bytes); return o; };
+  take((12 + 8 * kmax) * 8 + 4 * 4);
+  p.o_base = take(32 * 8);
+  p.o_rowt = take(n2 * 2);
+  p.o_rs = take(t.nzt * 4);
+  p.o_rv = take(t.nzt * 2);
+  p.o_btab = take((t.kb + 1) * 16);
+  p.o_ktab = take((t.kk + 1) * 16);
+  p.o_kcol = take(16 * t.nkblk * 4);
+  p.o_orow = take((t.nab + 31) / 32 * 32 * 4);
+  p.o_kete = take(3 * t.tkaxis * 8);
+  p.o_brae = take(2 * 3 * t.tbaxis * 8);
+  p.o_h = take(2 * 3 * 64 * h_steps(t.L) * 8);
+  p.o_zt = take(t.nzt * 8);
+  p.o_w = take(t.nr * 8);
+  // (u, v) of F: u su + v sv for u + v <= L - X; X = 0, and the least X of a second
+  // group (the ninth group's)
+  int x9 = 0;
+  for (int X = 0, n = 0; X <= t.Lb && n <= kWaves; ++X) {
+    n += std::min(la, X) - std::max(0, X - lb) + 1;
+    x9 = X;
+  }
+  const int sv = odd_row(t.Lk + 1), su = sv * (t.L + 1);
+  p.fsize = t.L * su + sv;
+  p.fsize1 = (la + 1) * (lb + 1) > kWaves ? (t.L - x9) * su + sv : 0;
+  p.nkunits = g_tix.ket[lc][ld].nunits;
+  p.o_f = take(std::max(kWaves * (p.fsize + p.fsize1), (t.nab + 31) / 32 * 32 * t.xs) * 8);
+  p.lds_bytes = off;
+  return p;
+}
+
+// Whether nq quartets of a class with l <= kSmallLMax run on the kernels of
+// eri4_quad.hip (one workgroup per compute unit, one recursion per primitive
+// quartet) or on those of eri4_small.hip (many waves per compute unit, but a
+// recursion per 32 or 48 bra rows).  Measured, quad : small in us, single
+// primitives and 5151 (K = 5 in shells a and c):
+//   256 quartets  (dd|dd) 19 : 25 and 157 : 305 (64 quartets), (ff|ss) 16 : 45 and 137
+//                 : 808 (64), (pp|ff) 16 : 19; below L = 6 ((dp|ss) 14 : 12) no gain
+//   512           (ff|ss) 29 : 46, (ff|ff) 65 : 111, (fd|dd) 38 : 44, (dd|dd) 35 : 26
+//   768           (ff|ss) 42 : 47, (ff|fp) 64 : 78, (fd|dd) 55 : 45
+//   4096          (ff|ff) 458 : 584 and 4804 : 7342, (ff|fd) 388 : 475 and 3993 : 7091,
+//                 (ff|dd) 330 : 296 and 3445 : 5069, (ff|ss) 213 : 113
+bool quad_route(int la, int lb, int lc, int ld, int kmax, int64_t nq, int cus) {
+  const int Lb = la + lb, Lk = lc + ld;
+  if (std::max(std::max(la, lb), std::max(lc, ld)) > kSmallLMax || Lb + Lk < 6) return false;
+  if (Lb == 6 && (Lk >= 5 || (Lk == 4 && kmax > 1))) return true;
+  return nq <= (int64_t)cus * (Lb == 6 ? 3 : Lb == 5 ? 2 : 1);
+}
+
 // LDS layout of the solid (exch false) and exchange kernels and the tables of their
 // recursion (their places need d, an initialised device): [r], whose
 // unused cells hold W, then zt and the per-axis tables, for exch under the bra
@@ -499,6 +559,16 @@ eri4_status eri4_batch(int la, int lb, int lc, int ld, int64_t nquartets, const 
   eri4_status s = ensure_device(&d);
   if (s != ERI4_SUCCESS) return s;
   ClassParams p;
+  if (quad_route(la, lb, lc, ld, kmax, nquartets, d->cus)) {
+    const QuadParams qp = quad_params(la, lb, lc, ld, kmax);
+    const int64_t qchunk = (int64_t)1 << 22;  // grid below 2^32 work-items
+    for (int64_t q0 = 0; q0 < nquartets; q0 += qchunk) {
+      const int64_t nq = std::min(qchunk, nquartets - q0);
+      const hipError_t e = quad_launch(qp, nq, stream, d->tables(), centers, exponents, coeffs, nprim, out, q0);
+      if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
+    }
+    return ERI4_SUCCESS;
+  }
   if (small_params(la, lb, lc, ld, kmax, d, &p)) {
     const int64_t qchunk = (int64_t)1 << 24;  // grid of qchunk workgroups of at most 256 threads
     for (int64_t q0 = 0; q0 < nquartets; q0 += qchunk) {

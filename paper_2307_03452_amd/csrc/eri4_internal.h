@@ -239,6 +239,16 @@ struct TileTableIndex {
   } bra[kTileLimits][kTableLMax + 1][kTableLMax + 1], ket[kTableLMax + 1][kTableLMax + 1];
 };
 
+// The same for the kernels of eri4_quad.hip: of t, what does not concern LDS.
+struct QuadParams {
+  TileParams t;
+  int fsize, fsize1;  // doubles of F of a wave's first and second group
+  int nkunits;   // units of the ket
+  int o_base, o_rowt, o_rs, o_rv, o_btab, o_ktab, o_kcol, o_orow;
+  int o_kete, o_brae, o_h, o_zt, o_w, o_f;
+  int lds_bytes;
+};
+
 // The same for the Coulomb (J-engine) kernels (eri4_coulomb.hip).
 struct JParams {
   int la, lb, lc, ld;

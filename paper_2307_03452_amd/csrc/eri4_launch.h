@@ -33,6 +33,11 @@ hipError_t small_launch(const ClassParams& p, int64_t nq, hipStream_t s, const T
 hipError_t small4_launch(const ClassParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
                          const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0);
 
+// One workgroup of eight waves per quartet (eri4_quad.hip): p from quad_params.
+hipError_t quad_set_attrs();
+hipError_t quad_launch(const QuadParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
+                       const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0);
+
 // Solid-harmonic output (eri4_solid.hip): the H matrices of quartets q0..q0+nq-1
 // into hbra / hket (hbs / hks doubles per primitive pair, kmax^2 pair slots
 // per quartet), then the integral kernels that read them.  stab: the device

@@ -6,6 +6,8 @@ result by up to 1e3 for the shells drawn here (exponents 0.2..5 within 1.5 Bohr)
 over fewer than 1e3 terms per step: 1e-16 * 1e3 * 1e2 relative to the largest
 integral of the quartet, 1e-11.
 """
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -40,6 +42,35 @@ def close(a, b, scale):
     assert torch.isfinite(a).all()
     d = (a - b).abs().max().item()
     assert d <= TOL * scale, (d, scale)
+
+
+LOW = [ls for ls in itertools.product(range(4), repeat=4) if sum(ls) >= 6]
+
+
+@pytest.mark.parametrize("part", range(8))
+def test_few_quartets_and_many(part):
+    """l <= 3: a few quartets take the one-workgroup form, copies of them past any
+    count at which the rule allows it (or, where it always does, as a plan) the
+    other; one contraction length is out of range."""
+    for ls in LOW[part::8]:
+        kmax = 1 + sum(ls) % 3
+        s = shells(ls, 5, kmax, 7 + part)
+        s[3][3, 1] = kmax + 1
+        few = integrals(ls, s)
+        if ls[0] + ls[1] == 6 and ls[2] + ls[3] >= 4:
+            keep = [0, 1, 2, 4]
+            t = [x[keep].contiguous() for x in s]
+            p = eri4.Plan(np.tile(np.array(ls, np.int32), (4, 1)), t[3].cpu().numpy(), kmax)
+            many = torch.empty(few[keep].numel(), dtype=torch.float64, device="cuda")
+            p.execute(*t[:3], out=many)
+            assert torch.isnan(few[3]).all()
+            few, many = few[keep], many.reshape(few[keep].shape)
+        else:
+            many = integrals(ls, [x.repeat([200] + [1] * (x.dim() - 1)) for x in s])[-5:]
+            assert torch.isnan(few[3]).all() and torch.isnan(many[3]).all()
+            few, many = few[[0, 1, 2, 4]], many[[0, 1, 2, 4]]
+        for a, b in zip(few, many):
+            close(a, b, b.abs().max().item())
 
 
 # ket orders 0..14 (the shapes of the integral kernels), bra orders at the widths of
@@ -77,3 +108,24 @@ def test_contractions_of_the_integrals(ls):
         ref = torch.tensordot(ref, c, dims=([i + 1], [1])).movedim(-1, i + 1)
     for q in range(nq):
         close(sol[q], ref[q], eri[q].abs().max().item() * 10.0)
+
+
+def test_tiny_prefactors():
+    """A quartet whose Gaussian products are near the smallest normal number keeps its
+    digits in every form, and one that underflows gives zeros."""
+    ls = (4, 4, 4, 4)
+    s = shells(ls, 3, 1, 3, np.ones((3, 4), np.int64))
+    # exp(-a b / (a + b) r^2) of both pairs together: 2^-980 and 2^-1200
+    for q, bits in ((0, 980.0), (1, 1200.0)):
+        for sh in (0, 2):
+            a, b = s[1][q, sh, 0].item(), s[1][q, sh + 1, 0].item()
+            r = (0.5 * bits * np.log(2.0) * (a + b) / (a * b)) ** 0.5
+            s[0][q, sh + 1] = s[0][q, sh] + torch.tensor([r, 0.0, 0.0], dtype=torch.float64, device="cuda")
+    eri = integrals(ls, s)
+    assert torch.isfinite(eri).all()
+    big = s[2].clone()
+    big[0] *= 2.0 ** 100  # 2^400 in all: exact
+    ref = integrals(ls, [s[0], s[1], big, s[3]])
+    m = ref[0].abs().max().item()
+    close(eri[0] * 2.0 ** 400, ref[0], m)
+    assert eri[1].abs().max().item() <= 1e-280
