@@ -394,8 +394,7 @@ bool small_four_waves(const ClassParams& p) { return p.nqb > 4; }
 // most 12 first-transform accumulator blocks of 16 x 16, spread evenly over
 // the passes: (fd|fd)'s 4 row blocks run as 2 + 2, not 3 + 1).  The [ab|q]
 // rows hold only the nq4 columns the second transform reads (the kernels
-// store no others); the one-wave kernel keeps the recursion table for L in
-// the last align16(8 nherm(L)) bytes.
+// store no others).
 bool small_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d, ClassParams* out) {
   if (la > kSmallLMax || lb > kSmallLMax || lc > kSmallLMax || ld > kSmallLMax) return false;
   const int nrb = (ncart(la) * ncart(lb) + 15) / 16, nqb = (nherm(lc + ld) + 15) / 16;
@@ -405,7 +404,21 @@ bool small_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d
   rg = (nrb + passes - 1) / passes;
   const int nq4 = (nherm(lc + ld) + 3) & ~3;
   ClassParams p = make_params(la, lb, lc, ld, kmax, rg, false, false, nq4 + 2);
-  if (!small_four_waves(p)) p.lds_bytes += align16(8 * nherm(p.L));
+  if (!small_four_waves(p)) {
+    // [r] and W, the bra tables, zt and the per-axis tables; or the [ab|q] rows and
+    // the ket tables
+    const int nzt = nuv(p.L), xb = p.o_kete - p.o_union;
+    p.o_rowt = p.o_union;
+    p.o_rs = p.o_rowt + align16((p.L + 1) * (p.L + 1) * 2);
+    p.o_rv = p.o_rs + align16(nzt * 4);
+    p.o_union = p.o_rv + align16(nzt * 2);
+    p.o_kete = p.o_union + xb;
+    p.o_brae = p.o_union + align16((r_cells(false, p.L) + (p.S1 == p.L + 1 ? p.L + 1 : 0)) * 8);
+    p.o_zt = p.o_brae + align16(3 * p.tbaxis * 8);
+    p.o_h = p.o_zt + align16(nzt * 8);
+    p.lds_bytes = align16(std::max(p.o_h + 3 * 64 * h_steps(p.L) * 8, p.o_kete + 3 * p.tkaxis * 8));
+    p.o_uv = g_tix.uv; p.o_hexp = g_tix.hexp;
+  }
   if (p.lds_bytes > kSmallLdsMax || p.nqb > 6) return false;
   p.rtab_off = d ? d->rstart[p.L] : 0;
   *out = p;

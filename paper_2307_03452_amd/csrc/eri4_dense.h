@@ -282,6 +282,25 @@ struct DenseLds {
   int2 *ptab, *qtab;
 };
 
+// Tables of row (u, v) of W, the k-th, of L+1-u-v values: it lies in the tail of the
+// k-th longest of [r]'s row tails (S1 - (L+1-n) values behind row (t, u) of n = t+u;
+// the (t, u) of largest n come last in the list uvs).  Without spare columns (S1 ==
+// L+1) the first row is one longer than any tail and goes behind the box.
+template <bool SLAB>
+__device__ __forceinline__ void w_row(const TileLds& s, const uint32_t* __restrict__ uvs, int L, int S1, int k) {
+  const uint32_t w = uvs[k];
+  const int u = (int)(w & 0xff), v = (int)((w >> 8) & 0xff), sum = (int)(w >> 24);
+  const int shift = S1 == L + 1;
+  int at = r_cells(SLAB, L);
+  if (k >= shift) {
+    const uint32_t e = uvs[nuv(L) - 1 - (k - shift)];
+    at = r_offset(SLAB, L, (int)(e & 0xff), (int)((e >> 8) & 0xff), L + 1 - (int)(e >> 24));
+  }
+  s.rowt[u * (L + 1) + v] = (uint16_t)at;
+  s.rs[k] = (uint32_t)(at | (sum << 16));
+  s.rv[k] = (uint16_t)(u | (v << 8));
+}
+
 // [r] into the box or slab layout from W: 16 rows (u, v) (the columns of the
 // product) by 16 t at a time.
 template <bool SLAB>
@@ -533,24 +552,7 @@ __device__ __forceinline__ void dense_tile(const ClassParams& cp, unsigned char*
   load_shells<PAIRS>(s.t.sh, shn, kmax, centers, exps, coefs, nprim, q, kcenters, kexps, kcoefs, nket, tid);
   build_htab(s.ptab, cp.Lb, cp.np, cp.np4, cp.S1, cp.S2, SLAB, tid);
   build_htab(s.qtab, cp.Lk, cp.nq, 16 * cp.nqb, cp.S1, cp.S2, SLAB, tid);
-  // rows (u, v) of W: the k-th, of L+1-u-v values, in the tail of the k-th longest
-  // of [r]'s row tails (S1 - (L+1-n) values behind row (t, u) of n = t+u; the (t, u)
-  // of largest n come last in the list of (u, v)).  Without spare columns (S1 ==
-  // L+1) the first row is one longer than any tail and goes behind the box.
-  if (tid < nuv(L)) {
-    const uint32_t* uvs = tb.ttab + cp.o_uv;
-    const uint32_t w = uvs[tid];
-    const int u = (int)(w & 0xff), v = (int)((w >> 8) & 0xff), sum = (int)(w >> 24);
-    const int shift = cp.S1 == L + 1;
-    int at = r_cells(SLAB, L);
-    if (tid >= shift) {
-      const uint32_t e = uvs[nuv(L) - 1 - (tid - shift)];
-      at = r_offset(SLAB, L, (int)(e & 0xff), (int)((e >> 8) & 0xff), L + 1 - (int)(e >> 24));
-    }
-    s.t.rowt[u * (L + 1) + v] = (uint16_t)at;
-    s.t.rs[tid] = (uint32_t)(at | (sum << 16));
-    s.t.rv[tid] = (uint16_t)(u | (v << 8));
-  }
+  if (tid < nuv(L)) w_row<SLAB>(s.t, tb.ttab + cp.o_uv, L, cp.S1, tid);
   // this wave's tasks of W and [r], one per lane
   const int ntask = (cp.ntask - wave + kWaves - 1) / kWaves;
   const int task = lane < ntask ? (int)tb.ttab[cp.o_task + wave + kWaves * lane] : 0;

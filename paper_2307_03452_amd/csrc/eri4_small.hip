@@ -10,55 +10,18 @@
 // the output, accumulated over the ket primitive pairs), RG bra row blocks at
 // a time, and many such waves share a compute unit, so that one quartet's
 // recursion runs while another's products occupy the matrix cores.
-#include "eri4_device.h"
+//
+// The one-wave kernel is bound by the latency of its steps: 4096 (dd|dd) quartets
+// take 63 us, their products 17 us and their output 10 us.  With the recursion as
+// three products and the 1-d tables by rows of lanes instead of level by level
+// and a table per lane, us for 1024 quartets of three primitives per shell: (pp|pp)
+// 423 -> 329, (dd|dd) 925 -> 818, (fd|fd) 2348 -> 2138; 4096 (dd|dd) 66 -> 64.
+#include "eri4_dense.h"
 
 namespace eri4 {
 namespace {
 
 constexpr int kSmallThreads = 64;
-// Hermite recursion entries per lane: nherm(12) = 455 <= 8 * 64
-constexpr int kSmallRE = 8;
-
-// eq. (md1) for decreasing m in the box layout, by one wave (entries
-// e = lane + 64 k of the recursion table for total order L, read from the
-// copy in LDS: held in registers they cost 16 VGPRs for the whole kernel).
-__device__ void hermite_r_wave(double* R, const double* baseM, int L, const double* PQ,
-                               const uint2* __restrict__ entl, int lane) {
-  if (lane == 0) R[0] = baseM[L];
-  __syncthreads();
-  const double px = PQ[0], py = PQ[1], pz = PQ[2];
-  for (int m = L - 1; m >= 0; --m) {
-    const int nact = nherm(L - m);
-    double nv[kSmallRE];
-    uint2 en[kSmallRE];
-#pragma unroll
-    for (int k = 0; k < kSmallRE; ++k) {
-      const int e = lane + k * kSmallThreads;
-      en[k] = e < nact ? entl[e] : make_uint2(0u, 0u);
-    }
-#pragma unroll
-    for (int k = 0; k < kSmallRE; ++k) {
-      const int e = lane + k * kSmallThreads;
-      if (e < nact) {
-        const int o1 = (int)(en[k].x >> 16);
-        const int o2 = (int)(en[k].y & 0xffffu);
-        const int dir = (int)((en[k].y >> 16) & 3u);
-        const int ri = (int)(en[k].y >> 18);
-        const double c1 = dir == 0 ? px : (dir == 1 ? py : pz);
-        nv[k] = c1 * R[o1] + (double)max(ri - 1, 0) * R[o2];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kSmallRE; ++k) {
-      const int e = lane + k * kSmallThreads;
-      if (e < nact && e > 0) R[en[k].x & 0xffffu] = nv[k];
-    }
-    if (lane == 0) R[0] = baseM[m];
-    __syncthreads();
-  }
-}
-
 // Second transform of the RG row blocks in X, in column groups of up to 3
 // output column blocks, written (kl == 0) or added to the output.  (Groups of
 // 4 hold 96 accumulator registers for RG = 3, which keeps the kernel from
@@ -88,22 +51,25 @@ constexpr int small_waves() { return RG * NCQ >= 12 ? 1 : 2; }
 // One quartet (q0 + blockIdx.x) per 64-lane workgroup.  RG: bra row blocks
 // held in the first transform's accumulators at a time (the X region of cp
 // holds RG * 16 rows); NCQ: 16-wide column blocks of [ab|q] (cp.nqb, at most
-// 4).  Box layout of R (cp.lay == kLayBox, L <= 12).  The last
-// align16(8 nherm(L)) bytes of the dynamic LDS hold the recursion entries.
+// 4).  Box layout of R (cp.lay == kLayBox, L <= 11); [r] comes
+// from three products (eri4_tile.h), W in the tails of its rows (w_row).
 template <int RG, int NCQ>
 __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(small_waves<RG, NCQ>()))) void eri4_small_kernel(
-    const ClassParams cp, const double* __restrict__ boys_tab, const uint2* __restrict__ rtab,
-    const double* __restrict__ centers, const double* __restrict__ exps, const double* __restrict__ coefs,
-    const int32_t* __restrict__ nprim, double* __restrict__ out, int64_t q0) {
+    const ClassParams cp, const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps,
+    const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ out, int64_t q0) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int lane = threadIdx.x;
   const int64_t q = q0 + blockIdx.x;
-  const int kmax = cp.kmax;
+  const int kmax = cp.kmax, L = cp.L;
   double* sh = (double*)(lds + cp.o_shell);
-  double* baseM = (double*)(lds + cp.o_base);
-  double* kpair = baseM + 32;
-  double* bpair = kpair + 16;
-  double* pqv = bpair + 16;
+  DenseLds s;
+  s.t.baseM = (double*)(lds + cp.o_base);
+  s.t.rowt = (uint16_t*)(lds + cp.o_rowt);
+  s.t.rs = (uint32_t*)(lds + cp.o_rs);
+  s.t.rv = (uint16_t*)(lds + cp.o_rv);
+  s.t.zt = (double*)(lds + cp.o_zt);
+  s.t.h = (double*)(lds + cp.o_h);
+  s.box = (double*)(lds + cp.o_union);
   int2* ptab = (int2*)(lds + cp.o_ptab);
   int2* qtab = (int2*)(lds + cp.o_qtab);
   double* R = (double*)(lds + cp.o_union);
@@ -120,11 +86,9 @@ __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(s
   if (lane < 4) shn[lane] = nprim[q * 4 + lane];
   build_htab<kSmallThreads>(ptab, cp.Lb, cp.np, cp.np4, cp.S1, cp.S2, false, lane);
   build_htab<kSmallThreads>(qtab, cp.Lk, cp.nq, 16 * cp.nqb, cp.S1, cp.S2, false, lane);
-  uint2* entl = (uint2*)(lds + cp.lds_bytes - ((8 * nherm(cp.L) + 15) & ~15));
-  {
-    const uint2* rt = rtab + cp.rtab_off;
-    for (int e = lane; e < nherm(cp.L); e += kSmallThreads) entl[e] = rt[e];
-  }
+  for (int k = lane; k < nuv(L); k += kSmallThreads) w_row<false>(s.t, tb.ttab + cp.o_uv, L, cp.S1, k);
+  const int hs = 64 * h_steps(L);
+  const int ntask = (nuv(L) + 15) >> 4;  // of W and [r]: 16 rows each
   __syncthreads();
   const int Ka = shn[0], Kb = shn[1], Kc = shn[2], Kd = shn[3];
   if (Ka < 1 || Ka > kmax || Kb < 1 || Kb > kmax || Kc < 1 || Kc > kmax || Kd < 1 || Kd > kmax) {
@@ -137,7 +101,6 @@ __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(s
   const double* D = sh + 9;
   const double* ex = sh + 12;
   const double* co = sh + 12 + 4 * kmax;
-  const double pref = 2.0 * pow(M_PI, 2.5);
   // columns q of this lane in each block (B operand of the first transform)
   int offq[NCQ], tq[NCQ];
 #pragma unroll
@@ -168,40 +131,49 @@ __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(s
       }
     }
     for (int kl = 0; kl < Kc * Kd; ++kl) {
-      if (lane == 0) {
-        const int k = kl / Kd, l = kl - (kl / Kd) * Kd;
-        make_pair(kpair, ex[2 * kmax + k], ex[3 * kmax + l], co[2 * kmax + k], co[3 * kmax + l], C, D);
-      }
+      const int k = kl / Kd, l = kl - (kl / Kd) * Kd;
+      const double zc = ex[2 * kmax + k], zd = ex[3 * kmax + l], iq = 1.0 / (zc + zd);
+      double cd2 = 0.0;
+#pragma unroll
+      for (int x = 0; x < 3; ++x) cd2 += (C[x] - D[x]) * (C[x] - D[x]);
+      const double wk = co[2 * kmax + k] * co[3 * kmax + l] * exp(-zc * zd * iq * cd2);
       d4 acc1[RG][NCQ];
 #pragma unroll
       for (int r = 0; r < RG; ++r)
 #pragma unroll
         for (int c = 0; c < NCQ; ++c) acc1[r][c] = acc_zero<false>();
       for (int ij = 0; ij < Ka * Kb; ++ij) {
-        if (lane == 0) {
-          const int i = ij / Kb, j = ij - (ij / Kb) * Kb;
-          make_pair(bpair, ex[i], ex[kmax + j], co[i], co[kmax + j], A, B);
-        }
-        __syncthreads();
-        if (lane < 3) pqv[lane] = bpair[2 + lane] - kpair[2 + lane];
-        if (lane <= cp.L) {
-          const double zp = bpair[0], zq = kpair[0];
-          const double zs = zp + zq;
-          const double rho = zp * zq / zs;
-          double r2 = 0.0;
+        int ln = lane;  // opaque, as in tile_body
+        asm volatile("" : "+v"(ln));
+        const int i = ij / Kb, j = ij - (ij / Kb) * Kb;
+        const double za = ex[i], zb = ex[kmax + j], iz = 1.0 / (za + zb);
+        double pq[3], ab2 = 0.0, r2 = 0.0;
 #pragma unroll
-          for (int x = 0; x < 3; ++x) {
-            const double dd = bpair[2 + x] - kpair[2 + x];
-            r2 += dd * dd;
-          }
-          const double F = boys_fm(lane, rho * r2, boys_tab);
-          double pw = 1.0;
-          for (int mm = 0; mm < lane; ++mm) pw *= -2.0 * rho;
-          baseM[lane] = pw * (pref / (zp * zq * sqrt(zs))) * (bpair[1] * kpair[1]) * F;
+        for (int x = 0; x < 3; ++x) {
+          pq[x] = (za * A[x] + zb * B[x]) * iz - (zc * C[x] + zd * D[x]) * iq;
+          ab2 += (A[x] - B[x]) * (A[x] - B[x]);
+          r2 += pq[x] * pq[x];
         }
-        build_etab<2 * kSmallLMax + 2>(brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, 0.5 / bpair[0], bpair + 5, bpair + 8, false, lane);
+        if (ln <= L) {
+          const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
+          s.t.baseM[ln] = hermite_base_m(ln, za + zb, zc + zd, r2, wb * wk, tb.boys);
+        }
+        build_htables(s.t.h, hs, tb.hcoef, tb.ttab + cp.o_hexp, pq[0], pq[1], pq[2], ln, kSmallThreads);
+        build_etab_rows(brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, ln >> 4, 4, ln & 15);
+        zero_rows(brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, ln, kSmallThreads);
         __syncthreads();
-        hermite_r_wave(R, baseM, cp.L, pqv, entl, lane);
+        if (L <= 1) {  // without products: (ps|ss) 1.5x faster
+          if (ln <= 3 * L)
+            s.box[ln == 0 ? 0 : ln == 1 ? cp.S2 : ln == 2 ? cp.S1 : 1] =
+                ln == 0 ? s.t.baseM[0] : (ln == 1 ? pq[0] : ln == 2 ? pq[1] : pq[2]) * s.t.baseM[1];
+        } else {
+          build_zt(s.t, s.t.h + 2 * hs, L, 0, 0, ln);
+          __syncthreads();
+          build_w(s.t, s.box, s.t.h + hs, L, 16 * ln, ntask, ln);
+          __syncthreads();
+          build_box<false>(s, L, cp.S1, cp.S2, 16 * ln, ntask, ln);
+        }
+        __syncthreads();
         gemm1_range<RG, NCQ, false, false>(acc1, brae, R, ptab, rowx, rowy, rowz, offq, tq, 0, cp.np4, cp.L, cp.S1,
                                            lane);
         __syncthreads();
@@ -217,7 +189,8 @@ __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(s
             for (int jj = 0; jj < 4; ++jj)
               X[(r * 16 + acc_row<false>(jj, lane >> 4)) * cp.xs + c * 16 + (lane & 15)] = acc1[r][c][jj];
           }
-      build_etab<2 * kSmallLMax + 2>(kete, cp.lc, cp.ld, cp.tkrow, cp.tkaxis, 0.5 / kpair[0], kpair + 5, kpair + 8, true, lane);
+      build_etab_rows(kete, cp.lc, cp.ld, cp.tkrow, cp.tkaxis, zc, zd, C, D, true, lane >> 4, 4, lane & 15);
+      zero_rows(kete, cp.lc, cp.ld, cp.tkrow, cp.tkaxis, lane, kSmallThreads);
       __syncthreads();
       small_gemm2<RG>(cp, X, kete, qtab, row0, outq, kl == 0, lane);
       __syncthreads();
@@ -441,8 +414,8 @@ __global__ __launch_bounds__(kSmall4Threads) __attribute__((amdgpu_waves_per_eu(
 template <int RG, int NCQ>
 hipError_t small_launch_t(const ClassParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
                           const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0) {
-  hipLaunchKernelGGL((eri4_small_kernel<RG, NCQ>), dim3((unsigned)nq), dim3(kSmallThreads), p.lds_bytes, s, p, t.boys,
-                     t.rtab, centers, exps, coefs, nprim, out, q0);
+  hipLaunchKernelGGL((eri4_small_kernel<RG, NCQ>), dim3((unsigned)nq), dim3(kSmallThreads), p.lds_bytes, s, p, t,
+                     centers, exps, coefs, nprim, out, q0);
   return hipGetLastError();
 }
 

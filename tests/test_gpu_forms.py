@@ -73,6 +73,19 @@ def test_few_quartets_and_many(part):
             close(a, b, b.abs().max().item())
 
 
+def test_smallest_classes_as_plan():
+    """Total order below 6: the one-wave kernel against the plan's."""
+    for ls in itertools.product(range(4), repeat=4):
+        if sum(ls) >= 6:
+            continue
+        s = shells(ls, 3, 2, sum(ls) + 11)
+        p = eri4.Plan(np.tile(np.array(ls, np.int32), (3, 1)), s[3].cpu().numpy(), 2)
+        a = integrals(ls, s)
+        b = p.execute(*s[:3])[: a.numel()].reshape(a.shape)
+        for x, y in zip(a, b):
+            close(x, y, y.abs().max().item())
+
+
 # ket orders 0..14 (the shapes of the integral kernels), bra orders at the widths of
 # the Coulomb kernels' chunks (8, 16, 32, 64, 128), total orders 15, 16, 17 (a second
 # block of the recursion), 19, 20, 24, 25 (layouts) and 28
