@@ -272,10 +272,12 @@ eri4_status eri4_plan_create(eri4_plan* plan, int64_t nquartets, const int32_t* 
  * size).  A tile is 16 * rows16 bra rows of one quartet (rows16 = 4 only with
  * the two box layouts and at most 16 ket column blocks, i.e. lc+ld <= 9); the Hermite integrals
  * of eq. (md1) live in LDS in one of three layouts:
- *   ERI4_LAYOUT_BOX   (L+1)^3 box, recursion in place            (L <= 24)
- *   ERI4_LAYOUT_SLAB  t-slabs, about half the space, in place      (L <= 28)
- *   ERI4_LAYOUT_BOX2  two boxes, levels alternate between them     (L <= 19)
- * where L = la+lb+lc+ld.  A choice applies to the quartets of class l whose
+ *   ERI4_LAYOUT_BOX   (L+1)^3 box                                  (L <= 24)
+ *   ERI4_LAYOUT_SLAB  t-slabs, about half the space                (L <= 28)
+ *   ERI4_LAYOUT_BOX2  the box, where LDS has room for two          (L <= 19)
+ * where L = la+lb+lc+ld.  They are the choices of solid-harmonic plans; Cartesian
+ * plans check a choice the same way and run one tiling and layout, which follow
+ * from the class.  A choice applies to the quartets of class l whose
  * product of the four contraction lengths lies in [kq_min, kq_max].
  */
 typedef enum { ERI4_LAYOUT_BOX = 0, ERI4_LAYOUT_SLAB = 1, ERI4_LAYOUT_BOX2 = 2 } eri4_layout;

@@ -1,6 +1,6 @@
 // eri4.hip -- host side of liberi4's C ABI (gfx950), and the small stage
-// kernels.  The fused and plan kernels live in eri4_device.h and are compiled
-// in eri4_fused.hip, eri4_plan64.hip and eri4_plan32.hip.
+// kernels.  The integral and contraction kernels are compiled in units of their
+// own (eri4_launch.h).
 //
 // (ab|cd) over contracted Cartesian Gaussians by the matrix form of the
 // McMurchie-Davidson scheme (Asadchev & Valeev, Sec. 2 and Sec. 3).
@@ -44,7 +44,8 @@ __global__ void zero_fill_kernel(double* __restrict__ out, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// stage kernels (same device code as the fused kernel)
+// stage kernels (Boys function and 1-d tables: device code of the integral
+// kernels; recursion: eq. (md1) level by level, which the others hold theirs against)
 // ---------------------------------------------------------------------------
 
 __global__ void boys_kernel(int mmax, int64_t n, const double* __restrict__ T, double* __restrict__ F,
@@ -268,7 +269,7 @@ ClassParams make_params(int la, int lb, int lc, int ld, int kmax, int rb, bool s
   p.o_union = off;
   const int box_b = r_cells(slab, p.L) * 8;
   p.lay = slab ? kLaySlab : (box2 ? kLayBox2 : kLayBox);
-  // phase 1: R box, bra tables[, second R box]
+  // phase 1: R box, bra tables (two-box layout: room for a second box)
   const int ph1 = align16(box_b) + (box2 ? align16(3 * p.tbaxis * 8) + box_b : 3 * p.tbaxis * 8);
   const int xb = align16(rb * 16 * p.xs * 8);
   const int ph2 = xb + 3 * p.tkaxis * 8;

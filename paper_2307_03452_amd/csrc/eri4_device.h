@@ -9,19 +9,16 @@
 //   [ab|q] = sum_p E_ab^p [p|q]                                      eq. (ab_to_hermite)
 //   (ab|cd) = sum_q E_cd^q [ab|q]                                    eq. (cd_to_hermite)
 //
-// One workgroup (8 waves) owns one quartet and a tile of RB*16 bra rows ab.
-// For each ket primitive pair kl it accumulates, over the bra primitive pairs
-// ij, the first transform [ab_tile|q] in FP64 MFMA registers (the contraction
-// is folded into the product dimension, Sec. 3), moves that tile to LDS and
-// applies the second transform straight into the output.  [p|q] is never
-// stored: its entries are gathered from the R box in LDS, whose linear layout
-// turns the index p+q into an address sum.  E entries are products of three
-// 1-d tables in LDS.  The sign (-1)^|q| is folded into the ket tables and the
-// Gaussian-product prefactors and contraction coefficients into [0]^(m).
+// Here: what several kernels share (matrix products, Boys function, 1-d tables,
+// Hermite index tables, shell data), the recursion of the stage kernel, and the
+// dense transforms of the low-l kernels.  The contraction is folded into the product dimension (Sec. 3),
+// [p|q] is gathered from [r] in LDS and never stored, the sign (-1)^|q| is part of
+// the ket tables, and the Gaussian-product prefactors and contraction coefficients
+// are part of [0]^(m).  eri4_tile.h holds the grouped scheme of the larger
+// classes, eri4_dense.h the solid-harmonic and exchange tiles.
 //
 // Everything here has internal linkage: each translation unit that launches
-// one of the kernels compiles its own copy (the fused kernels, the FP64 plan
-// kernel and the FP32 plan kernel are built in separate units, in parallel).
+// one of the kernels compiles its own copy, in parallel.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -293,17 +290,14 @@ __device__ __forceinline__ void make_pair(double* out, double za, double zb, dou
 //   acc[r][c] += sum_p E_ab[row block r][p] * box[off(p) + off(q in block c)]
 // E_ab is the product of three bra-table entries.  All LDS reads of a k step
 // are issued before its MFMAs; the next p index is fetched one step ahead.
-// gemm1_range runs the k steps kbeg..kend-1 (multiples of 4) only.
-template <int NR, int NC, bool SLAB, bool F32>
-__device__ __forceinline__ void gemm1_range(typename Acc<F32>::type (&acc)[NR][NC], const double* __restrict__ brae,
+template <int NR, int NC>
+__device__ __forceinline__ void gemm1_range(d4 (&acc)[NR][NC], const double* __restrict__ brae,
                                             const double* __restrict__ R, const int2* __restrict__ ptab,
                                             const int (&rowx)[NR], const int (&rowy)[NR], const int (&rowz)[NR],
-                                            const int (&offq)[NC], const int (&tq)[NC], int kbeg, int kend, int L,
-                                            int S1, int lane) {
-  if (kbeg >= kend) return;
+                                            const int (&offq)[NC], int np4, int lane) {
   const int g = lane >> 4;
-  int2 pt = ptab[kbeg + g];
-  for (int kk = kbeg; kk < kend; kk += 4) {
+  int2 pt = ptab[g];
+  for (int kk = 0; kk < np4; kk += 4) {
     const int tp = pt.x & 0xff, up = (pt.x >> 8) & 0xff, vp = (pt.x >> 16) & 0xff;
     double ex[NR], ey[NR], ez[NR], b[NC];
 #pragma unroll
@@ -313,20 +307,13 @@ __device__ __forceinline__ void gemm1_range(typename Acc<F32>::type (&acc)[NR][N
       ez[r] = brae[rowz[r] + vp];
     }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      if constexpr (SLAB) {
-        const int t = (pt.x >> 24) + tq[c];  // t of p+q selects the slab
-        b[c] = R[slab_base(t, L, S1) + pt.y + offq[c]];
-      } else {
-        b[c] = R[pt.y + offq[c]];
-      }
-    }
-    pt = ptab[min(kk + 4, kend - 4) + g];
+    for (int c = 0; c < NC; ++c) b[c] = R[pt.y + offq[c]];
+    pt = ptab[min(kk + 4, np4 - 4) + g];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const double a = ex[r] * ey[r] * ez[r];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) acc[r][c] = mfma16<F32>(a, b[c], acc[r][c]);
+      for (int c = 0; c < NC; ++c) acc[r][c] = mfma16<false>(a, b[c], acc[r][c]);
     }
   }
 }
@@ -335,11 +322,10 @@ __device__ __forceinline__ void gemm1_range(typename Acc<F32>::type (&acc)[NR][N
 // and NR row blocks, then the output write:
 //   out[ab][cd] (+)= sum_q X[ab][q] E_cd[cd][q]
 // E_cd is the product of three ket-table entries (sign of eq. (pq) folded in).
-template <int NR, int NC, bool F32, int CSTRIDE = 8>
+template <int NR, int NC, int CSTRIDE>
 __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double* __restrict__ X,
                                             const double* __restrict__ kete, const int2* __restrict__ qtab,
-                                            int cb0, int row0, double* __restrict__ outq, bool first,
-                                            double unscale, int lane) {
+                                            int cb0, int row0, double* __restrict__ outq, bool first, int lane) {
   const int g = lane >> 4, n = lane & 15;
   int kx[NC], ky[NC], kz[NC];
 #pragma unroll
@@ -360,11 +346,11 @@ __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double*
       kz[c] = 2 * cp.tkaxis + zr;
     }
   }
-  typename Acc<F32>::type acc[NR][NC];
+  d4 acc[NR][NC];
 #pragma unroll
   for (int r = 0; r < NR; ++r)
 #pragma unroll
-    for (int c = 0; c < NC; ++c) acc[r][c] = acc_zero<F32>();
+    for (int c = 0; c < NC; ++c) acc[r][c] = acc_zero<false>();
   const int xs = cp.xs, nq4 = cp.nq4;
   auto load = [&](int kk, int pk, double (&aa)[NR], double (&xx)[NC], double (&yy)[NC], double (&zz)[NC]) {
     const int tq = pk & 0xff, uq = (pk >> 8) & 0xff, vq = (pk >> 16) & 0xff;
@@ -382,7 +368,7 @@ __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double*
     for (int c = 0; c < NC; ++c) {
       const double b = xx[c] * yy[c] * zz[c];
 #pragma unroll
-      for (int r = 0; r < NR; ++r) acc[r][c] = mfma16<F32>(aa[r], b, acc[r][c]);
+      for (int r = 0; r < NR; ++r) acc[r][c] = mfma16<false>(aa[r], b, acc[r][c]);
     }
   };
   if constexpr (NR <= 2) {
@@ -423,11 +409,10 @@ __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double*
       const int cd = (cb0 + CSTRIDE * c) * 16 + n;
 #pragma unroll
       for (int jj = 0; jj < 4; ++jj) {
-        const int ab = row0 + r * 16 + acc_row<F32>(jj, g);
+        const int ab = row0 + r * 16 + acc_row<false>(jj, g);
         if (ab < cp.nab && cd < cp.ncd) {
           double* o = outq + (int64_t)ab * cp.ncd + cd;
-          double v = acc[r][c][jj];
-          if constexpr (F32) v *= unscale;
+          const double v = acc[r][c][jj];
           if (first)
             __builtin_nontemporal_store(v, o);
           else

@@ -124,12 +124,9 @@ constexpr int kRPerThread = (nherm(kMaxL) + kThreads - 1) / kThreads;  // 9, sla
 constexpr int kBoxLMax = 24;                                              // box layout only up to here
 constexpr int kRPerBox = (nherm(kBoxLMax) + kThreads - 1) / kThreads;     // 6
 constexpr int kMaxC1 = 6;  // first-transform column blocks per wave (L_ket <= 14)
-// Layouts of the R recursion (template parameter of the kernels):
-//   kLayBox   box, eq. (md1) in place (two barriers per level)
-//   kLaySlab  slab, in place
-//   kLayBox2  two boxes, levels alternate between them (one barrier per
-//             level); [r]^(0) ends in the first.  Fits in LDS up to total
-//             order kBox2LMax.
+// Layouts of [r] that a tile choice may name: kLayBox, kLaySlab, and kLayBox2, the box
+// where LDS had room for two of them (total order up to kBox2LMax): the recursion
+// needs one, so that it is the box layout with that condition.
 constexpr int kLayBox = 0, kLaySlab = 1, kLayBox2 = 2;
 constexpr int kBox2LMax = 19;
 

@@ -32,9 +32,9 @@ __device__ __forceinline__ void small_gemm2(const ClassParams& cp, const double*
                                             int row0, double* __restrict__ outq, bool first, int lane) {
   for (int cb0 = 0; cb0 < cp.ncdb; cb0 += 3) {
     switch (min(3, cp.ncdb - cb0)) {
-      case 3: gemm2_group<RG, 3, false, 1>(cp, X, kete, qtab, cb0, row0, outq, first, 1.0, lane); break;
-      case 2: gemm2_group<RG, 2, false, 1>(cp, X, kete, qtab, cb0, row0, outq, first, 1.0, lane); break;
-      default: gemm2_group<RG, 1, false, 1>(cp, X, kete, qtab, cb0, row0, outq, first, 1.0, lane); break;
+      case 3: gemm2_group<RG, 3, 1>(cp, X, kete, qtab, cb0, row0, outq, first, lane); break;
+      case 2: gemm2_group<RG, 2, 1>(cp, X, kete, qtab, cb0, row0, outq, first, lane); break;
+      default: gemm2_group<RG, 1, 1>(cp, X, kete, qtab, cb0, row0, outq, first, lane); break;
     }
   }
 }
@@ -102,12 +102,11 @@ __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(s
   const double* ex = sh + 12;
   const double* co = sh + 12 + 4 * kmax;
   // columns q of this lane in each block (B operand of the first transform)
-  int offq[NCQ], tq[NCQ];
+  int offq[NCQ];
 #pragma unroll
   for (int c = 0; c < NCQ; ++c) {
     const int2 e = qtab[c * 16 + (lane & 15)];
     offq[c] = e.y;
-    tq[c] = 0;
   }
 
   for (int row0 = 0; row0 < cp.nab; row0 += RG * 16) {
@@ -174,8 +173,7 @@ __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(s
           build_box<false>(s, L, cp.S1, cp.S2, 16 * ln, ntask, ln);
         }
         __syncthreads();
-        gemm1_range<RG, NCQ, false, false>(acc1, brae, R, ptab, rowx, rowy, rowz, offq, tq, 0, cp.np4, cp.L, cp.S1,
-                                           lane);
+        gemm1_range<RG, NCQ>(acc1, brae, R, ptab, rowx, rowy, rowz, offq, cp.np4, lane);
         __syncthreads();
       }
       // [ab|q] of the RG row blocks -> LDS (over the R box), ket tables
@@ -310,12 +308,11 @@ __global__ __launch_bounds__(kSmall4Threads) __attribute__((amdgpu_waves_per_eu(
   const int rw = SPLIT ? wave >> 1 : 0;  // its row block (SPLIT)
   // column block c of this wave, and whether it is one (not a repeat)
   auto col_block = [&](int c) { return SPLIT ? 3 * (wave & 1) + c : wave + 4 * c; };
-  int offq[NC1], tq[NC1];
+  int offq[NC1];
 #pragma unroll
   for (int c = 0; c < NC1; ++c) {
     const int cb = min(col_block(c), cp.nqb - 1);
     offq[c] = qtab[cb * 16 + (lane & 15)].y;
-    tq[c] = 0;
   }
 
   for (int row0 = 0; row0 < cp.nab; row0 += RG * 16) {
@@ -382,8 +379,7 @@ __global__ __launch_bounds__(kSmall4Threads) __attribute__((amdgpu_waves_per_eu(
         __syncthreads();
         hermite_r_4w(R, baseM, cp.L, pqv, ent, tid);
         if (col_block(0) < cp.nqb)
-          gemm1_range<NR1, NC1, false, false>(acc1, brae, R, ptab, rowx, rowy, rowz, offq, tq, 0, cp.np4, cp.L, cp.S1,
-                                              lane);
+          gemm1_range<NR1, NC1>(acc1, brae, R, ptab, rowx, rowy, rowz, offq, cp.np4, lane);
         __syncthreads();
       }
       // [ab|q] of this wave's blocks -> LDS (over the R box), ket tables
@@ -405,7 +401,7 @@ __global__ __launch_bounds__(kSmall4Threads) __attribute__((amdgpu_waves_per_eu(
       __syncthreads();
       // second transform: output column blocks wave, wave + 4, ...
       for (int cb0 = wave; cb0 < cp.ncdb; cb0 += 4)
-        gemm2_group<RG, 1, false, 4>(cp, X, kete, qtab, cb0, row0, outq, kl == 0, 1.0, lane);
+        gemm2_group<RG, 1, 4>(cp, X, kete, qtab, cb0, row0, outq, kl == 0, lane);
       __syncthreads();
     }
   }
