@@ -93,14 +93,19 @@ __device__ __forceinline__ void build_h(int l1, int l2, bool ket, const double* 
     const int kk = c0 + n;
     const int hx = kk < nk4 ? htab[kk].x : Lh + 1;
     const int t = hx & 0xff, u = (hx >> 8) & 0xff, w = (hx >> 16) & 0xff;
-    // P[m1][b][k] = sum_a C_1[m1][a] E_ab^k, one 16 x 16 block per b
+    const int t0 = __builtin_amdgcn_readfirstlane(htab[c0].x) & 0xff;  // the chunk's least t
+    // P[m1][b][k] = sum_a C_1[m1][a] E_ab^k, one 16 x 16 block per b; E is zero for
+    // ax < t - bx: the sum ends with the last a (ax decreasing) of ax >= t0 - bx
+    // ((ii|: 71% of the products; 512 (ii|ii) quartets 1.69 -> 1.61 ms in all)
     for (int b = wave; b < n2c; b += kWaves) {
-      const int cb = cart[1][b];
+      const int cb = __builtin_amdgcn_readfirstlane(cart[1][b]);
       const int bx = cb & 0xff, by = (cb >> 8) & 0xff, bz = (cb >> 16) & 0xff;
+      const int nx = l1 + 1 - max(0, t0 - bx);  // of l1 + 1 values of ax
+      const int nst = nx > 0 ? min(ks1, (nx * (nx + 1) / 2 + 3) >> 2) : 0;
       d4 acc = acc_zero<false>();
 #pragma unroll
       for (int st = 0; st < kHSteps; ++st) {
-        if (st < ks1) {
+        if (st < nst) {
           const int axp = ra[st];
           const int ax = axp & 0xff, ay = (axp >> 8) & 0xff, az = (axp >> 16) & 0xff;
           const double e = tabs[(ax * (l2 + 1) + bx) * trow + t] * tabs[taxis + (ay * (l2 + 1) + by) * trow + u] *
