@@ -10,6 +10,10 @@ its first ':').
   python -m paper_2307_03452_amd.autotune [--lvals 4,5,6,7] [--only-with 7] [--buckets 0,1,2]
                                           [--merge] [--reps 2]
 
+A choice decides rows and layout of solid-harmonic plans; Cartesian plans check it
+and run one tiling of their own, so that what is timed here (Cartesian plans) no
+longer tells choices apart: the committed table is of the kernels before.
+
 The buckets are ranges of K_a K_b K_c K_d (primitive quartets per quartet);
 each is timed at one contraction length per shell inside it.  --only-with l
 tunes only the classes with a shell of angular momentum l; --merge keeps the

@@ -387,7 +387,8 @@ class Plan:
     precision: "fp64" or "fp32", the arithmetic of the two transforms.
     tiles: optional tile choices (see tile_choices), e.g. an autotuner's table;
     tune_file: or the path of a tile table file the library reads itself
-    (eri4_plan_create_tunefile; TUNE_FILE is the one tuned here).
+    (eri4_plan_create_tunefile; TUNE_FILE is the one tuned here).  Choices are
+    checked against the classes; the tiling of these plans follows from the class.
     """
 
     def __init__(self, lq, nprim, kmax: int, precision: str = "fp64", tiles=None, tune_file=None):
