@@ -484,8 +484,8 @@ bool quad_route(int la, int lb, int lc, int ld, int kmax, int64_t nq, int cus) {
 
 // LDS layout of the solid (exch false) and exchange kernels and the tables of their
 // recursion (their places need d, an initialised device): [r], whose
-// unused cells hold W, then zt and the per-axis tables, for exch under the bra
-// tables; or the [ab|q] tile.  It fits wherever the layout of make_params does
+// unused cells hold W, then zt and the per-axis tables, for exch the bra tables
+// (behind or over them); or the [ab|q] tile.  It fits wherever the layout of make_params does
 // (checked over all classes, tiles and layouts), without the second box that the
 // two-box layout once held.
 void dense_layout(ClassParams* p, bool exch, const DeviceState* d) {
@@ -500,8 +500,12 @@ void dense_layout(ClassParams* p, bool exch, const DeviceState* d) {
   p->o_union = p->o_rv + align16(nzt * 2);
   p->o_zt = p->o_union + align16((r_cells(p->slab, p->L) + (p->S1 == p->L + 1 ? p->L + 1 : 0)) * 8);
   p->o_h = p->o_zt + align16(nzt * 8);
-  p->o_brae = p->o_zt;
-  const int end = std::max(p->o_h + 3 * 64 * h_steps(p->L) * 8, exch ? p->o_brae + 3 * p->tbaxis * 8 : 0);
+  int end = p->o_h + 3 * 64 * h_steps(p->L) * 8;
+  const int etab = exch ? align16(3 * p->tbaxis * 8) : 0;
+  // the bra tables in a place of their own where there is room (one workgroup runs
+  // per compute unit in any case), else over zt and the per-axis tables
+  p->o_brae = end + etab <= kMaxLdsBytes ? end : p->o_zt;
+  end = std::max(end, p->o_brae + etab);
   // over the tile at the end: the exchange blocks of every wave (exch_store)
   const int tile = std::max(p->rb * 16 * p->xs, exch ? kWaves * 4 * 64 : 0);
   p->lds_bytes = align16(std::max(end, p->o_union + tile * 8));

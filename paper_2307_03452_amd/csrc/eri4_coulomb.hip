@@ -345,14 +345,18 @@ __device__ __forceinline__ void jengine_quartet(
       // dket to its items; zt (three blocks at most)
       const double* __restrict__ dq = dket + (int64_t)((kl / Kd) * kmax + kl - (kl / Kd) * Kd) * cp.ds;
       for (int i = ti; i < cp.nq; i += kThreads) s.d[ttab[cp.o_qpos + i]] = dq[i];
-      if (wave < 3) {
-        const int jb = wave == 2, ub = wave == 1;
-        if (L >= 16 * (jb + ub)) build_zt(s.t, s.t.h + 2 * hs, L, jb, ub, la_);
+      if (L == 0) {
+        if (ti == 0) s.R[s.vrow[0] & 0xffff] = s.t.baseM[0];
+      } else {
+        if (wave < 3) {
+          const int jb = wave == 2, ub = wave == 1;
+          if (L >= 16 * (jb + ub)) build_zt(s.t, s.t.h + 2 * hs, L, jb, ub, la_);
+        }
+        __syncthreads();
+        build_w(s.t, W, s.t.h + hs, L, task, ntask, la_);
+        __syncthreads();
+        build_r(s, W, s.t.h, L, task, ntask, la_);
       }
-      __syncthreads();
-      build_w(s.t, W, s.t.h + hs, L, task, ntask, la_);
-      __syncthreads();
-      build_r(s, W, s.t.h, L, task, ntask, la_);
       __syncthreads();
       if (kl + 1 < nkl)
         prepare(ij, kl + 1, ti);

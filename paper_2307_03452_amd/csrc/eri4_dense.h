@@ -403,6 +403,7 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
   const int ncbw = (wave < cp.ncdb) ? (cp.ncdb - wave + 7) / 8 : 0;  // output column blocks of this wave
 
   const int hs = 64 * h_steps(L);
+  const bool over = cp.o_brae == cp.o_zt;
   const int e2 = tiny_exponent(s.t.sh, kmax, Ka, Kb, Kc, Kd);
   const double scale = ldexp(1.0, -e2), unscale = ldexp(1.0, e2);
   // EXCH: y blocks (row block, 16 columns c) of this wave, kept over the ket pairs
@@ -421,11 +422,12 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
       int ti = tid;  // opaque, as in tile_body
       asm volatile("" : "+v"(ti));
       const int la_ = ti & 63;
-      // [0]^(m) (wave 0) and the per-axis tables (the other waves)
+      // [0]^(m) (wave 0) and the per-axis tables, with room the bra tables too (the
+      // other waves); [r] of order 0 and 1 without products
+      double pq[3];
       {
         const double za = ex[i], zb = ex[kmax + j], zc = ex[2 * kmax + k], zd = ex[3 * kmax + l];
         const double iz = 1.0 / (za + zb), iq = 1.0 / (zc + zd);
-        double pq[3];
 #pragma unroll
         for (int x = 0; x < 3; ++x) pq[x] = (za * A[x] + zb * B[x]) * iz - (zc * C[x] + zd * D[x]) * iq;
         if (wave == 0) {
@@ -442,26 +444,39 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
             s.t.baseM[la_] = hermite_base_m(la_, za + zb, zc + zd, r2, wb * (wk * scale), tb.boys);
           }
         } else {
-          build_htables(s.t.h, hs, tb.hcoef, tb.ttab + cp.o_hexp, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
+          if (L > 1)
+            build_htables(s.t.h, hs, tb.hcoef, tb.ttab + cp.o_hexp, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
+          if (EXCH && !over) {
+            build_etab_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, (ti >> 4) - 4,
+                            kWaves * 4 - 4, la_ & 15);
+            if (wave == kWaves - 1) zero_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, la_, 64);
+          }
         }
       }
       __syncthreads();
-      if (wave < 3) {
-        const int jb = wave == 2, ub = wave == 1;
-        if (L >= 16 * (jb + ub)) build_zt(s.t, s.t.h + 2 * hs, L, jb, ub, la_);
+      if (L <= 1) {
+        if (ti <= 3 * L)
+          s.box[ti == 0 ? 0 : r_offset(SLAB, L, ti == 1, ti == 2, ti == 3)] =
+              ti == 0 ? s.t.baseM[0] : (ti == 1 ? pq[0] : ti == 2 ? pq[1] : pq[2]) * s.t.baseM[1];
+      } else {
+        if (wave < 3) {
+          const int jb = wave == 2, ub = wave == 1;
+          if (L >= 16 * (jb + ub)) build_zt(s.t, s.t.h + 2 * hs, L, jb, ub, la_);
+        }
+        __syncthreads();
+        build_w(s.t, s.box, s.t.h + hs, L, task, ntask, la_);
+        __syncthreads();
+        build_box<SLAB>(s, L, cp.S1, cp.S2, task, ntask, la_);
       }
-      __syncthreads();
-      build_w(s.t, s.box, s.t.h + hs, L, task, ntask, la_);
-      __syncthreads();
-      build_box<SLAB>(s, L, cp.S1, cp.S2, task, ntask, la_);
       __syncthreads();
       // first transform, accumulated over ij: [ab|q] += A_ab^p [p|q]
       if constexpr (EXCH) {
-        // (over zt and the per-axis tables)
-        build_etab_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, ex[i], ex[kmax + j], A, B, false, ti >> 4,
-                        kThreads / 16, la_ & 15);
-        zero_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, ti, kThreads);
-        __syncthreads();
+        if (over) {  // the bra tables over zt and the per-axis tables
+          build_etab_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, ex[i], ex[kmax + j], A, B, false, ti >> 4,
+                          kThreads / 16, la_ & 15);
+          zero_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, ti, kThreads);
+          __syncthreads();
+        }
         if constexpr (NC1 > 0) {
           gemm1_e<NR, NC1, SLAB>(acc1, s.brae, s.box, s.ptab, rowx, rowy, rowz, offq, tq, 0, kmin, L,
                                             cp.S1, lane);
