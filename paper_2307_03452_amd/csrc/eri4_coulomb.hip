@@ -270,7 +270,8 @@ __device__ __forceinline__ void jengine_quartet(
   }
   if (tid <= L) s.vrow[tid] = jrow_start(L, tid) | (((L + 1 - 2 * (tid >> 1)) | 1) << 16);
   if (tid < cp.nitems) s.item[tid] = make_uint2(ttab[cp.o_item + 2 * tid], ttab[cp.o_item + 2 * tid + 1]);
-  // places of [r] and dket that no step writes are read (and not used)
+  // places between the rows of [r] and of dket are read too; what they add is 0 times
+  // a value of dket or of [r], or goes to w that nobody reads
   for (int i = tid; i < cp.rsize; i += kThreads) s.R[i] = 0.0;
   for (int i = tid; i < cp.dsize; i += kThreads) s.d[i] = 0.0;
   // this wave's tasks of W and [r], one per lane
@@ -389,6 +390,12 @@ __device__ __forceinline__ void jengine_quartet(
       }
       __syncthreads();
     }
+    // the places the parts took, for the next bra pair: zero again between [r]'s rows
+    // (a value left there would reach w that nobody reads, be left there in turn, and
+    // grow by the density with every bra pair until it is infinite, and 0 times that
+    // reaches w that is read)
+    if (ij + 1 < ij1)
+      for (int i = tid; i < 12 * kThreads / 2; i += kThreads) s.R[kJPad + i] = 0.0;
     if (tid < cp.nchunk) {
 #pragma unroll
       for (int b = 0; b < 3; ++b) {
