@@ -297,8 +297,9 @@ __device__ __forceinline__ void jengine_quartet(
   const double* ex = s.t.sh + 12;
   const double* co = s.t.sh + 12 + 4 * kmax;
   const int hs = 64 * h_steps(L), nkl = Kc * Kd;
-  const int e2 = tiny_exponent(s.t.sh, kmax, Ka, Kb, Kc, Kd);
-  const double scale = ldexp(1.0, -e2), unscale = ldexp(1.0, e2);
+  int eb, ek;
+  tiny_exponents(s.t.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
+  const double scaleb = ldexp(1.0, -eb), scalek = ldexp(1.0, -ek), unscale = ldexp(1.0, eb + ek);
   // [0]^(m) (wave 0) and the per-axis tables (the other waves)
   auto prepare = [&](int ij, int kl, int ti) {
     const int i = ij / Kb, j = ij - (ij / Kb) * Kb, k = kl / Kd, l = kl - (kl / Kd) * Kd;
@@ -318,7 +319,7 @@ __device__ __forceinline__ void jengine_quartet(
         }
         const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
         const double wk = co[2 * kmax + k] * co[3 * kmax + l] * exp(-zc * zd * iq * cd2);
-        s.t.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, wb * (wk * scale), tb.boys);
+        s.t.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
       }
     } else {
       build_htables(s.t.h, hs, tb.hcoef, ttab + cp.o_hexp, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);

@@ -404,8 +404,9 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
 
   const int hs = 64 * h_steps(L);
   const bool over = cp.o_brae == cp.o_zt;
-  const int e2 = tiny_exponent(s.t.sh, kmax, Ka, Kb, Kc, Kd);
-  const double scale = ldexp(1.0, -e2), unscale = ldexp(1.0, e2);
+  int eb, ek;
+  tiny_exponents(s.t.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
+  const double scaleb = ldexp(1.0, -eb), scalek = ldexp(1.0, -ek), unscale = ldexp(1.0, eb + ek);
   // EXCH: y blocks (row block, 16 columns c) of this wave, kept over the ket pairs
   d4 yacc[2] = {acc_zero<false>(), acc_zero<false>()};
 
@@ -441,7 +442,7 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
             }
             const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
             const double wk = co[2 * kmax + k] * co[3 * kmax + l] * exp(-zc * zd * iq * cd2);
-            s.t.baseM[la_] = hermite_base_m(la_, za + zb, zc + zd, r2, wb * (wk * scale), tb.boys);
+            s.t.baseM[la_] = hermite_base_m(la_, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
           }
         } else {
           if (L > 1)

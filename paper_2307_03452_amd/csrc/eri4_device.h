@@ -262,9 +262,8 @@ __device__ __forceinline__ void load_rtab(uint2 (&ent)[NE], const uint2* __restr
 // Primitive-pair data, stored in LDS as 11 doubles:
 //   [0] z = za + zb, [1] w = ca cb exp(-za zb / z |A-B|^2) (Gaussian product
 //   prefactor times the two contraction coefficients), [2..4] P, [5..7] P-A, [8..10] P-B.
-// The ket pair's slots [11] and [12] hold the power-of-two scale of [0]^(m)
-// and its inverse (1 in FP64).
-constexpr int kPairDoubles = 11;
+// The ket pair's slots [13] and [11] hold the power-of-two scales of the bra's and
+// the ket's weights, [12] the inverse of their product (1 mostly, see tiny_exponents).
 
 __device__ __forceinline__ void make_pair(double* out, double za, double zb, double ca, double cb,
                                           const double* A, const double* B) {
@@ -422,11 +421,18 @@ __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double*
     }
 }
 
-// Power-of-two scale of [0]^(m) for the ket pair in kpair with FP32 transforms,
-// into kpair[11] and its inverse into kpair[12].  The scale brings the largest
-// product of bra and ket pair weights near 1 so that the FP32 operands of both
-// transforms stay inside FP32's exponent range for quartets with tiny integrals;
-// the output write divides it out.  sh: shell data (load_shells).
+// Power-of-two scales of the bra's and the ket's pair weights (coefficients times
+// Gaussian product prefactor), whose product [0]^(m) carries.  One scale for the
+// product would overflow where one side's weight is large and the other's tiny.
+__device__ __forceinline__ int weight_exponent(double w) {
+  return w > 0.0 && w < INFINITY ? max(-1000, min(1000, ilogb(w))) : 0;
+}
+
+// FP32 transforms: the scales that bring the largest weight of either side near 1,
+// for the ket pair in kpair, so that the FP32 operands of both transforms stay
+// inside FP32's exponent range for quartets with tiny integrals; into kpair[13]
+// (bra) and kpair[11] (ket), what the output write multiplies by into kpair[12].
+// sh: shell data (load_shells).
 __device__ __forceinline__ void fp32_scale(const double* sh, double* kpair, int kmax, int Ka, int Kb) {
   const double* A = sh;
   const double* B = sh + 3;
@@ -440,36 +446,40 @@ __device__ __forceinline__ void fp32_scale(const double* sh, double* kpair, int 
     const double za = ex[i], zb = ex[kmax + j];
     wmax = fmax(wmax, fabs(co[i] * co[kmax + j]) * exp(-za * zb / (za + zb) * ab2));
   }
-  const double wq = wmax * fabs(kpair[1]);
-  const int e = (wq > 0.0 && wq < INFINITY) ? max(-1020, min(1020, ilogb(wq))) : 0;
-  kpair[11] = ldexp(1.0, -e);
-  kpair[12] = ldexp(1.0, e);
+  const int eb = weight_exponent(wmax), ek = weight_exponent(fabs(kpair[1]));
+  kpair[13] = ldexp(1.0, -eb);
+  kpair[11] = ldexp(1.0, -ek);
+  kpair[12] = ldexp(1.0, eb + ek);
 }
 
-// FP64 transforms: the binary exponent of the largest Gaussian product
-// prefactor of the quartet whose shells are in sh where that is below -600, else
-// 0.  [0]^(m) carries its inverse and the output write restores it, so that the
-// steps between work on normal numbers: subnormal values carry few bits, and the
-// transforms amplify what their rounding loses by up to 1e6.  The largest
-// prefactor of a pair is that of its smallest exponents.
-__device__ __forceinline__ int tiny_exponent(const double* sh, int kmax, int Ka, int Kb, int Kc, int Kd) {
+// FP64 transforms: the binary exponents of the largest weights of both sides where
+// their product is below 2^-600, else 0.  [0]^(m) carries their inverses and the
+// output write restores them, so that the steps between work on normal numbers:
+// subnormal values carry few bits, and the transforms amplify what their rounding
+// loses by up to 1e6.  The largest prefactor of a pair is that of its smallest
+// exponents.
+__device__ __forceinline__ void tiny_exponents(const double* sh, int kmax, int Ka, int Kb, int Kc, int Kd, int& eb,
+                                               int& ek) {
   const double* ex = sh + 12;
-  double arg = 0.0;
+  const double* co = sh + 12 + 4 * kmax;
+  double e[2];
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
     const int n1 = side ? Kc : Ka, n2 = side ? Kd : Kb;
     const double* e1 = ex + 2 * side * kmax;
-    double z1 = e1[0], z2 = e1[kmax], r2 = 0.0;
-    for (int i = 1; i < n1; ++i) z1 = fmin(z1, e1[i]);
-    for (int i = 1; i < n2; ++i) z2 = fmin(z2, e1[kmax + i]);
+    const double* c1 = co + 2 * side * kmax;
+    double z1 = e1[0], z2 = e1[kmax], w1 = fabs(c1[0]), w2 = fabs(c1[kmax]), r2 = 0.0;
+    for (int i = 1; i < n1; ++i) z1 = fmin(z1, e1[i]), w1 = fmax(w1, fabs(c1[i]));
+    for (int i = 1; i < n2; ++i) z2 = fmin(z2, e1[kmax + i]), w2 = fmax(w2, fabs(c1[kmax + i]));
     for (int x = 0; x < 3; ++x) {
       const double d = sh[6 * side + x] - sh[6 * side + 3 + x];
       r2 += d * d;
     }
-    arg += z1 * z2 / (z1 + z2) * r2;
+    e[side] = weight_exponent(w1) + weight_exponent(w2) - 1.4426950408889634 * (z1 * z2 / (z1 + z2) * r2);
   }
-  const double e = -1.4426950408889634 * arg;  // log2
-  return e < -600.0 ? (int)fmax(e, -900.0) : 0;  // (room for the coefficients)
+  const bool tiny = e[0] + e[1] < -600.0;
+  eb = tiny ? (int)fmax(fmin(e[0], 900.0), -900.0) : 0;
+  ek = tiny ? (int)fmax(fmin(e[1], 900.0), -900.0) : 0;
 }
 
 // Shell data of quartet q into LDS: centres A B C D in sh[0..11], then the

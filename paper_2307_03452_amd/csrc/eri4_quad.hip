@@ -238,8 +238,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const double* D = s.sh + 9;
   const double* ex = s.sh + 12;
   const double* co = s.sh + 12 + 4 * kmax;
-  const int e2 = tiny_exponent(s.sh, kmax, Ka, Kb, Kc, Kd);
-  const double scale = ldexp(1.0, -e2), unscale = ldexp(1.0, e2);
+  int eb, ek;
+  tiny_exponents(s.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
+  const double scaleb = ldexp(1.0, -eb), scalek = ldexp(1.0, -ek), unscale = ldexp(1.0, eb + ek);
   const __amdgpu_buffer_rsrc_t rsrc = out_rsrc(outq, cp.nab * cp.ncd);
   const int nij = Ka * Kb;
   int step = 0;  // primitive quartets so far: which of the two buffers
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         }
         const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
         const double wk = co[2 * kmax + k] * co[3 * kmax + l] * exp(-zc * zd * iq * cd2);
-        s.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, wb * (wk * scale), tb.boys);
+        s.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
       }
     } else {
       build_htables(h_of(st), hs, tb.hcoef, ttab + cp.o_hexp, pq[0], pq[1], pq[2], ti, kThreads - 64);

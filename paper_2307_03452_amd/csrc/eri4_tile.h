@@ -631,7 +631,8 @@ __device__ __forceinline__ void tile_body(const TileParams& cp, unsigned char* l
   const double* ex = s.sh + 12;
   const double* co = s.sh + 12 + 4 * kmax;
   const int hs = 64 * h_steps(L);
-  const int e2 = F32 ? 0 : tiny_exponent(s.sh, kmax, Ka, Kb, Kc, Kd);
+  int eb = 0, ek = 0;
+  if constexpr (!F32) tiny_exponents(s.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
   constexpr int NG = kWaves * 4 - 4;  // rows of 16 lanes outside wave 0
   const __amdgpu_buffer_rsrc_t rsrc = out_rsrc(outq, cp.nab * cp.ncd);
 
@@ -645,8 +646,9 @@ __device__ __forceinline__ void tile_body(const TileParams& cp, unsigned char* l
       if constexpr (F32) {
         fp32_scale(s.sh, s.kpair, kmax, Ka, Kb);
       } else {
-        s.kpair[11] = ldexp(1.0, -e2);
-        s.kpair[12] = ldexp(1.0, e2);
+        s.kpair[13] = ldexp(1.0, -eb);
+        s.kpair[11] = ldexp(1.0, -ek);
+        s.kpair[12] = ldexp(1.0, eb + ek);
       }
     }
     // What the recursion and the first transform of bra pair ij read: [0]^(m)
@@ -668,7 +670,8 @@ __device__ __forceinline__ void tile_body(const TileParams& cp, unsigned char* l
             r2 += pq[x] * pq[x];
           }
           const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
-          s.baseM[lane] = hermite_base_m(lane, za + zb, zc + zd, r2, wb * (s.kpair[1] * s.kpair[11]), tb.boys);
+          s.baseM[lane] = hermite_base_m(lane, za + zb, zc + zd, r2, (wb * s.kpair[13]) * (s.kpair[1] * s.kpair[11]),
+                                          tb.boys);
         }
       } else {
         build_etab_rows(E, cp.la, cp.lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, (tid >> 4) - 4, NG, lane & 15);
