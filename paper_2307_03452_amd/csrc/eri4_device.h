@@ -453,33 +453,42 @@ __device__ __forceinline__ void fp32_scale(const double* sh, double* kpair, int 
 }
 
 // FP64 transforms: the binary exponents of the largest weights of both sides where
-// their product is below 2^-600, else 0.  [0]^(m) carries their inverses and the
-// output write restores them, so that the steps between work on normal numbers:
-// subnormal values carry few bits, and the transforms amplify what their rounding
-// loses by up to 1e6.  The largest prefactor of a pair is that of its smallest
-// exponents.
+// their Gaussian product prefactors are below 2^-600 together, else 0.  [0]^(m) carries
+// their inverses and the output write restores them, so that the steps between work
+// on normal numbers: subnormal values carry few bits, and the transforms amplify what
+// their rounding loses by up to 1e6.  The largest prefactor of a pair is that of its
+// smallest exponents.
 __device__ __forceinline__ void tiny_exponents(const double* sh, int kmax, int Ka, int Kb, int Kc, int Kd, int& eb,
                                                int& ek) {
   const double* ex = sh + 12;
-  const double* co = sh + 12 + 4 * kmax;
   double e[2];
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
     const int n1 = side ? Kc : Ka, n2 = side ? Kd : Kb;
     const double* e1 = ex + 2 * side * kmax;
-    const double* c1 = co + 2 * side * kmax;
-    double z1 = e1[0], z2 = e1[kmax], w1 = fabs(c1[0]), w2 = fabs(c1[kmax]), r2 = 0.0;
-    for (int i = 1; i < n1; ++i) z1 = fmin(z1, e1[i]), w1 = fmax(w1, fabs(c1[i]));
-    for (int i = 1; i < n2; ++i) z2 = fmin(z2, e1[kmax + i]), w2 = fmax(w2, fabs(c1[kmax + i]));
+    double z1 = e1[0], z2 = e1[kmax], r2 = 0.0;
+    for (int i = 1; i < n1; ++i) z1 = fmin(z1, e1[i]);
+    for (int i = 1; i < n2; ++i) z2 = fmin(z2, e1[kmax + i]);
     for (int x = 0; x < 3; ++x) {
       const double d = sh[6 * side + x] - sh[6 * side + 3 + x];
       r2 += d * d;
     }
-    e[side] = weight_exponent(w1) + weight_exponent(w2) - 1.4426950408889634 * (z1 * z2 / (z1 + z2) * r2);
+    e[side] = -1.4426950408889634 * (z1 * z2 / (z1 + z2) * r2);  // log2
   }
-  const bool tiny = e[0] + e[1] < -600.0;
-  eb = tiny ? (int)fmax(fmin(e[0], 900.0), -900.0) : 0;
-  ek = tiny ? (int)fmax(fmin(e[1], 900.0), -900.0) : 0;
+  eb = ek = 0;
+  if (e[0] + e[1] < -600.0) {
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+      for (int shell = 2 * side; shell < 2 * side + 2; ++shell) {
+        const int n = shell == 0 ? Ka : shell == 1 ? Kb : shell == 2 ? Kc : Kd;
+        double w = 0.0;
+        for (int i = 0; i < n; ++i) w = fmax(w, fabs(ex[(4 + shell) * kmax + i]));
+        e[side] += weight_exponent(w);
+      }
+    }
+    eb = (int)fmax(fmin(e[0], 900.0), -900.0);
+    ek = (int)fmax(fmin(e[1], 900.0), -900.0);
+  }
 }
 
 // Shell data of quartet q into LDS: centres A B C D in sh[0..11], then the
