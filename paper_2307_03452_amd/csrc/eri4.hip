@@ -330,7 +330,7 @@ TileParams tile_params(int la, int lb, int lc, int ld, int kmax) {
   p.nunits = b.nunits;
   p.ntiles = (b.nunits + kWaves / sh.cw - 1) / (kWaves / sh.cw);
   p.nkblk = k.nblocks;
-  p.o_uv = ix.uv; p.o_qcol = ix.qcol[p.Lk]; p.o_task = ix.task[p.L]; p.ntask = ix.ntask[p.L]; p.o_hexp = ix.hexp;
+  p.o_uv = ix.uv; p.o_qcol = ix.qcol[p.Lk]; p.o_task = ix.task[p.L]; p.ntask = ix.ntask[p.L];
   p.o_bunit = b.units; p.o_brows = b.rows;
   p.o_kunit = k.units; p.o_kcols = k.rows; p.o_klist = k.list;
   p.nks = 0;
@@ -417,7 +417,7 @@ bool small_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d
     p.o_zt = p.o_brae + align16(3 * p.tbaxis * 8);
     p.o_h = p.o_zt + align16(nzt * 8);
     p.lds_bytes = align16(std::max(p.o_h + 3 * 64 * h_steps(p.L) * 8, p.o_kete + 3 * p.tkaxis * 8));
-    p.o_uv = g_tix.uv; p.o_hexp = g_tix.hexp;
+    p.o_uv = g_tix.uv;
   }
   if (p.lds_bytes > kSmallLdsMax || p.nqb > 6) return false;
   p.rtab_off = d ? d->rstart[p.L] : 0;
@@ -491,7 +491,7 @@ bool quad_route(int la, int lb, int lc, int ld, int kmax, int64_t nq, int cus) {
 void dense_layout(ClassParams* p, bool exch, const DeviceState* d) {
   if (d) {
     const TileTableIndex& ix = g_tix;
-    p->ntask = ix.ntask[p->L]; p->o_uv = ix.uv; p->o_task = ix.task[p->L]; p->o_hexp = ix.hexp;
+    p->ntask = ix.ntask[p->L]; p->o_uv = ix.uv; p->o_task = ix.task[p->L];
   }
   const int nzt = nuv(p->L);
   p->o_rowt = p->o_qtab + align16(16 * p->nqb * 8);
@@ -695,7 +695,7 @@ JParams jengine_params(int la, int lb, int lc, int ld, int kmax) {
   p.ntask = ix.ntask[p.L]; p.nchunk = ix.nchunk[p.Lb]; p.nitems = ix.nitem[p.Lk];
   for (p.ncps = 3; (1 << p.ncps) < p.nchunk;) ++p.ncps;
   p.ncp = 1 << p.ncps;
-  p.o_uv = ix.uv; p.o_task = ix.task[p.L]; p.o_hexp = ix.hexp; p.o_chunk = ix.chunk[p.Lb];
+  p.o_uv = ix.uv; p.o_task = ix.task[p.L]; p.o_chunk = ix.chunk[p.Lb];
   p.o_item = ix.item[p.Lk]; p.o_qpos = ix.qpos[p.Lk];
   p.dsize = ix.dsize[p.Lk];
   int cells = 0;

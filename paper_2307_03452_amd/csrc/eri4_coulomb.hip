@@ -322,7 +322,7 @@ __device__ __forceinline__ void jengine_quartet(
         s.t.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
       }
     } else {
-      build_htables(s.t.h, hs, tb.hcoef, ttab + cp.o_hexp, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
+      build_htables(s.t.h, hs, tb.hcoef, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
     }
   };
   double J[kJAb];

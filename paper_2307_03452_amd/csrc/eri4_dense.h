@@ -446,7 +446,7 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
           }
         } else {
           if (L > 1)
-            build_htables(s.t.h, hs, tb.hcoef, tb.ttab + cp.o_hexp, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
+            build_htables(s.t.h, hs, tb.hcoef, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
           if (EXCH && !over) {
             build_etab_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, (ti >> 4) - 4,
                             kWaves * 4 - 4, la_ & 15);

@@ -156,7 +156,7 @@ struct ClassParams {
   int o_kete;    // ket tables (phase 2)
   int o_ptab, o_qtab, o_base, o_shell;
   int o_rowt, o_rs, o_rv, o_zt, o_h;        // recursion of the solid and exchange kernels (eri4_dense.h)
-  int ntask, o_uv, o_task, o_hexp;          // and its tables (make_tile_tables), in words
+  int ntask, o_uv, o_task;                  // and its tables (make_tile_tables), in words
   int lds_bytes;
 };
 
@@ -179,7 +179,7 @@ struct TileParams {
   int nunits, ntiles;  // bra units, and tiles of them
   int nkblk;           // 16-wide column blocks of (ab|cd), grouped by (cx, dx)
   int ntask;           // wave tasks of W
-  int o_uv, o_qcol, o_task, o_hexp;
+  int o_uv, o_qcol, o_task;
   int o_bunit, o_brows, o_kunit, o_kcols, o_klist;
   // LDS layout (byte offsets)
   int o_row1;   // row tables of the second unit of a tile
@@ -227,7 +227,7 @@ constexpr int tile_shape(int nqb) {
 // Where the tables of the Cartesian integral kernels start (make_tile_tables),
 // in words: per order n, and per shell pair (l1, l2) as bra or ket.
 struct TileTableIndex {
-  int uv, hexp;
+  int uv;
   int qcol[2 * kTableLMax + 1], task[kMaxL + 1], ntask[kMaxL + 1];
   int chunk[2 * kTableLMax + 1], nchunk[2 * kTableLMax + 1];
   int item[2 * kTableLMax + 1], nitem[2 * kTableLMax + 1], dsize[2 * kTableLMax + 1], qpos[2 * kTableLMax + 1];
@@ -260,7 +260,7 @@ struct JParams {
   int kmax;
   int ds;              // doubles of dket per ket primitive pair
   int rsize, dsize;    // doubles of [r] (with kJPad before and after it) and of dket in LDS
-  int o_uv, o_task, o_hexp, o_chunk, o_item, o_qpos;
+  int o_uv, o_task, o_chunk, o_item, o_qpos;
   // LDS (byte offsets): fixed part (kJ..), dket, [r] (or parts of w), then W, zt
   // and the per-axis tables; or the bra tables, w and the folded w
   int o_d, o_r, o_w, o_zt, o_h, o_wp, o_wf;

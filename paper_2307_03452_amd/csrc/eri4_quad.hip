@@ -238,6 +238,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const double* D = s.sh + 9;
   const double* ex = s.sh + 12;
   const double* co = s.sh + 12 + 4 * kmax;
+  const double flim = far_limit(A, B);
   int eb, ek;
   tiny_exponents(s.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
   const double scaleb = ldexp(1.0, -eb), scalek = ldexp(1.0, -ek), unscale = ldexp(1.0, eb + ek);
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         s.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
       }
     } else {
-      build_htables(h_of(st), hs, tb.hcoef, ttab + cp.o_hexp, pq[0], pq[1], pq[2], ti, kThreads - 64);
+      build_htables(h_of(st), hs, tb.hcoef, pq[0], pq[1], pq[2], ti, kThreads - 64, flim);
       build_etab_rows(brae_of(st), la, lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, ti >> 4, kWaves * 4 - 4, ti & 15);
     }
   };

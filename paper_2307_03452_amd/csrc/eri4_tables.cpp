@@ -324,10 +324,9 @@ static TileTableIndex::Side make_ket_side(std::vector<uint32_t>& tab, int l1, in
   return side;
 }
 
-// Tables of the Cartesian integral kernels (eri4_tile.h), 32-bit words:
+// Coefficients hcoef of the per-axis tables (eri4_tile.h: build_htables) in operand
+// order, and tables of the Cartesian integral kernels, 32-bit words:
 //   uv    (u, v) in order of increasing s = u + v, then u: u | v << 8 | u << 16 | s << 24
-//   hexp  exponents of the per-axis tables in operand order (hcoef: their
-//         coefficients, 0 where H is)
 //   qcol  per order n: t | u << 8 | s << 16 of each Hermite function, in (u, v)
 //         order, t fastest, padded with zeros to whole blocks of 16
 //   task  per order L: the blocks of W, most steps first: first pair (v, j) | ub << 12
@@ -342,18 +341,14 @@ void make_tile_tables(std::vector<uint32_t>& tab, std::vector<double>& hcoef, Ti
   ix.uv = 0;
   for (int s = 0; s <= kMaxL; ++s)
     for (int u = 0; u <= s; ++u) tab.push_back((uint32_t)(u | ((s - u) << 8) | (u << 16) | (s << 24)));
-  ix.hexp = (int)tab.size();
   for (int st = 0; st < h_steps(kMaxL); ++st)
     for (int lane = 0; lane < 64; ++lane) {
       const int t = lane % 16 + (st < 4 ? 0 : 16), j = 4 * (st < 4 ? st : st - 2) + lane / 16;
       long double c = 0.0L;
-      int e = 0;
       if (j <= t && 2 * j >= t && t <= kMaxL) {
         c = 1.0L;  // t! / (a! (t-2a)! 2^a) for a = t - j, an integer below 2^53
         for (int a = 0; a < t - j; ++a) c = c * (long double)((t - 2 * a) * (t - 2 * a - 1)) / (2.0L * (a + 1));
-        e = 2 * j - t;
       }
-      tab.push_back((uint32_t)e);
       hcoef.push_back((double)c);
     }
   for (int n = 0; n <= 2 * kTableLMax; ++n) {

@@ -170,16 +170,37 @@ __device__ __forceinline__ d4 small_product(int nk, FA fa, FB fb) {
   return acc;
 }
 
-// Per-axis tables h of P - Q by threads i, i + n, ...: hcoef * (P-Q)_axis^hexp.
-__device__ __forceinline__ void build_htables(double* h, int hs, const double* __restrict__ hcoef,
-                                              const uint32_t* __restrict__ hexp, double px, double py, double pz,
-                                              int i, int n) {
+// Limit of the distances P - Q (build_htables).  None where the bra's shells are more
+// than 2^30 apart: their Gaussian product prefactor is zero, and the powers of P - Q
+// and of A - B in G could have an infinite product.
+__device__ __forceinline__ double far_limit(const double* A, const double* B) {
+  double r2 = 0.0;
+#pragma unroll
+  for (int x = 0; x < 3; ++x) r2 += (A[x] - B[x]) * (A[x] - B[x]);
+  return r2 > 0x1p60 ? 0.0 : 0x1p54;
+}
+
+// Per-axis tables h of P - Q by threads i, i + n, ...: hcoef * (P-Q)_axis^e, entry (row
+// t, column j) with e = 2 j - t (hcoef is 0 where that is no exponent).  A distance above
+// 2^54 counts as infinite and an entry above 2^250 as nothing: what they multiply, [0]^(j)
+// with j >= e, is then below 2^-250 of [0]^(0) or has long been rounded to 0, and 0
+// times an infinite power would be NaN.
+__device__ __forceinline__ void build_htables(double* h, int hs, const double* __restrict__ hcoef, double px,
+                                              double py, double pz, int i, int n, double lim = 0x1p54) {
+  px = fabs(px) > lim ? 0.0 : px;
+  py = fabs(py) > lim ? 0.0 : py;
+  pz = fabs(pz) > lim ? 0.0 : pz;
+  auto entry = [](double c, double x, int e) {
+    const double v = c * ipow(x, e);
+    return fabs(v) <= 0x1p250 ? v : 0.0;  // (an infinite power times 0, too)
+  };
   for (; i < hs; i += n) {
     const double c = hcoef[i];
-    const int e = (int)hexp[i];
-    h[i] = c * ipow(px, e);
-    h[hs + i] = c * ipow(py, e);
-    h[2 * hs + i] = c * ipow(pz, e);
+    const int s = i >> 6;
+    const int e = max(0, (s < 4 ? 8 * s : 8 * s - 32) + 2 * ((i >> 4) & 3) - (i & 15));
+    h[i] = entry(c, px, e);
+    h[hs + i] = entry(c, py, e);
+    h[2 * hs + i] = entry(c, pz, e);
   }
 }
 
@@ -631,6 +652,7 @@ __device__ __forceinline__ void tile_body(const TileParams& cp, unsigned char* l
   const double* ex = s.sh + 12;
   const double* co = s.sh + 12 + 4 * kmax;
   const int hs = 64 * h_steps(L);
+  const double flim = far_limit(A, B);
   int eb = 0, ek = 0;
   if constexpr (!F32) tiny_exponents(s.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
   constexpr int NG = kWaves * 4 - 4;  // rows of 16 lanes outside wave 0
@@ -675,7 +697,7 @@ __device__ __forceinline__ void tile_body(const TileParams& cp, unsigned char* l
         }
       } else {
         build_etab_rows(E, cp.la, cp.lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, (tid >> 4) - 4, NG, lane & 15);
-        build_htables(s.h, hs, tb.hcoef, ttab + cp.o_hexp, pq[0], pq[1], pq[2], tid - 64, kThreads - 64);
+        build_htables(s.h, hs, tb.hcoef, pq[0], pq[1], pq[2], tid - 64, kThreads - 64, flim);
         if (wave == kWaves - 1) zero_rows(E, cp.la, cp.lb, cp.tbrow, cp.tbaxis, lane, 64);
       }
     };

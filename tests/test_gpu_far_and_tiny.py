@@ -70,3 +70,37 @@ def test_a_tiny_pair_with_a_large_one(ls, tiny):
         # (in "one" values may be subnormal in forms that do not scale)
         m = y.abs().max().item()
         assert m > 0.0 and (x - y).abs().max().item() <= TOL * m, (k, (x - y).abs().max().item() / m)
+
+
+# (two shells on one centre have a charge only if their l add to an even number)
+@pytest.mark.parametrize("ls", [ls for ls in CLASSES if (ls[2] + ls[3]) % 2 == 0])
+def test_pairs_far_apart(ls):
+    """Two charge distributions a great distance R apart repel as their charges do,
+    q q / R: the same times R at every R, up to their extent over R (below 1e-6 from
+    1e9 on).  Solid harmonics of different l on one centre have no charge: what is left
+    of the Cartesian integrals they are sums of is held against the largest of those."""
+    c, e = quartet(ls, 9 + sum(ls))
+    w = np.ones((1, 4, 1))
+    ref = None
+    for R in (1e9, 1e12, 1e16, 1e20, 1e30):
+        c[0, 2:] = [R, 0.0, 0.0]
+        got = every_form(ls, c, e, w)
+        if ref is None:
+            ref = {k: x.flatten() * R for k, x in got.items()}
+        for k, x in got.items():
+            x = x.flatten() * R
+            assert torch.isfinite(x).all(), (k, R)
+            m = ref["batch" if k.startswith("solid") else k].abs().max().item()
+            assert (x - ref[k]).abs().max().item() <= 1e-6 * m, (k, R)
+
+
+@pytest.mark.parametrize("ls", CLASSES)
+@pytest.mark.parametrize("side", [0, 2])
+def test_shells_of_a_pair_far_apart(ls, side):
+    """A Gaussian product prefactor that is zero gives zeros, wherever the centres are."""
+    c, e = quartet(ls, 3 + sum(ls))
+    e[0, side + 1] = e[0, side]  # their product sits between them, by the other pair
+    for R in (1e3, 1e9, 1e13, 1e16, 1e20):
+        c[0, side], c[0, side + 1] = [R, 0.0, 0.0], [-R, 0.0, 0.0]
+        for k, x in every_form(ls, c, e, np.ones((1, 4, 1))).items():
+            assert (x == 0.0).all(), (k, R)
