@@ -32,7 +32,7 @@ void make_tile_tables(std::vector<uint32_t>& tab, std::vector<double>& hcoef, Ti
 void solid_dense(int l, double* C);
 
 __global__ void reset_counter_kernel(int* counter) {
-  if (threadIdx.x == 0) counter[0] = 0;
+  if (threadIdx.x < 2) counter[threadIdx.x] = 0;
 }
 
 // out[0..n) = 0 (a kernel rather than a memset, so that graph captures of the
@@ -176,10 +176,14 @@ std::deque<DeviceState> g_dev;  // a deque: growing it keeps pointers to existin
 
 eri4_status set_attrs() {
   HIP_TRY(fused_set_attrs());
+  HIP_TRY(cart_set_attrs());
   HIP_TRY(small_set_attrs());
   HIP_TRY(quad_set_attrs());
   HIP_TRY(solid_set_attrs());
-  HIP_TRY(plan_solid_set_attrs());
+  HIP_TRY(plan_set_attrs_solid());
+  HIP_TRY(plan_set_attrs_solidp());
+  HIP_TRY(plan_set_attrs_cart());
+  HIP_TRY(plan_set_attrs_cartp());
   HIP_TRY(coulomb_set_attrs());
   HIP_TRY(exchange_set_attrs());
   HIP_TRY(plan_coulomb_set_attrs());
@@ -359,9 +363,9 @@ TileParams tile_params(int la, int lb, int lc, int ld, int kmax) {
 }
 
 // Estimated cycles of each tile of a quartet, per primitive quartet (products,
-// reads over t, and the steps before them) and per ket primitive pair.
-struct TileCost { double quartet, ket; };
-std::vector<TileCost> tile_costs(const TileParams& p) {
+// reads over t, and the steps before them) and per ket primitive pair: f(quartet, ket).
+template <class F>
+void each_tile_cost(const TileParams& p, F f) {
   const TileShapeInfo sh = kTileShapes[p.shape];
   const int ug = kWaves / sh.cw;
   auto steps = [](const uint32_t* w) { return (double)((w[1] + 3) / 4); };
@@ -370,7 +374,6 @@ std::vector<TileCost> tile_costs(const TileParams& p) {
     const uint32_t* w = g_ttab.data() + p.o_kunit + 8 * i;
     ket += steps(w) * (w[0] >> 8) * (64.0 + 16.0 * ((w[0] & 0xff) / 4 + 1)) / 4.0;
   }
-  std::vector<TileCost> cost;
   for (int rt = 0; rt < p.ntiles; ++rt) {
     double g1 = 0.0, g2 = 0.0;
     for (int i = 0; i < ug && rt * ug + i < p.nunits; ++i) {
@@ -380,8 +383,13 @@ std::vector<TileCost> tile_costs(const TileParams& p) {
       const uint32_t v = w[7];
       g2 += (((v & 0xff) + ((v >> 8) & 0xff) + ((v >> 16) & 0xff) + (v >> 24)) + 15) / 16;
     }
-    cost.push_back({g1 + 5000.0 + 2.0 * p.nr, g2 * ket + 3000.0});
+    f(g1 + 5000.0 + 2.0 * p.nr, g2 * ket + 3000.0);
   }
+}
+struct TileCost { double quartet, ket; };
+std::vector<TileCost> tile_costs(const TileParams& p) {
+  std::vector<TileCost> cost;
+  each_tile_cost(p, [&](double q, double k) { cost.push_back({q, k}); });
   return cost;
 }
 
@@ -482,13 +490,13 @@ bool quad_route(int la, int lb, int lc, int ld, int kmax, int64_t nq, int cus) {
   return nq <= (int64_t)cus * (Lb == 6 ? 3 : Lb == 5 ? 2 : 1);
 }
 
-// LDS layout of the solid (exch false) and exchange kernels and the tables of their
-// recursion (their places need d, an initialised device): [r], whose
-// unused cells hold W, then zt and the per-axis tables, for exch the bra tables
-// (behind or over them); or the [ab|q] tile.  It fits wherever the layout of make_params does
-// (checked over all classes, tiles and layouts), without the second box that the
-// two-box layout once held.
-void dense_layout(ClassParams* p, bool exch, const DeviceState* d) {
+// LDS layout of the kernels of eri4_dense.h (mode: what they compute) and the
+// tables of their recursion (whose places need d, an initialised device): [r], whose
+// unused cells hold W, then zt and the per-axis tables, then but for solid harmonics the bra tables (behind or over them) and
+// for Cartesian integrals the ket tables; or the [ab|q] tile.  For solid harmonics and
+// exchange it fits wherever the layout of make_params does (checked over all classes,
+// tiles and layouts), without the second box that the two-box layout once held.
+void dense_layout(ClassParams* p, int mode, const DeviceState* d) {
   if (d) {
     const TileTableIndex& ix = g_tix;
     p->ntask = ix.ntask[p->L]; p->o_uv = ix.uv; p->o_task = ix.task[p->L];
@@ -498,17 +506,63 @@ void dense_layout(ClassParams* p, bool exch, const DeviceState* d) {
   p->o_rs = p->o_rowt + align16((p->L + 1) * (p->L + 1) * 2);
   p->o_rv = p->o_rs + align16(nzt * 4);
   p->o_union = p->o_rv + align16(nzt * 2);
+  if (p->L <= kWaveL) p->o_union = p->o_rowt + align16(nherm(p->L) * 8);  // (or, of low orders, the recursion's table)
   p->o_zt = p->o_union + align16((r_cells(p->slab, p->L) + (p->S1 == p->L + 1 ? p->L + 1 : 0)) * 8);
   p->o_h = p->o_zt + align16(nzt * 8);
   int end = p->o_h + 3 * 64 * h_steps(p->L) * 8;
-  const int etab = exch ? align16(3 * p->tbaxis * 8) : 0;
+  const int etab = mode != kDenseSolid ? align16(3 * p->tbaxis * 8) : 0;
   // the bra tables in a place of their own where there is room (one workgroup runs
   // per compute unit in any case), else over zt and the per-axis tables
   p->o_brae = end + etab <= kMaxLdsBytes ? end : p->o_zt;
   end = std::max(end, p->o_brae + etab);
   // over the tile at the end: the exchange blocks of every wave (exch_store)
-  const int tile = std::max(p->rb * 16 * p->xs, exch ? kWaves * 4 * 64 : 0);
-  p->lds_bytes = align16(std::max(end, p->o_union + tile * 8));
+  const int tile = std::max(p->rb * 16 * p->xs, mode == kDenseExch ? kWaves * 4 * 64 : 0);
+  p->o_kete = align16(std::max(end, p->o_union + tile * 8));
+  p->lds_bytes = p->o_kete + (mode == kDenseCart ? align16(3 * p->tkaxis * 8) : 0);
+}
+
+// Parameters of the dense Cartesian kernels for a class, if it fits: the tile height
+// that holds its rows, 64 at most.
+bool cart_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d, int limit, ClassParams* out) {
+  if (la + lb + lc + ld > kBoxLMax) return false;
+  const int nrb = (ncart(la) * ncart(lb) + 15) / 16;
+  for (int rb = nrb > 2 ? 4 : nrb; rb >= 1; rb >>= 1) {
+    ClassParams p = make_params(la, lb, lc, ld, kmax, rb, false, false);
+    dense_layout(&p, kDenseCart, d);
+    if (p.lds_bytes > limit || (p.nqb + 7) / 8 > (rb == 4 ? 2 : 4)) continue;
+    p.rtab_off = d->rstart[p.L];
+    *out = p;
+    return true;
+  }
+  return false;
+}
+
+// Whether the Cartesian integrals of nq quartets of a class run as dense tiles (p,
+// eri4_dense.h) or as grouped ones (t, eri4_tile.h): kb * kk and kk primitive quartets
+// and ket pairs of a quartet.  Grouped tiles have fewer products, but leave groups of
+// a few rows in blocks of 16 and repeat the recursion for every two or three blocks.
+// The times below (us) were fitted to 1004 calls: all classes with l <= 3 and la >=
+// lb, lc >= ld as plans, 110 higher ones as batches, 16 to 2048 quartets of one and
+// three primitives per shell (to 9% and 12%; the margin takes the forms' own tie).  Of
+// those calls, dense : grouped in us, 300 quartets:
+//   (ss|ss) 18 : 31, (pp|pp) 22 : 47, (dd|dd) 34 : 70, (ff|ff) 91 : 123, (hp|ss) 31 : 62,
+//   (fd|hp) 44 : 69, (gf|ss) 66 : 106, (gg|gg) 297 : 210, (kd|gd) 210 : 186
+double grouped_us(double kbkk, double kk, double tq, double tk) { return kbkk * 7.9e-4 * tq + kk * 8.1e-4 * tk + 6.9; }
+double dense_us(const ClassParams& p, double kbkk, double kk) {
+  const double s1 = p.np4 / 4 * ((p.nqb + 7) / 8) * p.rb, s2 = p.nq4 / 4 * ((p.ncdb + 7) / 8) * p.rb;
+  return kbkk * (1.9 + 0.062 * s1 + 0.0063 * nherm(p.L)) + kk * 0.079 * s2 + 5.1;
+}
+constexpr double kGroupedLaunch = 4.5, kDenseLaunch = 4.1;
+bool cart_route(const TileParams& t, const ClassParams& p, double nq, double kbkk, double kk, int cus) {
+#ifdef ROUTE_ALL
+  return ROUTE_ALL;
+#endif
+  double tq = 0.0, tk = 0.0;
+  each_tile_cost(t, [&](double q, double k) { tq += q; tk += k; });
+  const double grouped =
+      std::ceil(nq * t.ntiles / cus) * grouped_us(kbkk, kk, tq / t.ntiles, tk / t.ntiles) + kGroupedLaunch;
+  const double dense = std::ceil(nq * p.nrt / cus) * dense_us(p, kbkk, kk) + kDenseLaunch;
+  return dense < (p.L <= 13 ? 0.95 : 0.85) * grouped;
 }
 
 // Solid-harmonic output: the library's tile for the class, with rows and
@@ -521,7 +575,17 @@ void to_solid(ClassParams* p, const DeviceState* d) {
   p->ncd = p->nc * p->nd;
   p->nrt = (p->nab + 16 * p->rb - 1) / (16 * p->rb);
   p->ncdb = (p->ncd + 15) / 16;
-  dense_layout(p, false, d);
+  dense_layout(p, kDenseSolid, d);
+}
+
+// The library's own tile of solid harmonics, no taller than the rows there are: 4000
+// (ss|ss) 177 -> 160 us with 16 rows for one instead of 64.
+void fit_rows(ClassParams* p, const DeviceState* d) {
+  const int nrb = (p->nab + 15) / 16;
+  if (nrb > 2 || nrb >= p->rb) return;
+  p->rb = nrb;
+  p->nrt = 1;
+  dense_layout(p, kDenseSolid, d);
 }
 
 bool solid_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d, ClassParams* p, int64_t* hbs,
@@ -530,6 +594,7 @@ bool solid_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d
   to_solid(p, d);
   *hbs = (int64_t)p->nrt * p->rb * 16 * p->np4;
   *hks = (int64_t)p->ncdb * 16 * p->nq4;
+  fit_rows(p, d);
   return true;
 }
 
@@ -602,6 +667,17 @@ eri4_status eri4_batch(int la, int lb, int lc, int ld, int64_t nquartets, const 
     return ERI4_SUCCESS;
   }
   const TileParams t = tile_params(la, lb, lc, ld, kmax);
+  const double kk = (double)kmax * kmax;
+  if (cart_params(la, lb, lc, ld, kmax, d, kMaxLdsBytes - 64, &p) &&
+      cart_route(t, p, (double)nquartets, kk * kk, kk, d->cus)) {
+    const int64_t qchunk = ((int64_t)1 << 22) / p.nrt;  // grid below 2^32 work-items
+    for (int64_t q0 = 0; q0 < nquartets; q0 += qchunk) {
+      const int64_t nq = std::min(qchunk, nquartets - q0);
+      const hipError_t e = cart_launch(p, nq, stream, d->tables(), centers, exponents, coeffs, nprim, out, q0);
+      if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
+    }
+    return ERI4_SUCCESS;
+  }
   const int64_t qchunk = ((int64_t)1 << 22) / t.ntiles;  // grid below 2^32 work-items
   for (int64_t q0 = 0; q0 < nquartets; q0 += qchunk) {
     const int64_t nq = std::min(qchunk, nquartets - q0);
@@ -777,8 +853,13 @@ static bool exchange_params(int la, int lb, int lc, int ld, int kmax, const Devi
                             int64_t* fbs, int64_t* ps) {
   if (!pick_params(la, lb, lc, ld, kmax, d, kMaxLdsBytes, p)) return false;
   const int blocks = p->nb * ((p->na + 15) / 16);
+  // no taller than the rows there are
+  if (blocks <= 2 && blocks < p->rb) {
+    const int lay = p->lay;
+    if (!try_params(la, lb, lc, ld, kmax, blocks, lay, d, kMaxLdsBytes, p)) return false;
+  }
   p->nrt = (blocks + p->rb - 1) / p->rb;
-  dense_layout(p, true, d);
+  dense_layout(p, kDenseExch, d);
   *fbs = (int64_t)((p->nc + 15) / 16) * 16 * p->nq4;
   *ps = (int64_t)p->nb * p->na * p->nc;
   return true;
@@ -869,6 +950,9 @@ struct eri4_plan_s {
   int nclasses = 0;
   int lds_bytes = 0;
   int grid = 0;
+  // Cartesian plans: the items of classes that run as dense tiles, behind the others
+  int ncart_items = 0, cart_lds = 0, cart_grid = 0;
+  ClassParams* d_cart = nullptr;
   bool f32 = false;  // ERI4_PREC_FP32
   bool pairs = false;  // made from a bra and a ket list of shell pairs
   int64_t nbra = 0, nket = 0;
@@ -899,6 +983,7 @@ static void plan_free(eri4_plan_s* p) {
   if (!p) return;
   if (p->d_classes) (void)hipFree(p->d_classes);
   if (p->d_items) (void)hipFree(p->d_items);
+  if (p->d_cart) (void)hipFree(p->d_cart);
   if (p->d_qoff) (void)hipFree(p->d_qoff);
   if (p->d_nprim) (void)hipFree(p->d_nprim);
   if (p->d_counter) (void)hipFree(p->d_counter);
@@ -1048,29 +1133,76 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     }
   }
   if (solid)
-    for (ClassParams& c : cps) to_solid(&c, d);  // rows and columns over solid functions; same tile and LDS
-  // Cartesian plans run the kernels of eri4_tile.h, whose one layout of [r] and
-  // tiling follow from the class; a tile choice is checked and changes nothing
+    for (size_t c = 0; c < keys.size(); ++c) {  // rows and columns over solid functions; same tile
+      to_solid(&cps[c], d);
+      if (keys[c][4] < 0) fit_rows(&cps[c], d);
+    }
+  // Cartesian plans run the kernels of eri4_tile.h, or those of eri4_dense.h (cart_route:
+  // dense[c]), whose tilings follow from the class; a tile choice is checked and changes
+  // nothing
   std::vector<TileParams> tps;
+  std::vector<ClassParams> dps;
+  std::vector<char> dense;
   std::vector<std::vector<TileCost>> tcs;
-  if (!solid && !coul)
-    for (const auto& k : keys) {
+  if (!solid && !coul) {
+    std::vector<std::array<double, 3>> work(keys.size(), {0.0, 0.0, 0.0});  // quartets, primitive quartets, ket pairs
+    for (int64_t q = 0; q < nquartets; ++q) {
+      const double kk = (double)nprim[4 * q + 2] * nprim[4 * q + 3];
+      auto& w = work[qcls[q]];
+      w[0] += 1.0, w[1] += (double)nprim[4 * q] * nprim[4 * q + 1] * kk, w[2] += kk;
+    }
+    for (size_t c = 0; c < keys.size(); ++c) {
+      const auto& k = keys[c];
+      ClassParams dp{};
       tps.push_back(tile_params(k[0], k[1], k[2], k[3], kmax));
+      // as if all quartets were of this class: they share the compute units
+      dense.push_back(cart_params(k[0], k[1], k[2], k[3], kmax, d, limit, &dp) &&
+                      cart_route(tps.back(), dp, (double)nquartets, work[c][1] / work[c][0], work[c][2] / work[c][0],
+                                 d->cus));
+      dps.push_back(dp);
       tcs.push_back(tile_costs(tps.back()));
     }
+    // The two kernels of a plan of both kinds run one after the other, each for as long
+    // as its longest tile takes: where few quartets make that the time, all take one
+    // (60 quartets of f and g, 2 primitives at most: 420 us in both, 253 in one).
+    const auto any = [&](char x) { return std::find(dense.begin(), dense.end(), x) != dense.end(); };
+    if (any(0) && any(1)) {
+      double sum[3] = {}, most[3] = {};  // both kinds: grouped, dense; all grouped
+      for (int64_t q = 0; q < nquartets; ++q) {
+        const int c = qcls[q];
+        const double kk = (double)nprim[4 * q + 2] * nprim[4 * q + 3], kbkk = kk * nprim[4 * q] * nprim[4 * q + 1];
+        for (const TileCost& t : tcs[c]) {
+          const double us = grouped_us(kbkk, kk, t.quartet, t.ket);
+          for (int x : {0, 2})
+            if (x == 2 || !dense[c]) sum[x] += us, most[x] = std::max(most[x], us);
+        }
+        if (dense[c]) {
+          const double us = dense_us(dps[c], kbkk, kk);
+          sum[1] += us * dps[c].nrt, most[1] = std::max(most[1], us);
+        }
+      }
+      double us[3];
+      for (int x = 0; x < 3; ++x) us[x] = std::max(most[x], sum[x] / d->cus + 0.5 * most[x]);
+      if (us[2] + kGroupedLaunch < us[0] + us[1] + kGroupedLaunch + kDenseLaunch)
+        std::fill(dense.begin(), dense.end(), (char)0);
+    }
+  }
   p->nclasses = (int)keys.size();
   if (coul)
     for (const JParams& c : jps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
   else if (solid)
     for (const ClassParams& c : cps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
   else
-    for (const TileParams& c : tps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
+    for (size_t c = 0; c < keys.size(); ++c) {
+      int& lds = dense[c] ? p->cart_lds : p->lds_bytes;
+      lds = std::max(lds, dense[c] ? dps[c].lds_bytes : tps[c].lds_bytes);
+    }
 
   // output offsets in input order, and work items with their cost
   p->qoff.resize(nquartets);
   int64_t off = 0;
-  std::vector<int2> items;
-  std::vector<double> cost;
+  std::vector<int2> items, cart_items;
+  std::vector<double> cost, cart_cost;
   for (int64_t q = 0; q < nquartets; ++q) {
     const double kb = (double)nprim[4 * q] * nprim[4 * q + 1], kk = (double)nprim[4 * q + 2] * nprim[4 * q + 3];
     p->qoff[q] = off;
@@ -1086,7 +1218,7 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     }
     const ClassParams& c = cps[qcls[q]];
     off += (int64_t)c.nab * c.ncd;
-    if (!solid) {
+    if (!solid && !dense[qcls[q]]) {
       const std::vector<TileCost>& t = tcs[qcls[q]];
       for (size_t rt = 0; rt < t.size(); ++rt) {
         cost.push_back(kb * kk * t[rt].quartet + kk * t[rt].ket + 4000.0);
@@ -1094,28 +1226,32 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
       }
       continue;
     }
-    for (int rt = 0; rt < c.nrt; ++rt) {
-      const int rows = 16 * std::min(c.rb, (c.nab - rt * c.rb * 16 + 15) / 16);
+    const ClassParams& dc = solid ? c : dps[qcls[q]];
+    for (int rt = 0; rt < dc.nrt; ++rt) {
+      const int rows = 16 * std::min(dc.rb, (dc.nab - rt * dc.rb * 16 + 15) / 16);
       // MFMA cycles of the two transforms at 128 FLOP/clk per CU, plus a
       // latency-bound estimate for Boys and the recursion per primitive quartet
-      const double g1 = 2.0 * rows * c.np4 * 16.0 * c.nqb * kb * kk;
-      const double g2 = 2.0 * rows * c.nq4 * 16.0 * c.ncdb * kk;
-      cost.push_back((g1 + g2) / 128.0 + kb * kk * (8000.0 + 4.0 * nherm(c.L)) + 4000.0);
-      items.push_back(make_int2((int)q, rt | (qcls[q] << 16)));
+      const double g1 = 2.0 * rows * dc.np4 * 16.0 * dc.nqb * kb * kk;
+      const double g2 = 2.0 * rows * dc.nq4 * 16.0 * dc.ncdb * kk;
+      (solid ? cost : cart_cost).push_back((g1 + g2) / 128.0 + kb * kk * (8000.0 + 4.0 * nherm(dc.L)) + 4000.0);
+      (solid ? items : cart_items).push_back(make_int2((int)q, rt | (qcls[q] << 16)));
     }
   }
   p->out_size = off;
-  const std::vector<int2> sorted = largest_first(items, cost);
-  if (sorted.size() > (size_t)INT32_MAX) {
+  std::vector<int2> sorted = largest_first(items, cost);
+  const std::vector<int2> cart_sorted = largest_first(cart_items, cart_cost);
+  if (sorted.size() + cart_sorted.size() > (size_t)INT32_MAX) {
     plan_free(p);
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "too many work items");
   }
+  p->ncart_items = (int)cart_sorted.size();
   p->nitems = (int)sorted.size();
 
   int ncu = 0, per_cu = 0;
   HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, p->device));
   const hipError_t oe = p->coul ? plan_coulomb_occupancy(p->lds_bytes, &per_cu)
-                        : p->solid ? plan_solid_occupancy(p->pairs, p->lds_bytes, &per_cu)
+                        : p->solid ? (p->pairs ? plan_occupancy_solidp(p->lds_bytes, &per_cu)
+                                              : plan_occupancy_solid(p->lds_bytes, &per_cu))
                         : p->pairs ? (p->f32 ? plan_occupancy_f32p(p->lds_bytes, &per_cu)
                                            : plan_occupancy_f64p(p->lds_bytes, &per_cu))
                                  : (p->f32 ? plan_occupancy_f32(p->lds_bytes, &per_cu)
@@ -1123,19 +1259,30 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   if (oe != hipSuccess || per_cu < 1) per_cu = 1;
   p->grid = (int)std::min<int64_t>(std::max(p->nitems, 1), (int64_t)ncu * per_cu);
 
+  if (p->ncart_items > 0) {
+    if ((p->pairs ? plan_occupancy_cartp(p->cart_lds, &per_cu) : plan_occupancy_cart(p->cart_lds, &per_cu)) != hipSuccess ||
+        per_cu < 1)
+      per_cu = 1;
+    p->cart_grid = (int)std::min<int64_t>(p->ncart_items, (int64_t)ncu * per_cu);
+    sorted.insert(sorted.end(), cart_sorted.begin(), cart_sorted.end());
+  }
+
   const void* params = coul ? (const void*)jps.data() : solid ? (const void*)cps.data() : (const void*)tps.data();
   const size_t params_size = keys.size() * (coul ? sizeof(JParams) : solid ? sizeof(ClassParams) : sizeof(TileParams));
   const bool ok = hipMalloc(&p->d_classes, std::max<size_t>(1, params_size)) == hipSuccess &&
                   hipMalloc(&p->d_items, std::max<size_t>(1, sorted.size()) * sizeof(int2)) == hipSuccess &&
                   hipMalloc(&p->d_qoff, std::max<int64_t>(1, nquartets) * sizeof(int64_t)) == hipSuccess &&
                   hipMalloc(&p->d_nprim, std::max<int64_t>(1, 4 * nquartets) * sizeof(int32_t)) == hipSuccess &&
-                  hipMalloc(&p->d_counter, 64) == hipSuccess;
+                  hipMalloc(&p->d_counter, 64) == hipSuccess &&
+                  (p->ncart_items == 0 || hipMalloc(&p->d_cart, keys.size() * sizeof(ClassParams)) == hipSuccess);
   if (!ok) {
     plan_free(p);
     return fail(ERI4_ERROR_OUT_OF_MEMORY, "device allocation for the plan failed");
   }
   hipError_t e = hipSuccess;
   if (params_size) e = hipMemcpy(p->d_classes, params, params_size, hipMemcpyHostToDevice);
+  if (e == hipSuccess && p->ncart_items > 0)
+    e = hipMemcpy(p->d_cart, dps.data(), keys.size() * sizeof(ClassParams), hipMemcpyHostToDevice);
   if (e == hipSuccess && !sorted.empty())
     e = hipMemcpy(p->d_items, sorted.data(), sorted.size() * sizeof(int2), hipMemcpyHostToDevice);
   if (e == hipSuccess && nquartets > 0)
@@ -1242,7 +1389,7 @@ eri4_status eri4_plan_output_offsets(eri4_plan plan, int64_t* offsets) {
 // Enqueue the counter reset and the persistent kernel of a plan.
 static eri4_status plan_launch(eri4_plan plan, const Shells& shl, double* work, int64_t work_size, double* out,
                                hipStream_t stream) {
-  if (plan->nitems == 0) return ERI4_SUCCESS;
+  if (plan->nitems + plan->ncart_items == 0) return ERI4_SUCCESS;
   if (!shl.centers || !shl.exps || !shl.coefs || !out || (plan->pairs && (!shl.kcenters || !shl.kexps || !shl.kcoefs)))
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "NULL buffer pointer");
   if (plan->solid && (!work || work_size < plan->work))
@@ -1264,8 +1411,16 @@ static eri4_status plan_launch(eri4_plan plan, const Shells& shl, double* work, 
                    out};
   const Tables t = d->tables();
   const dim3 grid(plan->grid);
+  if (plan->ncart_items > 0) {
+    const PlanArgs c{plan->d_cart, plan->d_items + plan->nitems, plan->ncart_items, plan->d_qoff, plan->d_nprim,
+                     plan->d_counter + 1, shl, out};
+    HIP_TRY(plan->pairs ? plan_launch_cartp(dim3(plan->cart_grid), plan->cart_lds, stream, t, c)
+                        : plan_launch_cart(dim3(plan->cart_grid), plan->cart_lds, stream, t, c));
+    if (plan->nitems == 0) return ERI4_SUCCESS;
+  }
   if (plan->solid)
-    HIP_TRY(plan_solid_launch(plan->pairs, grid, plan->lds_bytes, stream, t, a, plan->nbra, plan->d_hoff, work));
+    HIP_TRY(plan->pairs ? plan_launch_solidp(grid, plan->lds_bytes, stream, t, a, plan->nbra, plan->d_hoff, work)
+                        : plan_launch_solid(grid, plan->lds_bytes, stream, t, a, plan->nbra, plan->d_hoff, work));
   else if (plan->pairs)
     HIP_TRY(plan->f32 ? plan_launch_f32p(grid, plan->lds_bytes, stream, t, a)
                       : plan_launch_f64p(grid, plan->lds_bytes, stream, t, a));

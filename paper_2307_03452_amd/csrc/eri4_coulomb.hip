@@ -299,7 +299,7 @@ __device__ __forceinline__ void jengine_quartet(
   const int hs = 64 * h_steps(L), nkl = Kc * Kd;
   int eb, ek;
   tiny_exponents(s.t.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
-  const double scaleb = ldexp(1.0, -eb), scalek = ldexp(1.0, -ek), unscale = ldexp(1.0, eb + ek);
+  eb = __builtin_amdgcn_readfirstlane(eb), ek = __builtin_amdgcn_readfirstlane(ek);
   // [0]^(m) (wave 0) and the per-axis tables (the other waves)
   auto prepare = [&](int ij, int kl, int ti) {
     const int i = ij / Kb, j = ij - (ij / Kb) * Kb, k = kl / Kd, l = kl - (kl / Kd) * Kd;
@@ -319,7 +319,7 @@ __device__ __forceinline__ void jengine_quartet(
         }
         const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
         const double wk = co[2 * kmax + k] * co[3 * kmax + l] * exp(-zc * zd * iq * cd2);
-        s.t.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
+        s.t.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, ldexp(wb, -eb) * ldexp(wk, -ek), tb.boys);
       }
     } else {
       build_htables(s.t.h, hs, tb.hcoef, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
@@ -461,7 +461,7 @@ __device__ __forceinline__ void jengine_quartet(
   }
 #pragma unroll
   for (int r = 0; r < kJAb; ++r)
-    if (tid + r * kThreads < cp.nab) outJ[tid + r * kThreads] = J[r] * unscale;
+    if (tid + r * kThreads < cp.nab) outJ[tid + r * kThreads] = ldexp(J[r], eb + ek);
 }
 
 // Batch form: one workgroup per (quartet q0 + blockIdx.x / kmax^2, bra
@@ -558,8 +558,8 @@ hipError_t plan_coulomb_occupancy(int lds_bytes, int* per_cu) {
                                                       lds_bytes);
 }
 
-// The three steps of a Coulomb pair-list plan (after the caller reset the work
-// counter): dket of every ket entry, the persistent kernel, the reduction.
+// The steps of a Coulomb pair-list plan (after the caller reset the work counter):
+// dket of every ket entry, the persistent kernel, the reduction.
 hipError_t plan_coulomb_launch(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a,
                                int nbra, int kmax, int uv, const int32_t* pl, const int32_t* pn, const double* ket_dens,
                                const int64_t* doff, const int64_t* dkoff, const int64_t* joff, double* dket,
@@ -569,11 +569,13 @@ hipError_t plan_coulomb_launch(dim3 grid, int lds_bytes, hipStream_t s, const Ta
                      kmax, t.ttab + uv, pl + 2 * nbra, pn + 2 * nbra, x.kcenters, x.kexps, ket_dens, doff, dkoff, dket);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(eri4_plan_coulomb_kernel, grid, dim3(kThreads), lds_bytes, s, (const JParams*)a.classes, a.items, a.nitems,
-                     a.qoff, a.counter, t, x.centers, x.exps, x.coefs, a.nprim, jpart, x.kcenters, x.kexps, x.kcoefs,
-                     x.nket, dkoff, dket);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (a.nitems > 0) {
+    hipLaunchKernelGGL(eri4_plan_coulomb_kernel, grid, dim3(kThreads), lds_bytes, s, (const JParams*)a.classes, a.items,
+                       a.nitems, a.qoff, a.counter, t, x.centers, x.exps, x.coefs, a.nprim, jpart, x.kcenters, x.kexps,
+                       x.kcoefs, x.nket, dkoff, dket);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(coulomb_reduce_kernel, dim3((unsigned)nbra), dim3(256), 0, s, x.nket, pl, a.qoff, jpart, joff,
                      out);
   return hipGetLastError();

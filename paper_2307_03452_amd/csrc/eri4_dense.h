@@ -1,9 +1,11 @@
-// eri4_dense.h -- gfx950 device code of the solid-harmonic integrals and of the
-// exchange contraction (FP64): one workgroup computes one tile of bra rows of one
-// quartet by a dense first transform, [ab|q] += sum_p A_ab^p [p+q], whose
-// operand [p+q] is read from [r] in LDS as the sum of two offsets.  (The rows of
-// a solid harmonic mix all x exponents, and a tile of the exchange contraction
-// holds all a of one b, so that the grouping of eri4_tile.h does not apply.)
+// eri4_dense.h -- gfx950 device code of the solid-harmonic integrals, of the
+// exchange contraction and of small classes of Cartesian integrals (FP64): one
+// workgroup computes one tile of bra rows of one quartet by a dense first transform,
+// [ab|q] += sum_p A_ab^p [p+q], whose operand [p+q] is read from [r] in LDS as the sum
+// of two offsets.  (The rows of a solid harmonic mix all x exponents, and a tile of
+// the exchange contraction holds all a of one b, so that the grouping of eri4_tile.h
+// does not apply; of small classes it leaves groups of a few rows in blocks of 16, and
+// a recursion for every two or three of them.)
 #pragma once
 #include "eri4_tile.h"
 
@@ -119,8 +121,9 @@ __device__ __forceinline__ void gemm1_h(typename Acc<false>::type (&acc)[NR][NC]
 // H_cd (Hk: this lane's element of column block 0, k step 0), then the output
 // write, as gemm2_group.  The operands of eight steps are requested while the eight
 // before them run: requested one step ahead, a tile of (ii|ii) waited 75 000 of the
-// 120 000 cycles of this transform.
-template <int NR, int NC>
+// 120 000 cycles of this transform
+// (U; four of low orders).
+template <int NR, int NC, int U>
 __device__ __forceinline__ void gemm2_group_h(const ClassParams& cp, const double* __restrict__ X,
                                               const double* __restrict__ Hk, int cb0, int row0,
                                               double* __restrict__ outq, bool first, double unscale,
@@ -133,7 +136,6 @@ __device__ __forceinline__ void gemm2_group_h(const ClassParams& cp, const doubl
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[r][c] = acc_zero<false>();
   const int xs = cp.xs, nq4 = cp.nq4;
-  constexpr int U = 8;
   double b[U][NC], bn[U][NC];
   auto fetch = [&](double (&x)[U][NC], int kk) {
 #pragma unroll
@@ -196,18 +198,18 @@ __device__ __forceinline__ void exch_row(const ClassParams& cp, int pr, int& ia,
 // y blocks of one ket pair: NR * ncc blocks of row block r = blk / ncc and column
 // block cc = blk % ncc (c = 16 cc + lane % 16),
 //   y[r][cc] += sum_q X[row block r][q] F^b[q][cc],  b the row block's shell-b component.
-// Up to eight blocks: 8 / blocks waves share the k of one (exch_split); else wave w
-// takes blocks w and w + 8.  F^b of this ket pair at F + (b * ncc + cc) * nq4 * 16
-// in operand order (k step s, lane l: F^b[4 s + l / 16][16 cc + l % 16]); eight
-// steps of it are requested while the eight before them run.
-__device__ __forceinline__ int exch_split(int nblk) { return nblk <= kWaves ? kWaves / nblk : 1; }
+// Up to eight blocks of many k: 8 / blocks waves share the k of one (exch_split; of few
+// steps, adding the parts took longer than the steps: 4000 (ss|ss) 114 us, 92 without);
+// else wave w takes blocks w and w + 8.  F^b of this ket pair at F + (b * ncc + cc) * nq4 * 16
+// in operand order (k step s, lane l: F^b[4 s + l / 16][16 cc + l % 16]); U
+// steps of it are requested while the U before them run.
+__device__ __forceinline__ int exch_split(int nblk, int nq4) { return nblk <= kWaves && nq4 > 64 ? kWaves / nblk : 1; }
 
-template <int NR>
+template <int NR, int U>
 __device__ __forceinline__ void exch_gemm(const ClassParams& cp, const double* __restrict__ X,
                                           const double* __restrict__ F, int row0, int wave, int lane, d4 (&yacc)[2]) {
-  constexpr int U = 8;
   const int g = lane >> 4, n = lane & 15;
-  const int ncc = (cp.nc + 15) / 16, nblk = NR * ncc, split = exch_split(nblk);
+  const int ncc = (cp.nc + 15) / 16, nblk = NR * ncc, split = exch_split(nblk, cp.nq4);
   const int P = exch_rows_per_b(cp);
   const int64_t fs = (int64_t)cp.nq4 * 16;
   const int steps = cp.nq4 >> 2;
@@ -252,7 +254,7 @@ template <int NR>
 __device__ __forceinline__ void exch_store(const ClassParams& cp, const d4 (&yacc)[2], double scale,
                                            double* __restrict__ outq, double* parts, int row0, int wave, int lane) {
   const int g = lane >> 4, n = lane & 15;
-  const int ncc = (cp.nc + 15) / 16, nblk = NR * ncc, split = exch_split(nblk);
+  const int ncc = (cp.nc + 15) / 16, nblk = NR * ncc, split = exch_split(nblk, cp.nq4);
   if (split > 1) {
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) parts[(wave * 4 + jj) * 64 + lane] = yacc[0][jj];
@@ -278,8 +280,9 @@ __device__ __forceinline__ void exch_store(const ClassParams& cp, const d4 (&yac
 // LDS regions of a tile (see dense_layout).
 struct DenseLds {
   TileLds t;  // shells, [0]^(m) and what the recursion's steps share with eri4_tile.h
-  double *box, *brae, *X;
+  double *box, *brae, *kete, *X;
   int2 *ptab, *qtab;
+  uint2* entl;  // recursion table of total orders up to kWaveL, in the place of rowt
 };
 
 // Tables of row (u, v) of W, the k-th, of L+1-u-v values: it lies in the tail of the
@@ -328,7 +331,8 @@ __device__ __forceinline__ void build_box(const DenseLds& s, int L, int S1, int 
 }
 
 // Everything a workgroup does after its prologue, for NR valid row blocks and
-// NC1 first-transform column blocks of this wave.  [r] comes from three products
+// NC1 first-transform column blocks of this wave.  [r] comes from one wave
+// (hermite_r_wave; LOW: total orders up to kWaveL) or from three products
 // (eri4_tile.h); W sits in the tails of [r]'s rows, so that the box needs no room
 // beside it.  Bound by the first transform's products: of a tile of (ii|ii), 216 000
 // cycles for solid harmonics, they take 143 000 (117 000 at the matrix cores' rate),
@@ -336,24 +340,30 @@ __device__ __forceinline__ void build_box(const DenseLds& s, int L, int S1, int 
 // of single primitives took 2172 us (solid) and 256 of them 3434 us (exchange) with
 // the recursion level by level and operands requested one or two steps ahead; 1682
 // and 2690 us so.
-// Solid harmonics (EXCH false): rows and columns are real solid harmonics and both
+// kDenseSolid: rows and columns are real solid harmonics and both
 // transforms read their H matrices from hb / hk (this quartet's, hbs / hks doubles
 // per primitive pair, pair (i, j) of shells with K1, K2 primitives at slot
 // i * K2 + j).
-// EXCH: no second transform; bra rows are ordered (b, a) with a padded
+// kDenseCart: E as products of 1-d tables in both transforms (gemm1_e, gemm2_group).
+// kDenseExch: no second transform; bra rows are ordered (b, a) with a padded
 // to a multiple of 16 (exch_row), so each 16-row block has one b, and [ab|q]
 // is contracted on the matrix cores with F^b[q][c] = sum_d E_cd^q D_bd of ket
 // pair (k, l) (exchange_f_kernel, at hk + (k * kmax + l) * hks in operand
 // order), accumulated over the ket pairs into y[a][c] = sum_d (ab|cd) D_bd,
 // written to outq[(b * na + a) * nc + c] for the tile's b (Cartesian).  A row
 // block holds no a with ax above that of its first, and E_ab^tuv = 0 for t > ax+bx:
-// its first transform ends with that t (of (ii|ii)'s products 23% fall away).
-template <int NR, int NC1, bool SLAB, bool EXCH>
+// its first transform ends with that t (of (ii|ii)'s products 23% fall away).  Of few
+// values of p, or of p and column blocks together, the separate ends of the row blocks
+// cost more than the products: 300 (pp|pp) 35 us cut, 34 whole, (gg|ss) 131 and 115,
+// (hh|dp) 407 and 412, (kk|ss) 1578 and 1638.
+constexpr int kCutP = 84, kCutPq = 200;
+template <int NR, int NC1, bool SLAB, int MODE, bool LOW>
 __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds& s, const Tables& tb,
                                            double* __restrict__ outq, int row0, int Ka, int Kb, int Kc, int Kd,
                                            int task, int ntask, int tid, int wave, int lane,
                                            const double* __restrict__ hb, const double* __restrict__ hk, int64_t hbs,
                                            int64_t hks) {
+  constexpr bool EXCH = MODE == kDenseExch, CART = MODE == kDenseCart;
   const int kmax = cp.kmax, L = cp.L;
   const double* A = s.t.sh;
   const double* B = s.t.sh + 3;
@@ -367,9 +377,14 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
   // each row block end
   int rowx[NR], rowy[NR], rowz[NR], kend[NR], kmin = cp.np4;
 #pragma unroll
-  for (int r = 0; r < NR && EXCH; ++r) {
+  for (int r = 0; r < NR && (EXCH || CART); ++r) {
     int ia, ib, ax, ay, az, bx, by, bz;
-    exch_row(cp, row0 + r * 16 + (lane & 15), ia, ib);
+    if constexpr (EXCH) {
+      exch_row(cp, row0 + r * 16 + (lane & 15), ia, ib);
+    } else {
+      ia = (row0 + r * 16 + (lane & 15)) / cp.nb;
+      ib = row0 + r * 16 + (lane & 15) - ia * cp.nb;
+    }
     if (ia < cp.na && ib < cp.nb) {
       cart_of(cp.la, ia, ax, ay, az);
       cart_of(cp.lb, ib, bx, by, bz);
@@ -382,6 +397,8 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
       rowy[r] = cp.tbaxis + zr;
       rowz[r] = 2 * cp.tbaxis + zr;
     }
+    kend[r] = cp.np4;
+    if (CART || cp.np4 <= kCutP || cp.np4 * cp.nqb <= kCutPq) continue;
     exch_row(cp, row0 + r * 16, ia, ib);  // the block's first row: the largest ax
     kend[r] = 0;
     if (ib < cp.nb) {
@@ -403,9 +420,10 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
   const int ncbw = (wave < cp.ncdb) ? (cp.ncdb - wave + 7) / 8 : 0;  // output column blocks of this wave
 
   const int hs = 64 * h_steps(L);
-  const bool over = cp.o_brae == cp.o_zt;
-  int eb, ek;
-  tiny_exponents(s.t.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
+  const bool over = !LOW && cp.o_brae == cp.o_zt;
+  // (of low orders the transforms amplify little, and it would be a tenth of a tile's time)
+  int eb = 0, ek = 0;
+  if constexpr (!LOW) tiny_exponents(s.t.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
   const double scaleb = ldexp(1.0, -eb), scalek = ldexp(1.0, -ek), unscale = ldexp(1.0, eb + ek);
   // EXCH: y blocks (row block, 16 columns c) of this wave, kept over the ket pairs
   d4 yacc[2] = {acc_zero<false>(), acc_zero<false>()};
@@ -423,16 +441,16 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
       int ti = tid;  // opaque, as in tile_body
       asm volatile("" : "+v"(ti));
       const int la_ = ti & 63;
-      // [0]^(m) (wave 0) and the per-axis tables, with room the bra tables too (the
-      // other waves); [r] of order 0 and 1 without products
-      double pq[3];
+      // [0]^(m), of low orders [r] (wave 0) and the per-axis tables, with room the bra
+      // tables too, and for kDenseCart at first the ket tables (the other waves)
       {
         const double za = ex[i], zb = ex[kmax + j], zc = ex[2 * kmax + k], zd = ex[3 * kmax + l];
-        const double iz = 1.0 / (za + zb), iq = 1.0 / (zc + zd);
+        double pq[3];
+        if constexpr (!LOW) {
+          const double iz = 1.0 / (za + zb), iq = 1.0 / (zc + zd);
 #pragma unroll
-        for (int x = 0; x < 3; ++x) pq[x] = (za * A[x] + zb * B[x]) * iz - (zc * C[x] + zd * D[x]) * iq;
-        if (wave == 0) {
-          if (la_ <= L) {
+          for (int x = 0; x < 3; ++x) pq[x] = (za * A[x] + zb * B[x]) * iz - (zc * C[x] + zd * D[x]) * iq;
+          if (wave == 0 && la_ <= L) {
             double ab2 = 0.0, cd2 = 0.0, r2 = 0.0;
 #pragma unroll
             for (int x = 0; x < 3; ++x) {
@@ -444,22 +462,45 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
             const double wk = co[2 * kmax + k] * co[3 * kmax + l] * exp(-zc * zd * iq * cd2);
             s.t.baseM[la_] = hermite_base_m(la_, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
           }
-        } else {
-          if (L > 1)
+        } else if (wave == 0) {
+          // the bra pair in lanes 0..31, the ket pair in the others
+          const int ket = la_ >> 5;
+          const double z1 = ket ? zc : za, z2 = ket ? zd : zb, z = z1 + z2, iz = 1.0 / z;
+          const double c = ket ? co[2 * kmax + k] * co[3 * kmax + l] : co[i] * co[kmax + j];
+          double p[3], d2 = 0.0, r2 = 0.0;
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            const double s1 = A[6 * ket + x], s2 = A[6 * ket + 3 + x];
+            p[x] = (z1 * s1 + z2 * s2) * iz;
+            d2 += (s1 - s2) * (s1 - s2);
+          }
+          const double w = c * exp(-z1 * z2 * iz * d2), zo = __shfl_xor(z, 32), wo = __shfl_xor(w, 32);
+#pragma unroll
+          for (int x = 0; x < 3; ++x) {
+            const double o = __shfl_xor(p[x], 32);
+            pq[x] = ket ? o - p[x] : p[x] - o;
+            r2 += pq[x] * pq[x];
+          }
+          if (la_ <= L) s.t.baseM[la_] = hermite_base_m(la_, z, zo, r2, w * wo, tb.boys);
+          hermite_r_wave(s.box, s.t.baseM, L, pq[0], pq[1], pq[2], s.entl, la_);
+        }
+        if (wave != 0) {
+          if constexpr (!LOW)
             build_htables(s.t.h, hs, tb.hcoef, pq[0], pq[1], pq[2], ti - 64, kThreads - 64);
-          if (EXCH && !over) {
+          if (MODE != kDenseSolid && !over) {
             build_etab_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, (ti >> 4) - 4,
                             kWaves * 4 - 4, la_ & 15);
             if (wave == kWaves - 1) zero_rows(s.brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, la_, 64);
           }
+          if (CART && ij == 0) {
+            build_etab_rows(s.kete, cp.lc, cp.ld, cp.tkrow, cp.tkaxis, zc, zd, C, D, true, (ti >> 4) - 4,
+                            kWaves * 4 - 4, la_ & 15);
+            if (wave == kWaves - 1) zero_rows(s.kete, cp.lc, cp.ld, cp.tkrow, cp.tkaxis, la_, 64);
+          }
         }
       }
       __syncthreads();
-      if (L <= 1) {
-        if (ti <= 3 * L)
-          s.box[ti == 0 ? 0 : r_offset(SLAB, L, ti == 1, ti == 2, ti == 3)] =
-              ti == 0 ? s.t.baseM[0] : (ti == 1 ? pq[0] : ti == 2 ? pq[1] : pq[2]) * s.t.baseM[1];
-      } else {
+      if constexpr (!LOW) {
         if (wave < 3) {
           const int jb = wave == 2, ub = wave == 1;
           if (L >= 16 * (jb + ub)) build_zt(s.t, s.t.h + 2 * hs, L, jb, ub, la_);
@@ -468,8 +509,8 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
         build_w(s.t, s.box, s.t.h + hs, L, task, ntask, la_);
         __syncthreads();
         build_box<SLAB>(s, L, cp.S1, cp.S2, task, ntask, la_);
+        __syncthreads();
       }
-      __syncthreads();
       // first transform, accumulated over ij: [ab|q] += A_ab^p [p|q]
       if constexpr (EXCH) {
         if (over) {  // the bra tables over zt and the per-axis tables
@@ -481,18 +522,21 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
         if constexpr (NC1 > 0) {
           gemm1_e<NR, NC1, SLAB>(acc1, s.brae, s.box, s.ptab, rowx, rowy, rowz, offq, tq, 0, kmin, L,
                                             cp.S1, lane);
+          if (kmin < cp.np4) {
 #pragma unroll
-          for (int r = 0; r < NR; ++r) {
-            typename Acc<false>::type a[1][NC1];
-            const int x[1] = {rowx[r]}, y[1] = {rowy[r]}, z[1] = {rowz[r]};
+            for (int r = 0; r < NR; ++r) {
+              typename Acc<false>::type a[1][NC1];
+              const int x[1] = {rowx[r]}, y[1] = {rowy[r]}, z[1] = {rowz[r]};
 #pragma unroll
-            for (int c = 0; c < NC1; ++c) a[0][c] = acc1[r][c];
-            gemm1_e<1, NC1, SLAB>(a, s.brae, s.box, s.ptab, x, y, z, offq, tq, kmin, kend[r], L, cp.S1,
-                                             lane);
+              for (int c = 0; c < NC1; ++c) a[0][c] = acc1[r][c];
+              gemm1_e<1, NC1, SLAB>(a, s.brae, s.box, s.ptab, x, y, z, offq, tq, kmin, kend[r], L, cp.S1, lane);
 #pragma unroll
-            for (int c = 0; c < NC1; ++c) acc1[r][c] = a[0][c];
+              for (int c = 0; c < NC1; ++c) acc1[r][c] = a[0][c];
+            }
           }
         }
+      } else if constexpr (CART && NC1 > 0) {
+        gemm1_e<NR, NC1, SLAB>(acc1, s.brae, s.box, s.ptab, rowx, rowy, rowz, offq, tq, 0, cp.np4, L, cp.S1, lane);
       } else if constexpr (NC1 > 0) {
         gemm1_h<NR, NC1, SLAB>(acc1, hb + (i * Kb + j) * hbs + (row0 / 16) * (cp.np4 * 16) + lane, s.box, s.ptab,
                                offq, tq, cp.np4, L, cp.S1, lane);
@@ -515,22 +559,36 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
     __syncthreads();
     if constexpr (EXCH) {
       // y[a][c] += sum_q [ab|q] F^b[q][c] for this ket pair
-      exch_gemm<NR>(cp, s.X, hk + (k * kmax + l) * hks, row0, wave, lane, yacc);
+      const double* f = hk + (k * kmax + l) * hks;
+      if (LOW && cp.nq4 <= 32)
+        exch_gemm<NR, 2>(cp, s.X, f, row0, wave, lane, yacc);
+      else
+        exch_gemm<NR, 8>(cp, s.X, f, row0, wave, lane, yacc);
     } else {
       // second transform, written to HBM (accumulated over kl); groups of four
       // column blocks (2 with four row blocks, for the accumulators)
       constexpr int G2 = NR >= 4 ? 2 : 4;
-      const double* hkp = hk + (k * Kd + l) * hks + lane;
+      const double* hkp = CART ? nullptr : hk + (k * Kd + l) * hks + lane;
       for (int g0 = 0; g0 < ncbw; g0 += G2) {
         const int ng = min(G2, ncbw - g0);
         const int cb0 = wave + 8 * g0;
         const bool first = kl == 0;
+        auto group = [&](auto nc, int cb) {
+          if constexpr (CART)
+            gemm2_group<NR, decltype(nc)::value, 8>(cp, s.X, s.kete, s.qtab, cb, row0, outq, first, lane, unscale);
+          else if (LOW)
+            gemm2_group_h<NR, decltype(nc)::value, 4>(cp, s.X, hkp, cb, row0, outq, first, unscale, lane);
+          else
+            gemm2_group_h<NR, decltype(nc)::value, 8>(cp, s.X, hkp, cb, row0, outq, first, unscale, lane);
+        };
+        const std::integral_constant<int, 1> one;
+        const std::integral_constant<int, 2> two;
         if (ng >= 2)
-          gemm2_group_h<NR, 2>(cp, s.X, hkp, cb0, row0, outq, first, unscale, lane);
+          group(two, cb0);
         else
-          gemm2_group_h<NR, 1>(cp, s.X, hkp, cb0, row0, outq, first, unscale, lane);
-        if (ng == 3) gemm2_group_h<NR, 1>(cp, s.X, hkp, cb0 + 16, row0, outq, first, unscale, lane);
-        if (ng == 4) gemm2_group_h<NR, 2>(cp, s.X, hkp, cb0 + 16, row0, outq, first, unscale, lane);
+          group(one, cb0);
+        if (ng == 3) group(one, cb0 + 16);
+        if (ng == 4) group(two, cb0 + 16);
       }
     }
     __syncthreads();
@@ -540,8 +598,8 @@ __device__ __forceinline__ void dense_body(const ClassParams& cp, const DenseLds
 
 // All the work of one tile: quartet q, bra rows rt*RB*16.., whose integrals
 // start at outq.  Called by every thread of the workgroup; ends with a barrier.
-// PAIRS and the shell arrays: as load_shells.  EXCH, hb, hk: as dense_body.
-template <int RB, bool SLAB, bool PAIRS, bool EXCH>
+// PAIRS and the shell arrays: as load_shells.  MODE, hb, hk: as dense_body.
+template <int RB, bool SLAB, bool PAIRS, int MODE, bool LOW>
 __device__ __forceinline__ void dense_tile(const ClassParams& cp, unsigned char* lds, const Tables& tb,
                                            const double* __restrict__ centers, const double* __restrict__ exps,
                                            const double* __restrict__ coefs, const int32_t* __restrict__ nprim,
@@ -550,6 +608,7 @@ __device__ __forceinline__ void dense_tile(const ClassParams& cp, unsigned char*
                                            const double* __restrict__ kcoefs, int64_t nket,
                                            const double* __restrict__ hb, const double* __restrict__ hk, int64_t hbs,
                                            int64_t hks) {
+  constexpr bool EXCH = MODE == kDenseExch;
   const int kmax = cp.kmax, L = cp.L;
   DenseLds s;
   s.t.sh = (double*)(lds + cp.o_shell);
@@ -563,15 +622,22 @@ __device__ __forceinline__ void dense_tile(const ClassParams& cp, unsigned char*
   s.qtab = (int2*)(lds + cp.o_qtab);
   s.box = (double*)(lds + cp.o_union);
   s.brae = (double*)(lds + cp.o_brae);
+  s.kete = (double*)(lds + cp.o_kete);
+  s.entl = (uint2*)(lds + cp.o_rowt);
   s.X = (double*)(lds + cp.o_union);
   int* shn = (int*)(s.t.sh + 12 + 8 * kmax);
   load_shells<PAIRS>(s.t.sh, shn, kmax, centers, exps, coefs, nprim, q, kcenters, kexps, kcoefs, nket, tid);
   build_htab(s.ptab, cp.Lb, cp.np, cp.np4, cp.S1, cp.S2, SLAB, tid);
   build_htab(s.qtab, cp.Lk, cp.nq, 16 * cp.nqb, cp.S1, cp.S2, SLAB, tid);
-  if (tid < nuv(L)) w_row<SLAB>(s.t, tb.ttab + cp.o_uv, L, cp.S1, tid);
-  // this wave's tasks of W and [r], one per lane
-  const int ntask = (cp.ntask - wave + kWaves - 1) / kWaves;
-  const int task = lane < ntask ? (int)tb.ttab[cp.o_task + wave + kWaves * lane] : 0;
+  // tables of the recursion; this wave's tasks of W and [r], one per lane
+  int ntask = 0, task = 0;
+  if constexpr (LOW) {
+    if (tid < nherm(L)) s.entl[tid] = tb.rtab[cp.rtab_off + tid];
+  } else {
+    if (tid < nuv(L)) w_row<SLAB>(s.t, tb.ttab + cp.o_uv, L, cp.S1, tid);
+    ntask = (cp.ntask - wave + kWaves - 1) / kWaves;
+    task = lane < ntask ? (int)tb.ttab[cp.o_task + wave + kWaves * lane] : 0;
+  }
   __syncthreads();
 
   const int Ka = shn[0], Kb = shn[1], Kc = shn[2], Kd = shn[3];
@@ -597,7 +663,7 @@ __device__ __forceinline__ void dense_tile(const ClassParams& cp, unsigned char*
   const int nrows_all = EXCH ? cp.nb * 16 * ((cp.na + 15) / 16) : cp.nab;           // (padded) bra rows
   const int nrv = min(RB, (nrows_all - row0 + 15) / 16);                          // valid row blocks of this tile
 #define BODY(NR, NC1)                                                                                          \
-  dense_body<NR, NC1, SLAB, EXCH>(cp, s, tb, outq, row0, Ka, Kb, Kc, Kd, task, ntask, tid, wave, lane, hb, hk, \
+  dense_body<NR, NC1, SLAB, MODE, LOW>(cp, s, tb, outq, row0, Ka, Kb, Kc, Kd, task, ntask, tid, wave, lane, hb, hk, \
                                   hbs, hks)
   constexpr int NR2 = RB >= 2 ? 2 : 1;
   if constexpr (RB == 4) {

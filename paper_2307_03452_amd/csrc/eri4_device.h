@@ -249,6 +249,45 @@ __device__ void hermite_r_lds(double* R, const double* baseM, int L, const doubl
   }
 }
 
+// [r] of total order L <= kWaveL by eq. (md1) for decreasing m, by one wave (entries e =
+// lane + 64 k of the table): the waves of a workgroup need no barrier until it is done,
+// where the three products of higher orders take one each.  Measured, 300 quartets of
+// 81 primitive quartets of solid (ps|ps): 454 us with all waves level by level, 572
+// with the products, 371 so.
+constexpr int kWaveRE = (nherm(kWaveL) + 63) / 64;
+__device__ __forceinline__ void hermite_r_wave(double* R, const double* baseM, int L, double px, double py, double pz,
+                                               const uint2* entl, int lane) {
+  uint2 en[kWaveRE];
+#pragma unroll
+  for (int k = 0; k < kWaveRE; ++k) en[k] = entl[min(lane + 64 * k, nherm(L) - 1)];
+  // (memory operations of one wave on LDS run in order; the compiler keeps theirs)
+  auto order = []() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  };
+  order();
+  if (lane == 0) R[0] = baseM[L];
+  order();
+#pragma unroll 1
+  for (int m = L - 1; m >= 0; --m) {
+    const int nact = nherm(L - m);
+    double nv[kWaveRE];
+#pragma unroll
+    for (int k = 0; k < kWaveRE; ++k) {
+      const int o1 = (int)(en[k].x >> 16), o2 = (int)(en[k].y & 0xffffu);
+      const int dir = (int)((en[k].y >> 16) & 3u), ri = (int)(en[k].y >> 18);
+      const double c1 = dir == 0 ? px : (dir == 1 ? py : pz);
+      nv[k] = lane + 64 * k < nact ? c1 * R[o1] + (double)max(ri - 1, 0) * R[o2] : 0.0;
+    }
+    const double b = baseM[m];
+    order();
+#pragma unroll
+    for (int k = 0; k < kWaveRE; ++k)
+      if (lane + 64 * k < nact) R[en[k].x & 0xffffu] = k == 0 && lane == 0 ? b : nv[k];
+    order();
+  }
+}
+
 template <int NE>
 __device__ __forceinline__ void load_rtab(uint2 (&ent)[NE], const uint2* __restrict__ rt, int L, int tid) {
   const int n = nherm(L);
@@ -324,7 +363,8 @@ __device__ __forceinline__ void gemm1_range(d4 (&acc)[NR][NC], const double* __r
 template <int NR, int NC, int CSTRIDE>
 __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double* __restrict__ X,
                                             const double* __restrict__ kete, const int2* __restrict__ qtab,
-                                            int cb0, int row0, double* __restrict__ outq, bool first, int lane) {
+                                            int cb0, int row0, double* __restrict__ outq, bool first, int lane,
+                                            double unscale = 1.0) {
   const int g = lane >> 4, n = lane & 15;
   int kx[NC], ky[NC], kz[NC];
 #pragma unroll
@@ -411,7 +451,7 @@ __device__ __forceinline__ void gemm2_group(const ClassParams& cp, const double*
         const int ab = row0 + r * 16 + acc_row<false>(jj, g);
         if (ab < cp.nab && cd < cp.ncd) {
           double* o = outq + (int64_t)ab * cp.ncd + cd;
-          const double v = acc[r][c][jj];
+          const double v = acc[r][c][jj] * unscale;
           if (first)
             __builtin_nontemporal_store(v, o);
           else
@@ -473,7 +513,7 @@ __device__ __forceinline__ void tiny_exponents(const double* sh, int kmax, int K
       const double d = sh[6 * side + x] - sh[6 * side + 3 + x];
       r2 += d * d;
     }
-    e[side] = -1.4426950408889634 * (z1 * z2 / (z1 + z2) * r2);  // log2
+    e[side] = -1.4426950408889634 * (z1 * z2 * __builtin_amdgcn_rcp(z1 + z2) * r2);  // log2 (seven digits will do)
   }
   eb = ek = 0;
   if (e[0] + e[1] < -600.0) {

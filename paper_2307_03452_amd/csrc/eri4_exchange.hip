@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kThreads, 1) void exchange_f_kernel(
 
 // One workgroup = one quartet x one tile of RB*16 bra rows in (b, a) order
 // (dense_tile); the tile's y^b rows go to part + q * nb * na * nc.
-template <int RB, bool SLAB>
+template <int RB, bool SLAB, bool LOW>
 __global__ __launch_bounds__(kThreads, 1) void eri4_exchange_kernel(
     const ClassParams cp, const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps,
     const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ part, int64_t q0,
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kThreads, 1) void eri4_exchange_kernel(
   const int64_t q = q0 + i;
   const int rt = blockIdx.x % cp.nrt;
   const int64_t kk2 = (int64_t)cp.kmax * cp.kmax;
-  dense_tile<RB, SLAB, false, true>(cp, lds, tb, centers, exps, coefs, nprim,
+  dense_tile<RB, SLAB, false, kDenseExch, LOW>(cp, lds, tb, centers, exps, coefs, nprim,
                                     part + i * (int64_t)cp.nb * cp.na * cp.nc, q, rt, tid, wave, lane, nullptr,
                                     nullptr, nullptr, 0, nullptr, fb + i * kk2 * fss, 0, fss);
 }
@@ -154,11 +154,11 @@ __global__ void exchange_reduce_kernel(const ClassParams cp, const double* __res
   }
 }
 
-template <int RB, bool SLAB>
+template <int RB, bool SLAB, bool LOW>
 hipError_t exchange_launch_t(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
                              const double* exps, const double* coefs, const int32_t* nprim, double* part, int64_t q0,
                              const double* fb, int64_t fss) {
-  hipLaunchKernelGGL((eri4_exchange_kernel<RB, SLAB>), grid, dim3(kThreads), p.lds_bytes, s, p, t, centers, exps,
+  hipLaunchKernelGGL((eri4_exchange_kernel<RB, SLAB, LOW>), grid, dim3(kThreads), p.lds_bytes, s, p, t, centers, exps,
                      coefs, nprim, part, q0, fb, fss);
   return hipGetLastError();
 }
@@ -166,9 +166,10 @@ hipError_t exchange_launch_t(const ClassParams& p, dim3 grid, hipStream_t s, con
 }  // namespace
 
 hipError_t exchange_set_attrs() {
-  const void* k[5] = {(const void*)eri4_exchange_kernel<1, false>, (const void*)eri4_exchange_kernel<2, false>,
-                      (const void*)eri4_exchange_kernel<4, false>, (const void*)eri4_exchange_kernel<1, true>,
-                      (const void*)eri4_exchange_kernel<2, true>};
+#define K(RB, SLAB, LOW) (const void*)eri4_exchange_kernel<RB, SLAB, LOW>
+  const void* k[8] = {K(1, false, false), K(2, false, false), K(4, false, false), K(1, true, false),
+                      K(2, true, false),  K(1, false, true),  K(2, false, true),  K(4, false, true)};
+#undef K
   for (const void* f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     if (e != hipSuccess) return e;
@@ -189,11 +190,13 @@ hipError_t exchange_launch(const ClassParams& p, int64_t nq, hipStream_t s, cons
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)(nq * p.nrt));
   const int64_t fss = fbs * p.nb;  // doubles per ket pair slot
-#define L(RB, SLAB) exchange_launch_t<RB, SLAB>(p, grid, s, t, centers, exps, coefs, nprim, part, q0, fb, fss)
+#define L(RB, SLAB, LOW) exchange_launch_t<RB, SLAB, LOW>(p, grid, s, t, centers, exps, coefs, nprim, part, q0, fb, fss)
   if (p.slab)
-    e = p.rb == 2 ? L(2, true) : L(1, true);
+    e = p.rb == 2 ? L(2, true, false) : L(1, true, false);
+  else if (p.L <= kWaveL)
+    e = p.rb == 4 ? L(4, false, true) : p.rb == 2 ? L(2, false, true) : L(1, false, true);
   else
-    e = p.rb == 4 ? L(4, false) : p.rb == 2 ? L(2, false) : L(1, false);
+    e = p.rb == 4 ? L(4, false, false) : p.rb == 2 ? L(2, false, false) : L(1, false, false);
 #undef L
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(exchange_reduce_kernel, dim3((unsigned)nq), dim3(256), 0, s, p, part, out, q0);

@@ -122,7 +122,8 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
 constexpr int kRPerThread = (nherm(kMaxL) + kThreads - 1) / kThreads;  // 9, slab layout (L <= 28)
 constexpr int kBoxLMax = 24;                                              // box layout only up to here
-constexpr int kRPerBox = (nherm(kBoxLMax) + kThreads - 1) / kThreads;     // 6
+constexpr int kDenseSolid = 0, kDenseExch = 1, kDenseCart = 2;  // what a tile of eri4_dense.h computes
+constexpr int kWaveL = 8;  // total orders whose recursion one wave runs (eri4_dense.h)
 constexpr int kMaxC1 = 6;  // first-transform column blocks per wave (L_ket <= 14)
 // Layouts of [r] that a tile choice may name: kLayBox, kLaySlab, and kLayBox2, the box
 // where LDS had room for two of them (total order up to kBox2LMax): the recursion

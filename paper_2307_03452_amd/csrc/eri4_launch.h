@@ -25,6 +25,11 @@ hipError_t fused_set_attrs();
 hipError_t fused_launch(const TileParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
                         const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0);
 
+// The same by dense tiles (eri4_dense.hip), for classes with cart_params.
+hipError_t cart_set_attrs();
+hipError_t cart_launch(const ClassParams& p, int64_t nq, hipStream_t s, const Tables& t, const double* centers,
+                       const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0);
+
 // One wave per quartet (eri4_small.hip) for classes whose shells all have
 // l <= kSmallLMax: p from small_params (rb = bra row blocks per pass).
 hipError_t small_set_attrs();
@@ -102,10 +107,14 @@ struct PlanArgs {
 // contraction lengths per entry; bra entries first for pair-list plans, bra
 // and ket pair of each quartet alternating for quartet plans; hoff: where each
 // entry's H starts in h), then the persistent kernel that reads it.
-hipError_t plan_solid_set_attrs();
-hipError_t plan_solid_occupancy(bool pairs, int lds_bytes, int* per_cu);
-hipError_t plan_solid_launch(bool pairs, dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a,
-                             int64_t nbra, const int64_t* hoff, const double* h);
+#define ERI4_PLAN_SOLID_ENTRIES(sfx)                                                                          \
+  hipError_t plan_set_attrs_##sfx();                                                                         \
+  hipError_t plan_occupancy_##sfx(int lds_bytes, int* per_cu);                                               \
+  hipError_t plan_launch_##sfx(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a, \
+                               int64_t nbra, const int64_t* hoff, const double* h);
+ERI4_PLAN_SOLID_ENTRIES(solid)
+ERI4_PLAN_SOLID_ENTRIES(solidp)
+#undef ERI4_PLAN_SOLID_ENTRIES
 hipError_t plan_coulomb_set_attrs();
 hipError_t plan_coulomb_occupancy(int lds_bytes, int* per_cu);
 hipError_t plan_coulomb_launch(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a,
@@ -126,6 +135,9 @@ ERI4_PLAN_KERNEL_ENTRIES(f64)
 ERI4_PLAN_KERNEL_ENTRIES(f32)
 ERI4_PLAN_KERNEL_ENTRIES(f64p)
 ERI4_PLAN_KERNEL_ENTRIES(f32p)
+// the items that run as dense tiles (classes: ClassParams)
+ERI4_PLAN_KERNEL_ENTRIES(cart)
+ERI4_PLAN_KERNEL_ENTRIES(cartp)
 #undef ERI4_PLAN_KERNEL_ENTRIES
 
 }  // namespace eri4

@@ -241,7 +241,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const double flim = far_limit(A, B);
   int eb, ek;
   tiny_exponents(s.sh, kmax, Ka, Kb, Kc, Kd, eb, ek);
-  const double scaleb = ldexp(1.0, -eb), scalek = ldexp(1.0, -ek), unscale = ldexp(1.0, eb + ek);
+  eb = __builtin_amdgcn_readfirstlane(eb), ek = __builtin_amdgcn_readfirstlane(ek);
+  const double unscale = ldexp(1.0, eb + ek);
   const __amdgpu_buffer_rsrc_t rsrc = out_rsrc(outq, cp.nab * cp.ncd);
   const int nij = Ka * Kb;
   int step = 0;  // primitive quartets so far: which of the two buffers
@@ -266,10 +267,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         }
         const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
         const double wk = co[2 * kmax + k] * co[3 * kmax + l] * exp(-zc * zd * iq * cd2);
-        s.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, (wb * scaleb) * (wk * scalek), tb.boys);
+        s.baseM[ti & 63] = hermite_base_m(ti & 63, za + zb, zc + zd, r2, ldexp(wb, -eb) * ldexp(wk, -ek), tb.boys);
       }
     } else {
-      build_htables(h_of(st), hs, tb.hcoef, pq[0], pq[1], pq[2], ti, kThreads - 64, flim);
+      build_htables<false>(h_of(st), hs, tb.hcoef, pq[0], pq[1], pq[2], ti, kThreads - 64, flim);
       build_etab_rows(brae_of(st), la, lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, ti >> 4, kWaves * 4 - 4, ti & 15);
     }
   };

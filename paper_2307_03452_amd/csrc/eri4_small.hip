@@ -157,7 +157,7 @@ __global__ __launch_bounds__(kSmallThreads) __attribute__((amdgpu_waves_per_eu(s
           const double wb = co[i] * co[kmax + j] * exp(-za * zb * iz * ab2);
           s.t.baseM[ln] = hermite_base_m(ln, za + zb, zc + zd, r2, wb * wk, tb.boys);
         }
-        build_htables(s.t.h, hs, tb.hcoef, pq[0], pq[1], pq[2], ln, kSmallThreads);
+        build_htables<false>(s.t.h, hs, tb.hcoef, pq[0], pq[1], pq[2], ln, kSmallThreads);
         build_etab_rows(brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, za, zb, A, B, false, ln >> 4, 4, ln & 15);
         zero_rows(brae, cp.la, cp.lb, cp.tbrow, cp.tbaxis, ln, kSmallThreads);
         __syncthreads();

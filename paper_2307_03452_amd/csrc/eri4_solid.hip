@@ -198,64 +198,11 @@ __global__ __launch_bounds__(kThreads, 1) void solid_hpairs_kernel(
           h + hoff[p] + (int64_t)(i * K2 + j) * nunits * 16 * nk4, nunits, nk4, dyn, tid);
 }
 
-// Persistent kernel of a solid-harmonic plan: the work loop of
-// eri4_plan_kernel, both transforms reading the H matrices built by
-// solid_hpairs_kernel.  PAIRS: shells from the bra and ket lists, H of the
-// quartet's bra entry at h + hoff[q / nket] and of its ket entry at h +
-// hoff[nbra + q % nket]; otherwise shells from the quartet arrays and H at h +
-// hoff[2q] (bra) and h + hoff[2q + 1] (ket).
-template <bool PAIRS>
-__global__ __launch_bounds__(kThreads, 1) void eri4_plan_solid_kernel(
-    const ClassParams* __restrict__ classes, const int2* __restrict__ items, int nitems,
-    const int64_t* __restrict__ qoff, const int32_t* __restrict__ nprim, int* __restrict__ counter,
-    const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps, const double* __restrict__ coefs, double* __restrict__ out,
-    const double* __restrict__ kcenters, const double* __restrict__ kexps, const double* __restrict__ kcoefs,
-    int64_t nket, int64_t nbra, const int64_t* __restrict__ hoff, const double* __restrict__ h) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  __shared__ int next_item;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (;;) {
-    if (tid == 0) next_item = atomicAdd(counter, 1);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(next_item);
-    __syncthreads();
-    if (it >= nitems) break;
-    const int2 w = items[it];
-    const int q = __builtin_amdgcn_readfirstlane(w.x);
-    const int rc = __builtin_amdgcn_readfirstlane(w.y);
-    const ClassParams cp = classes[rc >> 16];
-    const int rt = rc & 0xffff;
-    double* oq = out + qoff[q];
-    const double* hb;
-    const double* hk;
-    if constexpr (PAIRS) {
-      const int64_t ib = q / nket, ik = q - ib * nket;
-      hb = h + hoff[ib];
-      hk = h + hoff[nbra + ik];
-    } else {
-      hb = h + hoff[2 * (int64_t)q];
-      hk = h + hoff[2 * (int64_t)q + 1];
-    }
-    const int64_t hbs = (int64_t)solid_pair_units(cp.la, cp.lb, false) * 16 * cp.np4;
-    const int64_t hks = (int64_t)cp.ncdb * 16 * cp.nq4;
-#define T(RB, SLAB)                                                                                             \
-  dense_tile<RB, SLAB, PAIRS, false>(cp, lds, tb, centers, exps, coefs, nprim, oq, q, rt, tid, wave, lane, kcenters, \
-                                     kexps, kcoefs, nket, hb, hk, hbs, hks)
-    if (cp.slab) {
-      if (cp.rb == 2) T(2, true); else T(1, true);
-    } else {
-      if (cp.rb == 4) T(4, false); else if (cp.rb == 2) T(2, false); else T(1, false);
-    }
-#undef T
-  }
-}
-
 // Solid-harmonic output, one class: one workgroup per tile of RB*16 rows over real
 // solid harmonics (cp.nab = (2la+1)(2lb+1), cp.ncd = (2lc+1)(2ld+1)).  The H
 // matrices of quartet q0 + i sit at hbra + i * kmax^2 * hbs and hket + i * kmax^2 *
 // hks (solid_h_kernel).
-template <int RB, bool SLAB>
+template <int RB, bool SLAB, bool LOW>
 __global__ __launch_bounds__(kThreads, 1) void eri4_solid_kernel(
     const ClassParams cp, const Tables tb, const double* __restrict__ centers, const double* __restrict__ exps,
     const double* __restrict__ coefs, const int32_t* __restrict__ nprim, double* __restrict__ out, int64_t q0,
@@ -267,49 +214,21 @@ __global__ __launch_bounds__(kThreads, 1) void eri4_solid_kernel(
   const int64_t q = q0 + i;
   const int rt = blockIdx.x % cp.nrt;
   const int64_t kk2 = (int64_t)cp.kmax * cp.kmax;
-  dense_tile<RB, SLAB, false, false>(cp, lds, tb, centers, exps, coefs, nprim,
+  dense_tile<RB, SLAB, false, kDenseSolid, LOW>(cp, lds, tb, centers, exps, coefs, nprim,
                                      out + q * (int64_t)cp.nab * cp.ncd, q, rt, tid, wave, lane, nullptr, nullptr,
                                      nullptr, 0, hbra + i * kk2 * hbs, hket + i * kk2 * hks, hbs, hks);
 }
 
-template <int RB, bool SLAB>
+template <int RB, bool SLAB, bool LOW>
 hipError_t solid_launch_t(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
                           const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0,
                           const double* hbra, const double* hket, int64_t hbs, int64_t hks) {
-  hipLaunchKernelGGL((eri4_solid_kernel<RB, SLAB>), grid, dim3(kThreads), p.lds_bytes, s, p, t, centers, exps, coefs,
+  hipLaunchKernelGGL((eri4_solid_kernel<RB, SLAB, LOW>), grid, dim3(kThreads), p.lds_bytes, s, p, t, centers, exps, coefs,
                      nprim, out, q0, hbra, hket, hbs, hks);
   return hipGetLastError();
 }
 
 }  // namespace
-
-hipError_t plan_solid_set_attrs() {
-  hipError_t e = hipFuncSetAttribute((const void*)eri4_plan_solid_kernel<true>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes - 64);
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void*)eri4_plan_solid_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             kMaxLdsBytes - 64);
-}
-
-hipError_t plan_solid_occupancy(bool pairs, int lds_bytes, int* per_cu) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      per_cu, pairs ? (const void*)eri4_plan_solid_kernel<true> : (const void*)eri4_plan_solid_kernel<false>, kThreads,
-      lds_bytes);
-}
-
-hipError_t plan_solid_launch(bool pairs, dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a,
-                             int64_t nbra, const int64_t* hoff, const double* h) {
-  const Shells& x = a.shells;
-  if (pairs)
-    hipLaunchKernelGGL(eri4_plan_solid_kernel<true>, grid, dim3(kThreads), lds_bytes, s, (const ClassParams*)a.classes, a.items, a.nitems,
-                       a.qoff, a.nprim, a.counter, t, x.centers, x.exps, x.coefs, a.out, x.kcenters,
-                       x.kexps, x.kcoefs, x.nket, nbra, hoff, h);
-  else
-    hipLaunchKernelGGL(eri4_plan_solid_kernel<false>, grid, dim3(kThreads), lds_bytes, s, (const ClassParams*)a.classes, a.items,
-                       a.nitems, a.qoff, a.nprim, a.counter, t, x.centers, x.exps, x.coefs, a.out,
-                       nullptr, nullptr, nullptr, (int64_t)0, (int64_t)0, hoff, h);
-  return hipGetLastError();
-}
 
 hipError_t solid_hpairs_launch(int64_t nbra, int64_t nentries, int kmax, int lds, hipStream_t s, const int32_t* pl,
                                const int32_t* pn, const Shells& x, const int64_t* hoff, const double* stab,
@@ -327,9 +246,10 @@ hipError_t solid_hpairs_launch(int64_t nbra, int64_t nentries, int kmax, int lds
 }
 
 hipError_t solid_set_attrs() {
-  const void* k[5] = {(const void*)eri4_solid_kernel<1, false>, (const void*)eri4_solid_kernel<2, false>,
-                      (const void*)eri4_solid_kernel<4, false>, (const void*)eri4_solid_kernel<1, true>,
-                      (const void*)eri4_solid_kernel<2, true>};
+#define K(RB, SLAB, LOW) (const void*)eri4_solid_kernel<RB, SLAB, LOW>
+  const void* k[8] = {K(1, false, false), K(2, false, false), K(4, false, false), K(1, true, false),
+                      K(2, true, false),  K(1, false, true),  K(2, false, true),  K(4, false, true)};
+#undef K
   for (const void* f : k) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     if (e != hipSuccess) return e;
@@ -354,9 +274,11 @@ hipError_t solid_h_launch(const ClassParams& p, int64_t nq, hipStream_t s, const
 hipError_t solid_launch(const ClassParams& p, dim3 grid, hipStream_t s, const Tables& t, const double* centers,
                         const double* exps, const double* coefs, const int32_t* nprim, double* out, int64_t q0,
                         const double* hbra, const double* hket, int64_t hbs, int64_t hks) {
-#define L(RB, SLAB) solid_launch_t<RB, SLAB>(p, grid, s, t, centers, exps, coefs, nprim, out, q0, hbra, hket, hbs, hks)
-  if (p.slab) return p.rb == 2 ? L(2, true) : L(1, true);
-  return p.rb == 4 ? L(4, false) : p.rb == 2 ? L(2, false) : L(1, false);
+#define L(RB, SLAB, LOW) \
+  solid_launch_t<RB, SLAB, LOW>(p, grid, s, t, centers, exps, coefs, nprim, out, q0, hbra, hket, hbs, hks)
+  if (p.slab) return p.rb == 2 ? L(2, true, false) : L(1, true, false);
+  if (p.L <= kWaveL) return p.rb == 4 ? L(4, false, true) : p.rb == 2 ? L(2, false, true) : L(1, false, true);
+  return p.rb == 4 ? L(4, false, false) : p.rb == 2 ? L(2, false, false) : L(1, false, false);
 #undef L
 }
 

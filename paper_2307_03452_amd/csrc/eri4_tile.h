@@ -184,7 +184,9 @@ __device__ __forceinline__ double far_limit(const double* A, const double* B) {
 // t, column j) with e = 2 j - t (hcoef is 0 where that is no exponent).  A distance above
 // 2^54 counts as infinite and an entry above 2^250 as nothing: what they multiply, [0]^(j)
 // with j >= e, is then below 2^-250 of [0]^(0) or has long been rounded to 0, and 0
-// times an infinite power would be NaN.
+// times an infinite power would be NaN.  Of total orders up to 12 no entry is infinite
+// without the second (CUT false).
+template <bool CUT = true>
 __device__ __forceinline__ void build_htables(double* h, int hs, const double* __restrict__ hcoef, double px,
                                               double py, double pz, int i, int n, double lim = 0x1p54) {
   px = fabs(px) > lim ? 0.0 : px;
@@ -192,12 +194,13 @@ __device__ __forceinline__ void build_htables(double* h, int hs, const double* _
   pz = fabs(pz) > lim ? 0.0 : pz;
   auto entry = [](double c, double x, int e) {
     const double v = c * ipow(x, e);
-    return fabs(v) <= 0x1p250 ? v : 0.0;  // (an infinite power times 0, too)
+    return !CUT || fabs(v) <= 0x1p250 ? v : 0.0;  // (an infinite power times 0, too)
   };
   for (; i < hs; i += n) {
     const double c = hcoef[i];
     const int s = i >> 6;
-    const int e = max(0, (s < 4 ? 8 * s : 8 * s - 32) + 2 * ((i >> 4) & 3) - (i & 15));
+    int e = max(0, (s < 4 ? 8 * s : 8 * s - 32) + 2 * ((i >> 4) & 3) - (i & 15));
+    if (!CUT) e = min(e, 15);  // (past the rows below 16, whose coefficients are 0)
     h[i] = entry(c, px, e);
     h[hs + i] = entry(c, py, e);
     h[2 * hs + i] = entry(c, pz, e);
