@@ -14,7 +14,7 @@ STAGES_LIB = os.path.join(HERE, "liberi4_stages.so")
 OBJDIR = os.path.join(HERE, "_build")
 SOURCES = ["eri4_plan_solid.hip", "eri4_plan_solidp.hip", "eri4_plan_cart.hip", "eri4_plan_cartp.hip", "eri4_plan64.hip",
            "eri4_plan32.hip", "eri4_plan64p.hip", "eri4_plan32p.hip", "eri4_fused.hip", "eri4_quad.hip", "eri4_dense.hip",
-           "eri4_small.hip", "eri4_solid.hip", "eri4_coulomb.hip", "eri4_exchange.hip",
+           "eri4_small.hip", "eri4_solid.hip", "eri4_coulomb.hip", "eri4_coulomb_low.hip", "eri4_exchange.hip",
            "eri4.hip", "eri4_tables.cpp"]
 HEADERS = ["eri4_dense.h", "eri4_device.h", "eri4_internal.h", "eri4_launch.h", "eri4_plan.h", "eri4_plan_cart.h",
            "eri4_plan_solid.h", "eri4_tile.h"]

@@ -185,6 +185,7 @@ eri4_status set_attrs() {
   HIP_TRY(plan_set_attrs_cart());
   HIP_TRY(plan_set_attrs_cartp());
   HIP_TRY(coulomb_set_attrs());
+  HIP_TRY(coulomb_low_set_attrs());
   HIP_TRY(exchange_set_attrs());
   HIP_TRY(plan_coulomb_set_attrs());
   HIP_TRY(plan_set_attrs_f64());
@@ -789,6 +790,45 @@ JParams jengine_params(int la, int lb, int lc, int ld, int kmax) {
   return p;
 }
 
+// Parameters of the Coulomb kernels of low orders (after ensure_device); false where
+// they do not apply: above kWaveL, or with a side of l1 + l2 > 6.
+bool jlow_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d, JLowParams* out) {
+  JLowParams p{};
+  p.la = la; p.lb = lb; p.lc = lc; p.ld = ld;
+  p.Lb = la + lb; p.Lk = lc + ld; p.L = p.Lb + p.Lk;
+  if (p.L > kWaveL || p.Lb > 6 || p.Lk > 6) return false;
+  p.nb = ncart(lb); p.nd = ncart(ld);
+  p.nab = ncart(la) * p.nb; p.ncd = ncart(lc) * p.nd;
+  p.np = nherm(p.Lb); p.nq = nherm(p.Lk);
+  p.S1 = box_s1(p.L); p.S2 = box_s2(p.L);
+  p.tbrow = odd_row(p.Lb + 2); p.tkrow = odd_row(p.Lk + 2);
+  p.tbaxis = ((la + 1) * (lb + 1) + 1) * p.tbrow;
+  p.tkaxis = ((lc + 1) * (ld + 1) + 1) * p.tkrow;
+  p.kmax = kmax;
+  p.ds = 16 * ((p.nq + 15) / 16);
+  p.rtab_off = d->rstart[p.L];
+  p.o_uv = g_tix.uv;
+  int off = 0;
+  auto take = [&](int bytes) { const int o = off; off += align16(bytes); return o; };
+  take((12 + 8 * kmax) * 8 + 4 * 4);
+  p.o_ptab = take(p.np * 8);
+  p.o_qtab = take(p.nq * 4);
+  p.o_entl = take(nherm(p.L) * 8);
+  p.o_wave = off;
+  off = 0;
+  take(16 * 8);
+  p.o_r = take(std::max(r_cells(false, p.L), p.nab) * 8);
+  p.o_d = take(std::max(64, p.nq) * 8);
+  p.o_w = take(p.np * 8);
+  p.o_e = take(3 * p.tbaxis * 8);
+  p.wsize = off;
+  p.lds_bytes = p.o_wave + p.wsize;
+  *out = p;
+  return true;
+}
+// Waves of their workgroups: one per bra primitive pair, kLowWaves at most.
+int jlow_waves(int kmax) { return std::min(kLowWaves, kmax * kmax); }
+
 // Workspace doubles per primitive pair slot: dket of the ket pair, J of the bra's.
 static int64_t coulomb_slot(int la, int lb, int lc, int ld) {
   return 16 * ((nherm(lc + ld) + 15) / 16) + ncart(la) * ncart(lb);
@@ -815,8 +855,16 @@ static eri4_status coulomb_passes(int la, int lb, int lc, int ld, int64_t nquart
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "workspace of %lld doubles is below one quartet's %lld",
                 (long long)work_size, (long long)perq);
   chunk = std::min<int64_t>(chunk, ((int64_t)1 << 22) / kk2);  // grid of chunk * kmax^2 workgroups
+  JLowParams low;
+  const bool is_low = jlow_params(la, lb, lc, ld, kmax, d, &low);
   for (int64_t q0 = 0; q0 < nquartets; q0 += chunk) {
     const int64_t nq = std::min(chunk, nquartets - q0);
+    if (is_low) {
+      const hipError_t e = coulomb_low_launch(low, jlow_waves(kmax), nq, stream, d->tables(), centers, exponents,
+                                              coeffs, nprim, dens, work, out, q0);
+      if (e != hipSuccess) return fail(ERI4_ERROR_HIP, "kernel launch: %s", hipGetErrorString(e));
+      continue;
+    }
     double* part = work + nq * kk2 * p.ds;
     hipError_t e = coulomb_dket_launch(p, nq, stream, d->tables(), centers, exponents, nprim, dens, work, q0);
     if (e == hipSuccess)
@@ -953,6 +1001,9 @@ struct eri4_plan_s {
   // Cartesian plans: the items of classes that run as dense tiles, behind the others
   int ncart_items = 0, cart_lds = 0, cart_grid = 0;
   ClassParams* d_cart = nullptr;
+  // Coulomb plans: the same for the kernel of low orders
+  int nlow = 0, low_lds = 0;
+  JLowParams* d_low = nullptr;
   bool f32 = false;  // ERI4_PREC_FP32
   bool pairs = false;  // made from a bra and a ket list of shell pairs
   int64_t nbra = 0, nket = 0;
@@ -984,6 +1035,7 @@ static void plan_free(eri4_plan_s* p) {
   if (p->d_classes) (void)hipFree(p->d_classes);
   if (p->d_items) (void)hipFree(p->d_items);
   if (p->d_cart) (void)hipFree(p->d_cart);
+  if (p->d_low) (void)hipFree(p->d_low);
   if (p->d_qoff) (void)hipFree(p->d_qoff);
   if (p->d_nprim) (void)hipFree(p->d_nprim);
   if (p->d_counter) (void)hipFree(p->d_counter);
@@ -1116,10 +1168,15 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   // per group: tile height and R layout (the table's, or see pick_params)
   std::vector<ClassParams> cps(coul ? 0 : keys.size());
   std::vector<JParams> jps;
+  std::vector<JLowParams> lps;
+  std::vector<char> is_low;
   for (size_t c = 0; c < keys.size(); ++c) {
     const auto& k = keys[c];
     if (coul) {
       jps.push_back(jengine_params(k[0], k[1], k[2], k[3], kmax));
+      JLowParams lp{};
+      is_low.push_back(jlow_params(k[0], k[1], k[2], k[3], kmax, d, &lp));
+      lps.push_back(lp);
     } else if (k[4] >= 0) {
       const eri4_tile_choice& ch = choices[k[4]];
       if (!try_params(k[0], k[1], k[2], k[3], kmax, ch.rows16, ch.layout, d, limit, &cps[c])) {
@@ -1188,8 +1245,19 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     }
   }
   p->nclasses = (int)keys.size();
+  // A Coulomb plan of both kinds runs two kernels one after the other: a gain where there
+  // are quartets enough to fill the chip many times (3969 of s to f: 195 us in one, 111 in
+  // two), a loss where the longest quartet is the time (225: 39 and 51; of three primitives
+  // per shell 435 and 575)
+  if (std::find(is_low.begin(), is_low.end(), (char)0) != is_low.end() && nquartets <= 4 * (int64_t)d->cus)
+    std::fill(is_low.begin(), is_low.end(), (char)0);
   if (coul)
-    for (const JParams& c : jps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
+    for (size_t c = 0; c < keys.size(); ++c) {
+      if (is_low[c])
+        p->low_lds = std::max(p->low_lds, lps[c].lds_bytes + (jlow_waves(kmax) - 1) * lps[c].wsize);
+      else
+        p->lds_bytes = std::max(p->lds_bytes, jps[c].lds_bytes);
+    }
   else if (solid)
     for (const ClassParams& c : cps) p->lds_bytes = std::max(p->lds_bytes, c.lds_bytes);
   else
@@ -1201,8 +1269,8 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
   // output offsets in input order, and work items with their cost
   p->qoff.resize(nquartets);
   int64_t off = 0;
-  std::vector<int2> items, cart_items;
-  std::vector<double> cost, cart_cost;
+  std::vector<int2> items, cart_items, low_items;
+  std::vector<double> cost, cart_cost, low_cost;
   for (int64_t q = 0; q < nquartets; ++q) {
     const double kb = (double)nprim[4 * q] * nprim[4 * q + 1], kk = (double)nprim[4 * q + 2] * nprim[4 * q + 3];
     p->qoff[q] = off;
@@ -1211,6 +1279,11 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
       // and the matrix-vector product, per bra pair the bra transform
       const JParams& j = jps[qcls[q]];
       off += j.nab;  // J rows per quartet
+      if (is_low[qcls[q]]) {
+        low_cost.push_back(kb * kk * (4000.0 + nherm(j.L) + 10.0 * j.nq) + kb * 2000.0);
+        low_items.push_back(make_int2((int)q, qcls[q]));
+        continue;
+      }
       cost.push_back(kb * kk * (5000.0 + 2.0 * nherm(j.L) + nherm(j.Lb) * (double)j.nq / 16.0) +
                      kb * (4000.0 + 8.0 * j.nab) + 4000.0);
       items.push_back(make_int2((int)q, qcls[q] << 16));
@@ -1245,6 +1318,8 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     return fail(ERI4_ERROR_INVALID_ARGUMENT, "too many work items");
   }
   p->ncart_items = (int)cart_sorted.size();
+  const std::vector<int2> low_sorted = largest_first(low_items, low_cost);
+  p->nlow = (int)low_sorted.size();
   p->nitems = (int)sorted.size();
 
   int ncu = 0, per_cu = 0;
@@ -1266,6 +1341,7 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
     p->cart_grid = (int)std::min<int64_t>(p->ncart_items, (int64_t)ncu * per_cu);
     sorted.insert(sorted.end(), cart_sorted.begin(), cart_sorted.end());
   }
+  sorted.insert(sorted.end(), low_sorted.begin(), low_sorted.end());
 
   const void* params = coul ? (const void*)jps.data() : solid ? (const void*)cps.data() : (const void*)tps.data();
   const size_t params_size = keys.size() * (coul ? sizeof(JParams) : solid ? sizeof(ClassParams) : sizeof(TileParams));
@@ -1274,13 +1350,16 @@ static eri4_status plan_create(eri4_plan* plan, int64_t nquartets, const int32_t
                   hipMalloc(&p->d_qoff, std::max<int64_t>(1, nquartets) * sizeof(int64_t)) == hipSuccess &&
                   hipMalloc(&p->d_nprim, std::max<int64_t>(1, 4 * nquartets) * sizeof(int32_t)) == hipSuccess &&
                   hipMalloc(&p->d_counter, 64) == hipSuccess &&
-                  (p->ncart_items == 0 || hipMalloc(&p->d_cart, keys.size() * sizeof(ClassParams)) == hipSuccess);
+                  (p->ncart_items == 0 || hipMalloc(&p->d_cart, keys.size() * sizeof(ClassParams)) == hipSuccess) &&
+                  (p->nlow == 0 || hipMalloc(&p->d_low, keys.size() * sizeof(JLowParams)) == hipSuccess);
   if (!ok) {
     plan_free(p);
     return fail(ERI4_ERROR_OUT_OF_MEMORY, "device allocation for the plan failed");
   }
   hipError_t e = hipSuccess;
   if (params_size) e = hipMemcpy(p->d_classes, params, params_size, hipMemcpyHostToDevice);
+  if (e == hipSuccess && p->nlow > 0)
+    e = hipMemcpy(p->d_low, lps.data(), keys.size() * sizeof(JLowParams), hipMemcpyHostToDevice);
   if (e == hipSuccess && p->ncart_items > 0)
     e = hipMemcpy(p->d_cart, dps.data(), keys.size() * sizeof(ClassParams), hipMemcpyHostToDevice);
   if (e == hipSuccess && !sorted.empty())
@@ -1627,7 +1706,7 @@ eri4_status eri4_plan_execute_coulomb(eri4_plan plan, const double* bra_centers,
   g_err.clear();
   if (!plan) return fail(ERI4_ERROR_INVALID_ARGUMENT, "NULL plan");
   if (!plan->coul) return fail(ERI4_ERROR_INVALID_ARGUMENT, "not a Coulomb plan (eri4_plan_create_coulomb)");
-  if (plan->nitems == 0) {
+  if (plan->nitems + plan->nlow == 0) {
     // an empty ket list: every J_i is an empty sum
     if (plan->out_size == 0) return ERI4_SUCCESS;
     if (!out) return fail(ERI4_ERROR_INVALID_ARGUMENT, "NULL buffer pointer");
@@ -1656,7 +1735,9 @@ eri4_status eri4_plan_execute_coulomb(eri4_plan plan, const double* bra_centers,
                    nullptr};
   HIP_TRY(plan_coulomb_launch(dim3(plan->grid), plan->lds_bytes, stream, d->tables(), a,
                               (int)plan->nbra, plan->kmax, g_tix.uv, plan->d_pl, plan->d_pn, ket_dens, plan->d_doff,
-                              plan->d_dkoff, plan->d_joff, work, work + plan->dket_size, out));
+                              plan->d_dkoff, plan->d_joff, work, work + plan->dket_size, out,
+                              LowItems{plan->d_low, plan->d_items + plan->nitems, plan->nlow, jlow_waves(plan->kmax),
+                                       plan->low_lds}));
   return ERI4_SUCCESS;
 }
 

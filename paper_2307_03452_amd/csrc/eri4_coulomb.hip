@@ -559,11 +559,11 @@ hipError_t plan_coulomb_occupancy(int lds_bytes, int* per_cu) {
 }
 
 // The steps of a Coulomb pair-list plan (after the caller reset the work counter):
-// dket of every ket entry, the persistent kernel, the reduction.
+// dket of every ket entry, the persistent kernel and that of low orders, the reduction.
 hipError_t plan_coulomb_launch(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a,
                                int nbra, int kmax, int uv, const int32_t* pl, const int32_t* pn, const double* ket_dens,
                                const int64_t* doff, const int64_t* dkoff, const int64_t* joff, double* dket,
-                               double* jpart, double* out) {
+                               double* jpart, double* out, const LowItems& low) {
   const Shells& x = a.shells;
   hipLaunchKernelGGL(coulomb_dket_pairs_kernel, dim3((unsigned)x.nket, (unsigned)(kmax * kmax)), dim3(kThreads), 0, s,
                      kmax, t.ttab + uv, pl + 2 * nbra, pn + 2 * nbra, x.kcenters, x.kexps, ket_dens, doff, dkoff, dket);
@@ -574,6 +574,11 @@ hipError_t plan_coulomb_launch(dim3 grid, int lds_bytes, hipStream_t s, const Ta
                        a.nitems, a.qoff, a.counter, t, x.centers, x.exps, x.coefs, a.nprim, jpart, x.kcenters, x.kexps,
                        x.kcoefs, x.nket, dkoff, dket);
     e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (low.n > 0) {
+    e = plan_coulomb_low_launch(low.n, low.waves, low.lds_bytes, s, t, low.classes, low.items, a.qoff, a.nprim, x,
+                                dkoff, dket, jpart);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(coulomb_reduce_kernel, dim3((unsigned)nbra), dim3(256), 0, s, x.nket, pl, a.qoff, jpart, joff,

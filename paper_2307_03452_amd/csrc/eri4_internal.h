@@ -278,6 +278,26 @@ constexpr int kJItem = kJVrow + 32 * 4;                                // items 
 constexpr int kJEnd = kJItem + 64 * 8;
 // Reads of [r] past its rows: at most 3 rows of S <= 29 and a few values.
 constexpr int kJPad = 112;
+// The Coulomb kernels of low orders (eri4_coulomb_low.hip): total orders up to kWaveL
+// with at most kLowHerm Hermite functions on either side.
+constexpr int kLowHerm = 84;  // l1 + l2 <= 6
+constexpr int kLowAb = 100;   // (ff|: the most rows
+constexpr int kLowWaves = 8;  // waves of a workgroup, at most
+struct JLowParams {
+  int la, lb, lc, ld;
+  int nab, ncd, nb, nd;
+  int Lb, Lk, L;
+  int np, nq;
+  int S1, S2;
+  int tbrow, tbaxis, tkrow, tkaxis;
+  int kmax, ds;
+  int rtab_off, o_uv;
+  // LDS (byte offsets): shells, Hermite tables and the recursion's table, then per wave
+  // (wsize bytes from o_wave): [0]^(m), [r], dket, w, bra tables; and J (over [r])
+  int o_ptab, o_qtab, o_entl, o_wave, wsize, o_r, o_d, o_w, o_e;
+  int lds_bytes;  // of one wave; + wsize for each more
+};
+
 // Values of w, or of a density block, folded over the groups (x1, x2) of a shell
 // pair: the (u, v) of each group.
 __host__ __device__ constexpr int nfold(int l1, int l2) {

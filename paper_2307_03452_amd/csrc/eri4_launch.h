@@ -68,6 +68,13 @@ hipError_t coulomb_launch(const JParams& p, int64_t nq, hipStream_t s, const Tab
                           const double* exps, const double* coefs, const int32_t* nprim, double* part, double* out,
                           int64_t q0, const double* dket);
 
+// The same for low orders (eri4_coulomb_low.hip; p from jlow_params): dket, then one
+// workgroup of `waves` waves per quartet that writes J itself.
+hipError_t coulomb_low_set_attrs();
+hipError_t coulomb_low_launch(const JLowParams& p, int waves, int64_t nq, hipStream_t s, const Tables& t,
+                              const double* centers, const double* exps, const double* coefs, const int32_t* nprim,
+                              const double* dens, double* dket, double* out, int64_t q0);
+
 // Exchange contraction (eri4_exchange.hip): F^b of every ket primitive pair
 // and shell-b component of quartets q0..q0+nq-1 (fbs doubles each), the
 // integral kernels writing the partial rows y^b into part, and the sum over b
@@ -115,12 +122,24 @@ struct PlanArgs {
 ERI4_PLAN_SOLID_ENTRIES(solid)
 ERI4_PLAN_SOLID_ENTRIES(solidp)
 #undef ERI4_PLAN_SOLID_ENTRIES
+// The quartets of a Coulomb plan that run on the kernel of low orders.
+struct LowItems {
+  const JLowParams* classes;
+  const int2* items;
+  int n, waves, lds_bytes;
+};
 hipError_t plan_coulomb_set_attrs();
 hipError_t plan_coulomb_occupancy(int lds_bytes, int* per_cu);
 hipError_t plan_coulomb_launch(dim3 grid, int lds_bytes, hipStream_t s, const Tables& t, const PlanArgs& a,
                                int nbra, int kmax, int uv, const int32_t* pl, const int32_t* pn, const double* ket_dens,
                                const int64_t* doff, const int64_t* dkoff, const int64_t* joff, double* dket,
-                               double* jpart, double* out);
+                               double* jpart, double* out, const LowItems& low);
+// J of the quartets of items (q, class) of low orders into jpart + qoff[q], from the dket
+// that plan_coulomb_launch's first kernel wrote; lds_bytes for all waves of a workgroup.
+hipError_t plan_coulomb_low_launch(int nitems, int waves, int lds_bytes, hipStream_t s, const Tables& t,
+                                   const JLowParams* classes, const int2* items, const int64_t* qoff,
+                                   const int32_t* nprim, const Shells& x, const int64_t* dkoff, const double* dket,
+                                   double* jpart);
 // nbra < 0: the alternating (quartet) form, all entries read from x.centers, ...;
 // lds: dynamic LDS bytes, solid_h_lds of the largest entry
 hipError_t solid_hpairs_launch(int64_t nbra, int64_t nentries, int kmax, int lds, hipStream_t s, const int32_t* pl,
