@@ -416,8 +416,11 @@ eri4_status eri4_plan_execute_coulomb(eri4_plan plan, const double* bra_centers,
 
 
 /*
- * Stage entry points.  They run the same device code the fused eri4_batch
- * kernel runs for one stage, so each stage can be checked on its own.
+ * Stage entry points.  They run device code of the integral kernels for one stage,
+ * so that each can be checked on its own: the Boys function and the 1-d tables that
+ * all use, and the recursion as the solid-harmonic, exchange and dense Cartesian
+ * tiles run it (level by level in one wave up to total order 8, three products above,
+ * whose first two the grouped Cartesian and the Coulomb kernels share).
  */
 
 /* Boys function of eq. (boys), F_m(T) = int_0^1 y^(2m) exp(-T y^2) dy, for

@@ -20,7 +20,7 @@
 #include <vector>
 
 #include "eri4.h"
-#include "eri4_device.h"
+#include "eri4_dense.h"
 #include "eri4_internal.h"
 #include "eri4_launch.h"
 
@@ -43,8 +43,7 @@ __global__ void zero_fill_kernel(double* __restrict__ out, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// stage kernels (Boys function and 1-d tables: device code of the integral
-// kernels; recursion: eq. (md1) level by level, which the others hold theirs against)
+// stage kernels: the device code of the integral kernels for one stage each
 // ---------------------------------------------------------------------------
 
 __global__ void boys_kernel(int mmax, int64_t n, const double* __restrict__ T, double* __restrict__ F,
@@ -57,36 +56,67 @@ __global__ void boys_kernel(int mmax, int64_t n, const double* __restrict__ T, d
   F[g] = boys_fm(m, T[i], tab);
 }
 
+// Places in LDS (bytes) of the stage kernel of the recursion.
+struct StageR {
+  int L, ntask, o_uv, o_task, rtab_off;
+  int o_rowt, o_rs, o_rv, o_box, o_zt, o_h, lds_bytes;
+};
+
+// [r] of one primitive quartet as the tiles of eri4_dense.h form it: of orders up to
+// kWaveL by one wave, above by the three products.
+template <bool SLAB>
 __global__ __launch_bounds__(kThreads, 1) void hermite_r_kernel(
-    int L, bool slab, const double* __restrict__ zp, const double* __restrict__ zq, const double* __restrict__ P,
-    const double* __restrict__ Q, double* __restrict__ R, const double* __restrict__ boys_tab,
-    const uint2* __restrict__ rtab_L) {
+    const StageR sp, const Tables tb, const double* __restrict__ zp, const double* __restrict__ zq,
+    const double* __restrict__ P, const double* __restrict__ Q, double* __restrict__ R) {
   extern __shared__ __align__(16) unsigned char lds[];
-  double* baseM = (double*)lds;
-  double* pq = baseM + 32;
-  double* box = baseM + 36;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t it = blockIdx.x;
-  const int n1 = L + 1;
-  const double a = zp[it], b = zq[it];
-  double PQ[3];
-  for (int x = 0; x < 3; ++x) PQ[x] = P[it * 3 + x] - Q[it * 3 + x];
-  if (tid < 3) pq[tid] = PQ[tid];
-  if (tid <= L) {
-    const double rho = a * b / (a + b);
-    const double T = rho * (PQ[0] * PQ[0] + PQ[1] * PQ[1] + PQ[2] * PQ[2]);
-    double pw = 1.0;
-    for (int mm = 0; mm < tid; ++mm) pw *= -2.0 * rho;
-    baseM[tid] = pw * (2.0 * pow(M_PI, 2.5) / (a * b * sqrt(a + b))) * boys_fm(tid, T, boys_tab);
+  const int L = sp.L, n1 = L + 1, S1 = box_s1(L), S2 = box_s2(L);
+  DenseLds s;
+  s.t.baseM = (double*)lds;
+  s.t.rowt = (uint16_t*)(lds + sp.o_rowt);
+  s.t.rs = (uint32_t*)(lds + sp.o_rs);
+  s.t.rv = (uint16_t*)(lds + sp.o_rv);
+  s.t.zt = (double*)(lds + sp.o_zt);
+  s.t.h = (double*)(lds + sp.o_h);
+  s.box = (double*)(lds + sp.o_box);
+  s.entl = (uint2*)(lds + sp.o_rowt);
+  const bool low = L <= kWaveL;
+  double pq[3], r2 = 0.0;
+  for (int x = 0; x < 3; ++x) {
+    pq[x] = P[it * 3 + x] - Q[it * 3 + x];
+    r2 += pq[x] * pq[x];
   }
-  uint2 rent[kRPerThread];
-  load_rtab(rent, rtab_L, L, tid);
+  if (tid <= L) s.t.baseM[tid] = hermite_base_m(tid, zp[it], zq[it], r2, 1.0, tb.boys);
+  const int hs = 64 * h_steps(L);
+  int ntask = 0, task = 0;
+  if (low) {
+    if (tid < nherm(L)) s.entl[tid] = tb.rtab[sp.rtab_off + tid];
+  } else {
+    if (tid < nuv(L)) w_row<SLAB>(s.t, tb.ttab + sp.o_uv, L, S1, tid);
+    ntask = (sp.ntask - wave + kWaves - 1) / kWaves;
+    task = lane < ntask ? (int)tb.ttab[sp.o_task + wave + kWaves * lane] : 0;
+    if (wave > 0) build_htables(s.t.h, hs, tb.hcoef, pq[0], pq[1], pq[2], tid - 64, kThreads - 64);
+  }
   __syncthreads();
-  hermite_r_lds(box, baseM, L, pq, rent, tid);
+  if (low) {
+    if (wave == 0) hermite_r_wave(s.box, s.t.baseM, L, pq[0], pq[1], pq[2], s.entl, lane);
+  } else {
+    if (wave < 3) {
+      const int jb = wave == 2, ub = wave == 1;
+      if (L >= 16 * (jb + ub)) build_zt(s.t, s.t.h + 2 * hs, L, jb, ub, lane);
+    }
+    __syncthreads();
+    build_w(s.t, s.box, s.t.h + hs, L, task, ntask, lane);
+    __syncthreads();
+    build_box<SLAB>(s, L, S1, S2, task, ntask, lane);
+  }
+  __syncthreads();
   double* o = R + it * (int64_t)n1 * n1 * n1;
   for (int e = tid; e < n1 * n1 * n1; e += kThreads) {
     const int t = e / (n1 * n1), u = (e / n1) % n1, v = e % n1;
-    o[e] = (t + u + v <= L) ? box[r_offset(slab, L, t, u, v)] : 0.0;
+    o[e] = (t + u + v <= L) ? s.box[r_offset(SLAB, L, t, u, v)] : 0.0;
   }
 }
 
@@ -99,17 +129,7 @@ __global__ void hermite_e_kernel(int la, int lb, const double* __restrict__ za, 
   const int64_t it = blockIdx.x;
   const int trow = odd_row(la + lb + 2);
   const int taxis = ((la + 1) * (lb + 1) + 1) * trow;
-  double* pair = tabs + 3 * taxis;
-  if (lane == 0) {
-    double Av[3], Bv[3];
-    for (int x = 0; x < 3; ++x) {
-      Av[x] = A[it * 3 + x];
-      Bv[x] = B[it * 3 + x];
-    }
-    make_pair(pair, za[it], zb[it], 1.0, 1.0, Av, Bv);
-  }
-  __syncthreads();
-  build_etab(tabs, la, lb, trow, taxis, 0.5 / pair[0], pair + 5, pair + 8, false, lane);
+  build_etab_rows(tabs, la, lb, trow, taxis, za[it], zb[it], A + it * 3, B + it * 3, false, lane >> 4, 4, lane & 15);
   __syncthreads();
   const int nt = la + lb + 1;
   const int per_axis = (la + 1) * (lb + 1) * nt;
@@ -154,7 +174,7 @@ struct DeviceState {
   double* boys = nullptr;
   uint2* rtab = nullptr;
   double* stab = nullptr;  // solid-harmonic coefficients (make_solid_table)
-  int rstart[2 * (kMaxL + 1)] = {0};  // [layout][L], in uint2 entries
+  int rstart[kMaxL + 1] = {0};  // per total order, in uint2 entries
   uint32_t* ttab = nullptr;  // tables of the Cartesian integral kernels (make_tile_tables)
   double* hcoef = nullptr;
   int cus = 0;  // compute units
@@ -192,7 +212,9 @@ eri4_status set_attrs() {
   HIP_TRY(plan_set_attrs_f32());
   HIP_TRY(plan_set_attrs_f64p());
   HIP_TRY(plan_set_attrs_f32p());
-  HIP_TRY(hipFuncSetAttribute((const void*)hermite_r_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+  HIP_TRY(hipFuncSetAttribute((const void*)hermite_r_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              kMaxLdsBytes));
+  HIP_TRY(hipFuncSetAttribute((const void*)hermite_r_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               kMaxLdsBytes));
   return ERI4_SUCCESS;
 }
@@ -215,7 +237,6 @@ eri4_status ensure_device(DeviceState** st) {
       make_rtabs(rt, rs);
       make_solid_table(st);
     }
-    if ((int)rt.size() != 2 * 2 * kRtabEntries) return fail(ERI4_ERROR_INTERNAL, "recursion table size mismatch");
     if (hipMalloc(&d.boys, boys.size() * sizeof(double)) != hipSuccess)
       return fail(ERI4_ERROR_OUT_OF_MEMORY, "device allocation of the Boys table failed");
     if (hipMalloc(&d.rtab, rt.size() * sizeof(uint32_t)) != hipSuccess)
@@ -230,7 +251,7 @@ eri4_status ensure_device(DeviceState** st) {
       return fail(ERI4_ERROR_OUT_OF_MEMORY, "device allocation of the tile tables failed");
     HIP_TRY(hipMemcpy(d.ttab, g_ttab.data(), g_ttab.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(d.hcoef, hc.data(), hc.size() * sizeof(double), hipMemcpyHostToDevice));
-    for (int i = 0; i < 2 * (kMaxL + 1); ++i) d.rstart[i] = rs[i];
+    for (int i = 0; i <= kMaxL; ++i) d.rstart[i] = rs[i];
     HIP_TRY(hipGetSymbolAddress((void**)&d.scratch, HIP_SYMBOL(scratch)));
     HIP_TRY(hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, dev));
     eri4_status s = set_attrs();
@@ -286,7 +307,9 @@ ClassParams make_params(int la, int lb, int lc, int ld, int kmax, int rb, bool s
 
 // Class parameters for one tile height and R layout, if they fit (limit:
 // bytes of LDS available for the dynamic area; column blocks per wave within
-// what the kernel bodies are instantiated for).
+// what the kernel bodies are instantiated for).  The sizes and orders tested here are
+// those of make_params, an upper bound of what the kernels take (dense_layout): a tile
+// choice is accepted or refused as it always was.
 bool try_params(int la, int lb, int lc, int ld, int kmax, int rb, int lay, const DeviceState* d, int limit,
                 ClassParams* out) {
   const bool slab = lay == kLaySlab, two = lay == kLayBox2;
@@ -296,8 +319,8 @@ bool try_params(int la, int lb, int lc, int ld, int kmax, int rb, int lay, const
   ClassParams p = make_params(la, lb, lc, ld, kmax, rb, slab, two);
   const int maxc = rb == 4 ? 2 : (slab && rb == 1 ? kMaxC1 : 4);
   if (p.lds_bytes > limit || p.L > kMaxL || (p.nqb + 7) / 8 > maxc) return false;
-  if (!slab && p.L > kBoxLMax) return false;  // the box recursion holds kRPerBox entries per thread
-  p.rtab_off = d ? d->rstart[(slab ? 1 : 0) * (kMaxL + 1) + p.L] : 0;
+  if (!slab && p.L > kBoxLMax) return false;
+  p.rtab_off = d ? d->rstart[p.L] : 0;
   *out = p;
   return true;
 }
@@ -1791,10 +1814,19 @@ eri4_status eri4_hermite_r(int L, int64_t n, const double* zp, const double* zq,
   DeviceState* d;
   eri4_status s = ensure_device(&d);
   if (s != ERI4_SUCCESS) return s;
-  const bool slab = (36 + r_cells(false, L)) * 8 > kMaxLdsBytes;
-  const int lds = (36 + r_cells(slab, L)) * 8;
-  hipLaunchKernelGGL(hermite_r_kernel, dim3((unsigned)n), dim3(kThreads), lds, stream, L, slab, zp, zq, P, Q, R,
-                     d->boys, d->rtab + d->rstart[(slab ? 1 : 0) * (kMaxL + 1) + L]);
+  const bool slab = L > kBoxLMax;
+  StageR p{};
+  p.L = L;
+  p.ntask = g_tix.ntask[L]; p.o_uv = g_tix.uv; p.o_task = g_tix.task[L]; p.rtab_off = d->rstart[L];
+  p.o_rowt = 32 * 8;
+  p.o_rs = p.o_rowt + align16((L + 1) * (L + 1) * 2);
+  p.o_rv = p.o_rs + align16(nuv(L) * 4);
+  p.o_box = L <= kWaveL ? p.o_rowt + align16(nherm(L) * 8) : p.o_rv + align16(nuv(L) * 2);
+  p.o_zt = p.o_box + align16((r_cells(slab, L) + (box_s1(L) == L + 1 ? L + 1 : 0)) * 8);
+  p.o_h = p.o_zt + align16(nuv(L) * 8);
+  p.lds_bytes = p.o_h + 3 * 64 * h_steps(L) * 8;
+  const auto kernel = slab ? hermite_r_kernel<true> : hermite_r_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(kThreads), p.lds_bytes, stream, p, d->tables(), zp, zq, P, Q, R);
   HIP_TRY(hipGetLastError());
   return ERI4_SUCCESS;
 }
@@ -1812,7 +1844,7 @@ eri4_status eri4_hermite_e(int la, int lb, int64_t n, const double* za, const do
   eri4_status s = ensure_device(&d);
   if (s != ERI4_SUCCESS) return s;
   const int trow = odd_row(la + lb + 2);
-  const int lds = (3 * ((la + 1) * (lb + 1) + 1) * trow + 16) * 8;
+  const int lds = 3 * ((la + 1) * (lb + 1) + 1) * trow * 8;
   hipLaunchKernelGGL(hermite_e_kernel, dim3((unsigned)n), dim3(64), lds, stream, la, lb, za, zb, A, B, E);
   HIP_TRY(hipGetLastError());
   return ERI4_SUCCESS;

@@ -10,7 +10,7 @@
 //   (ab|cd) = sum_q E_cd^q [ab|q]                                    eq. (cd_to_hermite)
 //
 // Here: what several kernels share (matrix products, Boys function, 1-d tables,
-// Hermite index tables, shell data), the recursion of the stage kernel, and the
+// Hermite index tables, shell data), the recursion of low orders, and the
 // dense transforms of the low-l kernels.  The contraction is folded into the product dimension (Sec. 3),
 // [p|q] is gathered from [r] in LDS and never stored, the sign (-1)^|q| is part of
 // the ket tables, and the Gaussian-product prefactors and contraction coefficients
@@ -205,50 +205,6 @@ __device__ __forceinline__ void cart_of(int l, int i, int& x, int& y, int& z) {
   x = l - n;
 }
 
-// [r]^(0) for |r| <= L in LDS (box or slab layout, encoded in the table), by
-// eq. (md1) for decreasing m, overwriting [r]^(m+1) with [r]^(m).  Each level
-// reads all its operands into registers, then writes after a barrier.
-// baseM[m] holds [0]^(m); PQ (3 doubles, LDS) is P - Q.  ent[] holds this
-// thread's recursion-table entries; they are made opaque every level so that
-// only the packed words stay live, not their decoded form.
-template <int NE>
-__device__ void hermite_r_lds(double* R, const double* baseM, int L, const double* PQ, const uint2 (&ent_in)[NE],
-                              int tid) {
-  uint2 ent[NE];
-#pragma unroll
-  for (int k = 0; k < NE; ++k) ent[k] = ent_in[k];
-  if (tid == 0) R[0] = baseM[L];
-  __syncthreads();
-  const double px = PQ[0], py = PQ[1], pz = PQ[2];
-  for (int m = L - 1; m >= 0; --m) {
-    const int nact = nherm(L - m);
-    const int kact = (nact + kThreads - 1) / kThreads;  // entry slots in use at this level (uniform)
-    double nv[NE];
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-      if (k < kact) {
-        asm volatile("" : "+v"(ent[k].x), "+v"(ent[k].y));
-        const int o1 = (int)(ent[k].x >> 16);
-        const int o2 = (int)(ent[k].y & 0xffffu);
-        const int dir = (int)((ent[k].y >> 16) & 3u);
-        const int ri = (int)(ent[k].y >> 18);
-        const double c1 = dir == 0 ? px : (dir == 1 ? py : pz);
-        nv[k] = c1 * R[o1] + (double)max(ri - 1, 0) * R[o2];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NE; ++k) {
-      if (k < kact) {
-        const int e = tid + k * kThreads;
-        if (e < nact && e > 0) R[ent[k].x & 0xffffu] = nv[k];
-      }
-    }
-    if (tid == 0) R[0] = baseM[m];
-    __syncthreads();
-  }
-}
-
 // [r] of total order L <= kWaveL by eq. (md1) for decreasing m, by one wave (entries e =
 // lane + 64 k of the table): the waves of a workgroup need no barrier until it is done,
 // where the three products of higher orders take one each.  Measured, 300 quartets of
@@ -285,16 +241,6 @@ __device__ __forceinline__ void hermite_r_wave(double* R, const double* baseM, i
     for (int k = 0; k < kWaveRE; ++k)
       if (lane + 64 * k < nact) R[en[k].x & 0xffffu] = k == 0 && lane == 0 ? b : nv[k];
     order();
-  }
-}
-
-template <int NE>
-__device__ __forceinline__ void load_rtab(uint2 (&ent)[NE], const uint2* __restrict__ rt, int L, int tid) {
-  const int n = nherm(L);
-#pragma unroll
-  for (int k = 0; k < NE; ++k) {
-    const int e = tid + k * kThreads;
-    ent[k] = (e < n) ? rt[e] : make_uint2(0u, 0u);
   }
 }
 

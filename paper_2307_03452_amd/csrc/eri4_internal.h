@@ -53,14 +53,12 @@ __host__ __device__ constexpr int r_offset(bool slab, int L, int t, int u, int v
   return (slab ? slab_base(t, L, box_s1(L)) : t * box_s2(L)) + u * box_s1(L) + v;
 }
 
-// Hermite recursion tables: for each layout (0 box, 1 slab) and each L in
-// 0..kMaxL, the nherm(L) triples (t,u,v) with t+u+v <= L ordered by total
+// Hermite recursion tables (box layout): for each L in 0..kMaxL, the nherm(L) triples (t,u,v) with t+u+v <= L ordered by total
 // order, each as two 32-bit words
 //   x: offset of (t,u,v) | offset of (t,u,v) - 1_i << 16
 //   y: offset of (t,u,v) - 2*1_i (or of -1_i when r_i < 2) | i << 16 | r_i << 18
 // where i is the axis eq. (md1) raises to reach (t,u,v) (the last non-zero of
 // t, u, v).  The first entry of each table is (0,0,0) with all fields 0.
-constexpr int kRtabEntries = 35960;  // sum_{L=0}^{28} nherm(L), per layout
 
 // Solid-harmonic coefficient table (make_solid_table): per (l, m) one entry of
 // kSolidEntry doubles, the count and up to kSolidTerms (Cartesian index,
@@ -120,8 +118,7 @@ constexpr int kSmallLdsMax = 64 * 1024;
 // One workgroup computes a tile of 16 or 32 bra rows (ab) of one quartet.
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * 64;
-constexpr int kRPerThread = (nherm(kMaxL) + kThreads - 1) / kThreads;  // 9, slab layout (L <= 28)
-constexpr int kBoxLMax = 24;                                              // box layout only up to here
+constexpr int kBoxLMax = 24;  // box layout only up to here
 constexpr int kDenseSolid = 0, kDenseExch = 1, kDenseCart = 2;  // what a tile of eri4_dense.h computes
 constexpr int kWaveL = 8;  // total orders whose recursion one wave runs (eri4_dense.h)
 constexpr int kMaxC1 = 6;  // first-transform column blocks per wave (L_ket <= 14)
