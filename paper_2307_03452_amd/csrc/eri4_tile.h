@@ -107,9 +107,31 @@ __device__ __forceinline__ void zero_rows(double* E, int l1, int l2, int trow, i
   for (; i < 3 * trow; i += n) E[(i / trow) * taxis + (l1 + 1) * (l2 + 1) * trow + i % trow] = 0.0;
 }
 
+// x^e with the rounding of one operation: each product carries its error term.
+__device__ __forceinline__ double ipow_exact(double x, int e) {  // 0 <= e < 32
+  double rh = 1.0, rl = 0.0, xh = x, xl = 0.0;
+#pragma unroll
+  for (int b = 0; b < 5; ++b) {
+    if (e & (1 << b)) {
+      const double p = rh * xh;
+      rl = fma(rh, xh, -p) + (rh * xl + rl * xh);
+      rh = p;
+    }
+    const double p = xh * xh;
+    xl = fma(2.0 * xh, xl, fma(xh, xh, -p));
+    xh = p;
+  }
+  const double r = rh + rl;
+  return fabs(rh) <= 0x1p1000 ? r : rh;  // (beyond, the error terms may be infinite)
+}
+
 // [0]^(m) = (-2 rho)^m 2 pi^(5/2) / (zp zq sqrt(zp + zq)) w F_m(rho |PQ|^2) of
 // one lane m.  Above the table F_m(T) = c_m / (T^m sqrt(T)), so the powers
-// join: (-2 rho / T)^m.
+// join: (-2 rho / T)^m = (-2 / |PQ|^2)^m.  The rounding of a power's base counts m
+// times and the sums that follow amplify it, so that the base is one operation where
+// it can be and the power adds none: error of [r], relative to its largest terms, 1.02
+// to 1.07 times that of eq. (md1) level by level with plain powers of -2 rho / T (800
+// points per order 8..28, geometric mean), 0.99 to 1.03 so.
 __device__ __forceinline__ double hermite_base_m(int m, double zp, double zq, double r2, double w,
                                                  const double* __restrict__ tab) {
   const double zs = zp + zq;
@@ -121,11 +143,11 @@ __device__ __forceinline__ double hermite_base_m(int m, double zp, double zq, do
     F = boys_fm(m, T, tab);
   } else if (T >= kBoysTMax) {
     F = tab[(size_t)kBoysAsymRow * kBoysCols + m] / sqrt(T);
-    x /= T;
+    x = -2.0 / r2;
   } else {
     F = __builtin_nan("");
   }
-  return ipow(x, m) * F * pref * w;  // w last: it may be subnormal
+  return ipow_exact(x, m) * F * pref * w;  // w last: it may be subnormal
 }
 
 // The Hermite integrals and F.  Eq. (md1) applied along one axis is
