@@ -725,7 +725,8 @@ def main():
     kb = wl["K"] * wl["K"]
     flops = b.nq * metrics.md4_flops(*ls, kb, kb)
     avg_launch_s = sum(launch_ms) / len(launch_ms) / 1e3
-    achieved = flops / avg_launch_s / 1e12
+    achieved = b.nq * metrics.grouped_flops(*ls, kb, kb) / avg_launch_s / 1e12
+    dense = flops / avg_launch_s / 1e12
     rec = {
         "metric": METRIC,
         "value": ints / (wall / args.steps),
@@ -742,12 +743,15 @@ def main():
         "config": {"workload": wl["desc"], "quartets": b.nq, "K_per_shell": wl["K"],
                    "integrals_per_step": ints, "md4_flops_per_step": flops},
         "pct_fp64_peak": 100.0 * achieved / FP64_PEAK_TFLOPS,
-        "md4_tflops": achieved,
+        "md4_tflops": dense,
+        "md4_dense_equivalent_pct": 100.0 * dense / FP64_PEAK_TFLOPS,
+        "legs_pct_fp64_peak": "dense count of the paper, which the grouped products undercut",
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_PEAK_TFLOPS, "traffic": traffic_from_profiles(args.workload),
                      "kernel": KERNEL, "avg_launch_ms": avg_launch_s * 1e3,
-                     "algorithmic_unit": "MD4 matrix FLOPs per quartet x quartets per launch (dense count; products "
-                                         "with zero blocks of E are not run, so that frac may pass 1)"},
+                     "algorithmic_unit": "matrix FLOPs per quartet x quartets per launch that the grouped products "
+                                         "need (metrics.grouped_flops; the dense count of the same work is "
+                                         "md4_tflops)"},
     }
     rec["parity_max_rel_err"] = parity_sample(wl, b, out)
     legs = {"secondary": args.secondary_steps > 0, "uneven": args.uneven_steps > 0, "mixed": args.mixed_steps > 0,

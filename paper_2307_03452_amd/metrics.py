@@ -42,6 +42,21 @@ def md4_flops_split(la, lb, lc, ld, kbra: int = 1, kket: int = 1):
     return 2 * nab * (kbra * npp) * (kket * nqq), 2 * nab * (kket * nqq) * ncd
 
 
+def grouped_flops(la, lb, lc, ld, kbra: int = 1, kket: int = 1) -> int:
+    """The products of md4_flops with the factorisation of E used: rows with x exponents
+    (ax, bx) run over the (u, v) of u + v <= la + lb - ax - bx alone (their sums over t
+    are formed once per group, on the side), and the columns of the ket likewise.  No
+    padding to blocks of 16 counted."""
+    def uv(l1, l2):  # sum over the rows of a shell pair of their (u, v)
+        n = 0
+        for x1 in range(l1 + 1):
+            for x2 in range(l2 + 1):
+                m = l1 + l2 - x1 - x2
+                n += (l1 - x1 + 1) * (l2 - x2 + 1) * (m + 1) * (m + 2) // 2
+        return n
+    return 2 * kket * (kbra * uv(la, lb) * nherm(lc + ld) + npair(la, lb) * uv(lc, ld))
+
+
 def integrals_per_quartet(la, lb, lc, ld) -> int:
     return ncart(la) * ncart(lb) * ncart(lc) * ncart(ld)
 
