@@ -1,18 +1,15 @@
-"""Autotuner for plan tiles: for each class (la lb|lc ld) and contraction-size
-bucket, time every tile choice (16 or 32 bra rows x R layout box / two boxes /
-slab) that fits, on a seeded synthetic batch of that class, and keep the
-fastest.  Writes the tile table the library reads (tune_<arch>.txt, for
-eri4_plan_create_tunefile / eri4.Plan(tune_file=...)) and a JSON record of
-every timing (tune_<arch>.json, whose "entries" eri4.Plan(tiles=...) also
-accepts).  Both are keyed by the device's architecture name (gcnArchName up to
-its first ':').
+"""Autotuner for the tiles of solid-harmonic plans: for each class (la lb|lc ld) and
+contraction-size bucket, time every tile choice (16, 32 or 64 rows x box or slab
+layout of [r]) that fits, on a seeded synthetic batch of that class, and keep the
+fastest.  (Cartesian plans check a choice and run tilings that follow from the class;
+the layout of two boxes runs as a box.)  Writes the tile table the library reads
+(tune_<arch>.txt, for eri4_plan_create_solid / eri4.SolidPlan(tune_file=...) and the
+other plans that take one) and a JSON record of every timing (tune_<arch>.json, whose
+"entries" eri4.PairPlan(tiles=...) also accepts).  Both are keyed by the device's
+architecture name (gcnArchName up to its first ':').
 
   python -m paper_2307_03452_amd.autotune [--lvals 4,5,6,7] [--only-with 7] [--buckets 0,1,2]
                                           [--merge] [--reps 2]
-
-A choice decides rows and layout of solid-harmonic plans; Cartesian plans check it
-and run one tiling of their own, so that what is timed here (Cartesian plans) no
-longer tells choices apart: the committed table is of the kernels before.
 
 The buckets are ranges of K_a K_b K_c K_d (primitive quartets per quartet);
 each is timed at one contraction length per shell inside it.  --only-with l
@@ -26,6 +23,7 @@ import itertools
 import json
 import os
 import sys
+import tempfile
 import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -36,18 +34,19 @@ BUCKETS = [(1, 1, 1), (2, 40, 2), (41, 400, 3), (401, 4096, 5)]
 # compute unit, so that the timing reflects the cost of a tile, not an idle GPU
 MIN_TILES = 512
 TILE_ROWS = 64
-CANDIDATES = [(4, "box2"), (2, "box2"), (1, "box2"), (4, "box"), (2, "box"), (1, "box"), (2, "slab"), (1, "slab")]
+CANDIDATES = [(4, "box"), (2, "box"), (1, "box"), (2, "slab"), (1, "slab")]
 
 
 def _time(plan, args, reps):
     import torch
-    out = plan.execute(*args)
+    work = torch.empty(max(1, plan.work_size), dtype=torch.float64, device="cuda")
+    out = plan.execute(*args, work=work)
     torch.cuda.synchronize()
     t0 = torch.cuda.Event(enable_timing=True)
     t1 = torch.cuda.Event(enable_timing=True)
     t0.record()
     for _ in range(reps):
-        plan.execute(*args, out=out)
+        plan.execute(*args, out=out, work=work)
     t1.record()
     torch.cuda.synchronize()
     return t0.elapsed_time(t1) / reps
@@ -62,21 +61,24 @@ def tune(classes, reps=2, log=print, buckets=BUCKETS):
     d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     entries, timings = [], []
     for ci, ls in enumerate(classes):
-        nab = ((ls[0] + 1) * (ls[0] + 2) // 2) * ((ls[1] + 1) * (ls[1] + 2) // 2)
+        nab = (2 * ls[0] + 1) * (2 * ls[1] + 1)
         nq = -(-MIN_TILES // -(-nab // TILE_ROWS))
         for kq_min, kq_max, k in buckets:
             b = inputs.class_batch(ls, nq, k, seed=7000 + 17 * ci + k, exp_range=(0.05, 200.0))
             lq = np.tile(np.array(ls, np.int32), (nq, 1))
             args = (d(b.centers), d(b.exps), d(b.coefs))
-            default = _time(eri4.Plan(lq, b.nprim, b.kmax), args, reps)
+            default = _time(eri4.SolidPlan(lq, b.nprim, b.kmax), args, reps)
             best = None
             res = {}
             for rows16, lay in CANDIDATES:
                 tile = {"l": list(ls), "kq": [kq_min, kq_max], "rows16": rows16, "layout": lay}
-                try:
-                    plan = eri4.Plan(lq, b.nprim, b.kmax, tiles=[tile])
-                except eri4.Eri4Error:
-                    continue  # does not fit
+                with tempfile.TemporaryDirectory() as tmp:
+                    path = os.path.join(tmp, "tile.txt")
+                    write_table(path, arch_name(), [tile])
+                    try:
+                        plan = eri4.SolidPlan(lq, b.nprim, b.kmax, tune_file=path)
+                    except eri4.Eri4Error:
+                        continue  # does not fit
                 ms = _time(plan, args, reps)
                 res[f"{rows16}x16/{lay}"] = ms
                 if best is None or ms < best[0]:
