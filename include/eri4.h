@@ -111,7 +111,11 @@ eri4_status eri4_init(void);
  *   out        device double [nquartets][Na][Nb][Nc][Nd], row-major, quartets in
  *              input order; every element is written
  *   stream     hipStream_t
- * Entries p >= nprim of exponents/coeffs are never read.
+ * Entries p >= nprim of exponents/coeffs do not enter the result.
+ * Small classes have several kernels, chosen by the class, nquartets, kmax and the
+ * number of compute units: the integrals of a quartet may differ in their last bits
+ * (some 1e-16 of its largest) between calls that differ in those, and between this
+ * call and a plan.  The same call gives the same bits.
  * Returns ERI4_SUCCESS, ERI4_ERROR_INVALID_ARGUMENT (bad l, sizes or NULL
  * pointers), ERI4_ERROR_UNSUPPORTED (l > ERI4_MAX_L), ERI4_ERROR_HIP or
  * ERI4_ERROR_OUT_OF_MEMORY (set-up on first use).
