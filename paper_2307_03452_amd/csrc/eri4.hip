@@ -336,7 +336,8 @@ bool pick_params(int la, int lb, int lc, int ld, int kmax, const DeviceState* d,
 }
 
 // Parameters of the Cartesian integral kernels for a class (after
-// ensure_device).  Every class with l <= ERI4_MAX_L fits: at most 149 KB.
+// ensure_device).  Every class with l <= ERI4_MAX_L fits: 159 616 bytes
+// at most, of the 163 776 that a persistent kernel's own variables leave.
 TileParams tile_params(int la, int lb, int lc, int ld, int kmax) {
   TileParams p{};
   p.la = la; p.lb = lb; p.lc = lc; p.ld = ld;

@@ -338,7 +338,7 @@ __device__ __forceinline__ void build_box(const DenseLds& s, int L, int S1, int 
 // cycles for solid harmonics, they take 143 000 (117 000 at the matrix cores' rate),
 // the second transform 58 000, the steps before them 15 000.  512 (ii|ii) quartets
 // of single primitives took 2172 us (solid) and 256 of them 3434 us (exchange) with
-// the recursion level by level and operands requested one or two steps ahead; 1682
+// the recursion level by level and operands requested one or two steps ahead; 1620
 // and 2690 us so.
 // kDenseSolid: rows and columns are real solid harmonics and both
 // transforms read their H matrices from hb / hk (this quartet's, hbs / hks doubles

@@ -209,7 +209,7 @@ __device__ __forceinline__ void cart_of(int l, int i, int& x, int& y, int& z) {
 // lane + 64 k of the table): the waves of a workgroup need no barrier until it is done,
 // where the three products of higher orders take one each.  Measured, 300 quartets of
 // 81 primitive quartets of solid (ps|ps): 454 us with all waves level by level, 572
-// with the products, 371 so.
+// with the products, 211 so (with 16 rows to a tile for 9).
 constexpr int kWaveRE = (nherm(kWaveL) + 63) / 64;
 __device__ __forceinline__ void hermite_r_wave(double* R, const double* baseM, int L, double px, double py, double pz,
                                                const uint2* entl, int lane) {

@@ -12,10 +12,11 @@
 // recursion runs while another's products occupy the matrix cores.
 //
 // The one-wave kernel is bound by the latency of its steps: 4096 (dd|dd) quartets
-// take 63 us, their products 17 us and their output 10 us.  With the recursion as
+// take 60 us, their products 17 us and their output 10 us; every quartet's wave makes
+// the index tables anew.  With the recursion as
 // three products and the 1-d tables by rows of lanes instead of level by level
 // and a table per lane, us for 1024 quartets of three primitives per shell: (pp|pp)
-// 423 -> 329, (dd|dd) 925 -> 818, (fd|fd) 2348 -> 2138; 4096 (dd|dd) 66 -> 64.
+// 423 -> 329, (dd|dd) 925 -> 818, (fd|fd) 2348 -> 2138; 4096 (dd|dd) 63 -> 60.
 #include "eri4_dense.h"
 
 namespace eri4 {
