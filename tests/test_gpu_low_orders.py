@@ -133,3 +133,37 @@ def test_lists_of_low_and_mixed_classes(lv, nb, nk):
             ref += (e * d).sum(1)
             scale += (e.abs() * d.abs()).sum(1)
         close(J[int(joff[i]):int(joff[i]) + na], ref, scale.max().item())
+
+
+def test_lists_of_two_kernels_replay_in_a_graph():
+    """Integrals and J of lists whose quartets take two persistent kernels each (a counter
+    of its own per kernel), captured and replayed with other work between: the same bits."""
+    kmax, nb, nk = 2, 40, 35
+    r = np.random.default_rng(77)
+    bl, kl = r.choice((0, 1, 4), (nb, 2)).astype(np.int32), r.choice((0, 1, 4), (nk, 2)).astype(np.int32)
+    bn, kn = r.integers(1, kmax + 1, (nb, 2)).astype(np.int32), r.integers(1, kmax + 1, (nk, 2)).astype(np.int32)
+    args = [up(x) for n in (nb, nk) for x in (r.uniform(0.0, 1.5, (n, 2, 3)), r.uniform(0.2, 5.0, (n, 2, kmax)),
+                                              r.uniform(0.3, 1.0, (n, 2, kmax)))]
+    pp, cj = eri4.PairPlan(bl, bn, kl, kn, kmax), eri4.CoulombPlan(bl, bn, kl, kn, kmax)
+    d = up(r.uniform(-1.0, 1.0, cj.ket_dens_size))
+    work = torch.empty(max(1, cj.work_size), dtype=torch.float64, device="cuda")
+    ref, jref = pp.execute(*args).clone(), cj.execute(*args, d, work=work).clone()
+    out, j = torch.zeros_like(ref), torch.zeros_like(jref)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        pp.execute(*args, out=out, stream=s)
+        cj.execute(*args, d, out=j, work=work, stream=s)
+    n, other = shells(8, kmax, 5)
+    for rep in range(3):
+        out.zero_()
+        j.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref) and torch.equal(j, jref), rep
+        eri4.batch((1, 0, 4, 0), *other)
+        pp.execute(*args)
+        torch.cuda.synchronize()
