@@ -61,7 +61,8 @@ typedef enum {
  *                   error is that of FP32 arithmetic (unit roundoff 2^-24) times
  *                   the magnitude of the terms summed, typically 1e-7 of a
  *                   quartet's largest integral; it does not reach 1e-10
- *                   absolute on quartets whose integrals exceed about 1e-3. */
+ *                   absolute on quartets whose integrals exceed about 1e-3.  Small
+ *                   classes (dense tiles) run in FP64 all the same. */
 typedef enum { ERI4_PREC_FP64 = 0, ERI4_PREC_FP32 = 1 } eri4_precision;
 
 /* Largest angular momentum per shell accepted by eri4_batch. */
@@ -235,10 +236,10 @@ eri4_status eri4_batch_solid(int la, int lb, int lc, int ld, int64_t nquartets, 
                              double* work, int64_t work_size, double* out, hipStream_t stream);
 
 /*
- * Plans -- one batch mixing classes and contraction lengths, computed by a single
- * persistent launch (Sec. 3, batched evaluation; the paper groups shell pairs of
+ * Plans -- one batch mixing classes and contraction lengths, computed by one
+ * persistent launch, or two where small classes are among them (Sec. 3, batched evaluation; the paper groups shell pairs of
  * equal total angular momentum and contraction order into lists, here the
- * grouping is per work item inside one launch).
+ * grouping is per work item inside a launch).
  *
  * eri4_plan_create reads the HOST arrays
  *   l      int32 [nquartets][4]   angular momenta of shells a, b, c, d, 0..ERI4_MAX_L
@@ -255,12 +256,12 @@ eri4_status eri4_batch_solid(int la, int lb, int lc, int ld, int64_t nquartets, 
  * own class, starts at offsets[q] doubles into out, quartets in input order
  * with no gaps; eri4_plan_output_size gives the total number of doubles.
  *
- * eri4_plan_execute enqueues on `stream` a one-thread counter reset and the
- * persistent kernel; it neither allocates nor synchronises, so it can be
+ * eri4_plan_execute enqueues on `stream` a small counter reset and the
+ * persistent kernels; it neither allocates nor synchronises, so it can be
  * captured into a HIP graph and replayed.  centers, exponents and coeffs are
  * device arrays laid out as for eri4_batch ([nquartets][4][3], [nquartets][4][kmax]);
  * the contraction lengths are the ones given at creation.  Executions of one
- * plan must not overlap in time (they share the plan's work counter); run them
+ * plan must not overlap in time (they share the plan's work counters); run them
  * on one stream or order them.  The plan must be executed on the device that
  * was current at creation.
  *

@@ -1011,7 +1011,7 @@ eri4_status eri4_batch_coulomb_static(int la, int lb, int lc, int ld, int64_t nq
 }
 
 // ---------------------------------------------------------------------------
-// plans: many classes and contraction lengths in one persistent launch
+// plans: many classes and contraction lengths in one persistent launch, or two
 // ---------------------------------------------------------------------------
 
 struct eri4_plan_s {

@@ -381,7 +381,7 @@ def hermite_e(la, lb, za, zb, A, B, E=None, stream=None):
 
 
 class Plan:
-    """A mixed-class batch computed by one persistent launch (eri4_plan_*).
+    """A mixed-class batch computed by one or two persistent launches (eri4_plan_*).
 
     lq, nprim: host int32 arrays [nq, 4] (angular momenta, contraction lengths).
     precision: "fp64" or "fp32", the arithmetic of the two transforms.
